@@ -20,13 +20,20 @@
 // Two ways to make the operands:
 //
 // Gather path (the cell size c = 16 W / G is a whole number of 1/16-px quanta
-// on both axes).  A bird at y = G c + r (0 <= r < c, in quanta) sits at the
-// same offset (n + 1/2) c - r from the centre of row G + n for every G, so its
-// factors are one row of an exact table indexed by r, built in LDS once per
-// workgroup.  Each lane of a wave builds its own v_mfma_f32_16x16x32_f16
-// operands from that table (one clamped index, one 32-bit read giving the
-// factors of two 16-row tiles), with no tile writes and no barriers; the
-// next k-step's operands are gathered while the current one's MFMAs run.
+// on both axes).  A bird at quantum q = 4 c Q + r (0 <= r < 4 c) sits at the
+// same offset (n + 1/2) c - r from the centre of cell 4 Q + n for every group
+// Q of four cells, so its factors are one row of an exact table indexed by r,
+// built in LDS once per workgroup as fp16 in 8-byte chunks of four cells.  A
+// v_mfma_f32_16x16x32_f16 operand (16 cells x 32 birds) is two transposing
+// LDS reads (ds_read_b64_tr_b16): each lane addresses one chunk of one bird,
+// one clamp and one add each, and gets four birds' factors of its own cell,
+// with no packing, no tile writes and no barriers.  (Reading a 32-bit factor
+// pair per lane and bird instead, as before, took eight clamped reads and
+// eight byte permutes for every two tiles: 256 x 8000 birds on 256 x 144
+// cells 143 us, now 79; 64 x 2000 on 128 x 72 17.2, now 11.1.)  What bounds
+// it now: a 32-bird step's reads and MFMAs do not overlap (28 and 21 of the
+// 79 us), the per-block bird test and staging (17 us), and launch, table
+// build and final sum (13 us).
 // Waves sharing a frame region add their tiles in a fixed order at the end;
 // batches with few (frame, region) pairs also split frames into bird slices
 // whose partial grids a second kernel adds in slice order.
@@ -56,6 +63,7 @@
 #include <cstring>
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -247,112 +255,110 @@ constexpr int kGWaves = 8;                 // waves per workgroup (two per SIMD)
 constexpr int kGThreads = 64 * kGWaves;
 constexpr int kGStep = 32;                 // birds per MFMA k-step (16 x 16 x 32)
 constexpr int kGRedTiles = 8;              // 16 x 16 tiles per round of the cross-wave sum
-constexpr int kGRing = 128;                // staged birds per wave (one k-step left over + one round)
-constexpr int kGMaxTableBytes = 96 * 1024; // both factor tables
+constexpr int kGPair = 2;                  // blocks of 64 birds a wave tests at a time
+constexpr int kGAhead = 2;                 // pairs of blocks loaded ahead
+constexpr int kGRing = 256;                // staged birds per wave (one k-step left over + one pair of blocks)
+constexpr int kGMaxLds = 159 * 1024;        // of a compute unit's 160 KiB
+constexpr int kGMaxTableBytes = kGMaxLds - kGWaves * kGRing * 16;  // both factor tables
+constexpr int kGMaxWindow = 30;             // window half-width, cells
 constexpr int kGMinWaveBirds = 32;         // kept birds per wave, at least, when a launch splits frames
-constexpr int32_t kGFar = 1 << 28;         // bird term that clamps every row to a zero entry
+constexpr int32_t kGFar = 1 << 28;         // bird term that clamps every cell to a zero chunk
 
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-// Factor table of one axis.  Row r (the bird's offset within its cell, in
-// quanta, 0 <= r < c) holds the factors of cells G + n, n = -j .. j, as
-// T(i) = f((i - 1 - j + 1/2) c - r) for i = 1 .. 2 j + 1 and T(i) = 0
-// elsewhere; its entry i (i = -16 .. PW - 1) is the pair (T(i), T(i + 16)), so
-// one 32-bit read gives a bird's factors for two 16-row tiles.
+// Factor table of one axis.  A bird at quantum q lies at r = q mod 4c of cell
+// group Q = q / 4c (four cells per group); row r (0 <= r < 4c) holds, as fp16,
+// the factors of cells 4 Q + n in chunks of four cells (8 bytes): chunk k has
+// n = 4 (k - j4) .. + 3, k = 0 .. nc - 1, which covers the window of every
+// bird of the row, and a cell outside its bird's window is 0.  Every row ends
+// with a zero chunk, and one more lies before row 0, so that both neighbours
+// of a row's chunks are zeros.
 struct GatherAxis {
     int32_t c;      // quanta per cell
-    int32_t j;      // window half-width, cells (2 j + 3 <= PW)
-    int32_t tab;    // byte offset of the table in LDS
+    int32_t j;      // window half-width, cells
+    int32_t j4;     // chunks before the bird's own group: ceil(j / 4)
+    int32_t nc;     // chunks per row: j4 + (j + 3) / 4 + 1
+    int32_t tab;    // byte offset of the table (its leading zero chunk) in LDS
 };
 
 struct GatherGeom {
     GatherAxis ay, ax;
-    int pw;           // 32 or 64
     float neg_k;      // -log2(e) / (2 s^2), px^-2
     float scale;      // 1 / (2 pi s^2 kLift^2)
     int table_bytes;  // the tables (one when both axes agree), 16-byte aligned
+    int red_tiles;    // tiles per round of the cross-wave sum: kGRedTiles, or 2 beside large tables
     int lds_bytes;
 };
 
 // One bird as a lane reads it: per axis the byte offset of its table row and
-// 4 (j + 17 - G), G its cell.
+// j4 - Q, Q its cell group.
 struct GBird {
     int32_t rb_y, g_y, rb_x, g_x;
 };
 
-// floor(v / c) for |v| < 2^24, 1 <= c < 2^20: a float reciprocal, then one
+__host__ __device__ __forceinline__ int32_t table_row_bytes(const GatherAxis &t) { return 8 * (t.nc + 1); }
+
+// floor(v / c) for |v| < 2^24, 1 <= c < 2^22: a float reciprocal, then one
 // correction step either way.
 __device__ __forceinline__ int32_t floor_div(int32_t v, int32_t c, float inv_c) {
-    int32_t q = (int32_t)floorf((float)v * inv_c);
-    if (q * c > v) --q;
-    else if ((q + 1) * c <= v) ++q;
-    return q;
+    const int32_t q = (int32_t)floorf((float)v * inv_c);
+    const int32_t r = v - __mul24(q, c);  // |q c| <= |v| + c: exact in 32 bits
+    return q + (int32_t)(r >= c) - (int32_t)(r < 0);
 }
 
-template <int PW>
-__device__ __forceinline__ void stage_axis(int32_t q, const GatherAxis &t, float inv_c, int32_t *rb, int32_t *g) {
+__device__ __forceinline__ void stage_axis(int32_t q, const GatherAxis &t, float inv_c4, int32_t *rb, int32_t *g) {
     // exact for |q| < 2^24; beyond that the bird is far outside any grid and
     // only the table row needs keeping in range
-    const int32_t G = floor_div(q, t.c, inv_c);
-    const int32_t r = min(max(q - G * t.c, 0), t.c - 1);
-    *rb = t.tab + 4 * (PW + 16) * r;
-    *g = 4 * (t.j + 17 - G);
+    const int32_t c4 = 4 * t.c;
+    const int32_t Q = floor_div(q, c4, inv_c4);
+    const int32_t r = min(max(q - __mul24(Q, c4), 0), c4 - 1);
+    *rb = t.tab + 8 + __mul24(table_row_bytes(t), r);
+    *g = t.j4 - Q;
 }
 
-// A bird's factor pair for tiles M and M + 1 (M even) of a lane: with
-// v = 4 (R0 + (lane & 15)) + 4 (j + 17 - G), the entry's byte offset in the
-// bird's row is clamp(v + 64 M, 0, 4 (PW + 15)) (16 rows of 4 bytes per
-// tile).  An index clamped from below or above holds two zeros, as do the
-// true factors there, so the clamp is exact.  Constant bounds make it one
-// v_med3, and the 64 M goes into the read's offset field.
-template <int M, int PW>
-__device__ __forceinline__ uint32_t factor_pair(const unsigned char *lds, int32_t rb, int32_t v) {
-    const int32_t o = min(max(v, -64 * M), 4 * (PW + 15) - 64 * M);
-    return *reinterpret_cast<const uint32_t *>(lds + rb + o + 64 * M);
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+typedef short short4v __attribute__((ext_vector_type(4)));
+
+// The MFMA operand of tile M (16 cells) for the 32 birds of a k-step.  The
+// 16 lanes of a group own eight birds (k = 8 group .. + 7); lane i of the
+// group addresses chunk i % 4 of the tile for birds i / 4 and i / 4 + 4, and
+// the transposing LDS read hands lane i the four birds' values of cell i.
+// With v = (first cell) / 4 + i % 4 + j4 - Q, the chunk's index in the bird's
+// row is clamp(v + 4 M, -1, nc): an index clamped from below or above meets a
+// zero chunk, as the true factors there are.
+struct LaneBirds {
+    int32_t rb0, v0, rb1, v1;
+};
+
+// median of v, lo and hi: clamp(v, LO, hi) for LO <= hi, as one instruction
+// (a wave-uniform bound and an inline constant)
+template <int LO>
+__device__ __forceinline__ int32_t clamp_uniform(int32_t v, int32_t hi) {
+    int32_t o;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(o) : "v"(v), "n"(LO), "s"(hi));
+    return o;
 }
 
-// Operands of tiles M and M + 1 from the pairs of eight birds.
-template <int M, int PW>
-__device__ __forceinline__ void operands(half8 &lo, half8 &hi, const int32_t (&rb)[8], const int32_t (&v)[8],
-                                         const unsigned char *lds) {
-    uint32_t w[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = factor_pair<M, PW>(lds, rb[e], v[e]);
-    uint32_t l4[4], h4[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        l4[e] = __builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x05040100u);  // low halves: tile M
-        h4[e] = __builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x07060302u);  // high halves: tile M + 1
-    }
-    lo = __builtin_bit_cast(half8, l4);
-    hi = __builtin_bit_cast(half8, h4);
+template <int M>
+__device__ __forceinline__ half4 read_chunk(const unsigned char *lds, int32_t rb, int32_t v, int32_t nc) {
+    constexpr int kLo = M & 3, kHi = M & ~3;  // inline constants reach -16: tiles 4 and up shift v first
+    const int32_t o = clamp_uniform<-1 - 4 * kLo>(v + 4 * kHi, nc - 4 * kLo);
+    typedef __attribute__((address_space(3))) short4v lds_short4;
+    return __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                         (lds_short4 *)(lds + (rb + 8 * o) + 32 * kLo)));
 }
 
-template <int TN, int PW, int N = 0>
-__device__ __forceinline__ void operands_x(half8 (&bx)[TN], const int32_t (&rb)[8], const int32_t (&v)[8],
-                                           const unsigned char *lds) {
-    if constexpr (N < TN) {
-        half8 hi;
-        operands<N, PW>(bx[N], hi, rb, v, lds);
-        if constexpr (N + 1 < TN) bx[N + 1] = hi;
-        operands_x<TN, PW, N + 2>(bx, rb, v, lds);
-    }
+template <int M>
+__device__ __forceinline__ half8 operand(const LaneBirds &b, int32_t nc, const unsigned char *lds) {
+    const half4 lo4 = read_chunk<M>(lds, b.rb0, b.v0, nc), hi4 = read_chunk<M>(lds, b.rb1, b.v1, nc);
+    return __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-template <int TM, int TN, int PW, int M = 0>
-__device__ __forceinline__ void contract_y(float4v (&acc)[TM][TN], const half8 (&bx)[TN], const int32_t (&rb)[8],
-                                           const int32_t (&v)[8], const unsigned char *lds) {
-    if constexpr (M < TM) {
-        half8 a0, a1;
-        operands<M, PW>(a0, a1, rb, v, lds);
-#pragma unroll
-        for (int n = 0; n < TN; ++n) acc[M][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, bx[n], acc[M][n], 0, 0, 0);
-        if constexpr (M + 1 < TM) {
-#pragma unroll
-            for (int n = 0; n < TN; ++n)
-                acc[M + 1][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, bx[n], acc[M + 1][n], 0, 0, 0);
-        }
-        contract_y<TM, TN, PW, M + 2>(acc, bx, rb, v, lds);
+template <int T, int N = 0>
+__device__ __forceinline__ void operands(half8 (&op)[T], const LaneBirds &b, int32_t nc, const unsigned char *lds) {
+    if constexpr (N < T) {
+        op[N] = operand<N>(b, nc, lds);
+        operands<T, N + 1>(op, b, nc, lds);
     }
 }
 
@@ -361,7 +367,8 @@ __device__ __forceinline__ void contract_y(float4v (&acc)[TM][TN], const half8 (
 // their tiles are added in a fixed order at the end (deterministic).  With
 // split > 1 the slices' grids go to `partial` for a second kernel to add.
 // The slices and waves of a (frame, region) take the frame's 64-bird blocks
-// in turn (a fixed assignment).
+// in turn (a fixed assignment).  A workgroup builds its tables once and takes
+// every gridDim.x-th group of kGWaves / waves items.
 //
 // Only birds whose window of cells (G - j .. G + j on both axes) meets the
 // region contribute to it: every other bird's factors there are table zeros.
@@ -370,112 +377,95 @@ __device__ __forceinline__ void contract_y(float4v (&acc)[TM][TN], const half8 (
 // ranks), and runs a k-step whenever 32 are staged; the last step is padded
 // with birds whose factors are all zero.  No barrier is needed until the
 // final sum.
-template <int TM, int TN, int PW>
-__global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) void density_gather_kernel(DensityArgs a, GatherGeom gg, int regions_y,
-                                                                   int regions_x, int split, int waves,
-                                                                   long long items, float *partial) {
+template <int TM, int TN>
+__global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) void density_gather_kernel(
+    DensityArgs a, GatherGeom gg, int regions_y, int regions_x, int split, int waves, uint32_t items, float *partial) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: item, bird counts and ring positions are scalars
 
-    // this wave's item and its part of the item's birds
-    const int per_wg = kGWaves / waves;
-    const long long item = (long long)blockIdx.x * per_wg + wave / waves;
     const int part = wave % waves;
-    const bool active = item < items;
     const int regions = regions_y * regions_x;
-    int f = 0, reg = 0, sl = 0;
-    if (active) {
-        sl = (int)(item % split);
-        const long long fr = item / split;
-        reg = (int)(fr % regions);
-        f = (int)(fr / regions);
-    }
-    const int row0 = (reg / regions_x) * 16 * TM;
-    const int col0 = (reg % regions_x) * 16 * TN;
-    int32_t b = 0, n = 0;
-    if (active) {
-        b = a.offsets[f];
-        const int32_t e = a.offsets[f + 1];
-        n = (b < 0 || e < b || e > a.total) ? 0 : e - b;
-    }
     // the split * waves (slice, part) units of a (frame, region) take the
     // frame's 64-bird blocks in turn: unit u = sl * waves + part reads blocks
     // u, u + split * waves, ...  Spatially grouped birds in the input then
     // spread over all units instead of loading one of them.
     const int32_t stride = 64 * split * waves;
-    const int2 *P = reinterpret_cast<const int2 *>(a.xy) + b;
 
     GBird *ring = reinterpret_cast<GBird *>(lds + gg.table_bytes) + wave * kGRing;
-    const float inv_cy = 1.0f / (float)gg.ay.c, inv_cx = 1.0f / (float)gg.ax.c;
+    const float inv_cy = 1.0f / (float)(4 * gg.ay.c), inv_cx = 1.0f / (float)(4 * gg.ax.c);
     const int r16 = lane & 15, grp = lane >> 4;
-    const int32_t yoff = 4 * (row0 + r16), xoff = 4 * (col0 + r16);
+    const int32_t ncy = gg.ay.nc, ncx = gg.ax.nc;
     // a bird in cell G meets rows [row0, row0 + 16 TM) when
-    // row0 - j <= G <= row0 + 16 TM - 1 + j, i.e. when its staged
-    // g = 4 (j + 17 - G) lies in [4 (17 - 16 TM + 1 - row0), 4 (2 j + 17 - row0)]
-    const int32_t gy_lo = 4 * (18 - 16 * TM - row0), gy_hi = 4 * (2 * gg.ay.j + 17 - row0);
-    const int32_t gx_lo = 4 * (18 - 16 * TN - col0), gx_hi = 4 * (2 * gg.ax.j + 17 - col0);
+    // row0 - j <= G <= row0 + 16 TM - 1 + j, i.e. when its quantum q lies in
+    // [(row0 - j) c, (row0 + 16 TM + j) c)  (below 2^31: c (grid + 2 j) is
+    // 16 times the frame's extent and two windows)
+    const uint32_t y_n = (uint32_t)(16 * TM + 2 * gg.ay.j) * (uint32_t)gg.ay.c;
+    const uint32_t x_n = (uint32_t)(16 * TN + 2 * gg.ax.j) * (uint32_t)gg.ax.c;
 
-    float4v acc[TM][TN];
+    // this wave's item, and its part of the item's birds: coordinates are
+    // loaded kGAhead pairs of 64-bird blocks ahead
+    const uint32_t per_wg = (uint32_t)(kGWaves / waves), groups = (items + per_wg - 1) / per_wg;
+    bool active = false;
+    uint32_t f = 0;
+    int sl = 0, row0 = 0, col0 = 0;
+    int32_t n = 0, left = 0;  // left: birds from the next block's first on
+    const int2 *P = nullptr;
+    int2 qn[kGAhead * kGPair];
+    // the u-th block on (n > 0; past the frame's end its last bird again):
+    // unconditional, so that the loads stay in flight across the blocks
+    auto load = [&](int u) {
+        return P[min((uint32_t)(n - left) + (uint32_t)(u * stride + lane), (uint32_t)(n - 1))];
+    };
+    auto begin = [&](uint32_t group) {
+        const uint32_t item = group * per_wg + (uint32_t)(wave / waves);
+        active = item < items;
+        const uint32_t it = active ? item : 0u, fr = it / (uint32_t)split;
+        sl = (int)(it - fr * (uint32_t)split);
+        f = fr / (uint32_t)regions;
+        const int reg = (int)(fr - f * (uint32_t)regions), ry = reg / regions_x;
+        row0 = ry * 16 * TM;
+        col0 = (reg - ry * regions_x) * 16 * TN;
+        const int32_t b = a.offsets[f], e = a.offsets[f + 1];
+        n = (!active || b < 0 || e < b || e > a.total) ? 0 : e - b;
+        P = reinterpret_cast<const int2 *>(a.xy) + b;
+        left = n - 64 * (sl * waves + part);
 #pragma unroll
-    for (int m = 0; m < TM; ++m)
-#pragma unroll
-        for (int t = 0; t < TN; ++t) acc[m][t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int u = 0; u < kGAhead * kGPair; ++u) qn[u] = n > 0 ? load(u) : make_int2(0, 0);
+    };
+    uint32_t group = blockIdx.x;
+    begin(group);  // the first coordinates are in flight while the tables are built
 
-    // the first round's coordinates are in flight while the tables are built
-    int2 qn = make_int2(0, 0);
-    int32_t next = 64 * (sl * waves + part);  // first bird of the next round
-    if (next + lane < n) qn = P[next + lane];
-    // the factor tables (exact: every distance is a multiple of 1/32 px).  A
-    // row's PW factors come in PW / 16 chunks of 16, one per thread, the
-    // threads of a row in adjacent lanes.  Entries -16 .. PW - 1 of a row form
-    // PW / 16 + 1 blocks of 16; block b pairs chunk b - 1 (low halves) with
-    // chunk b (high halves), chunks -1 and PW / 16 being zeros.  The thread of
-    // chunk k writes block k + 1 with its right neighbour's chunk, and the
-    // thread of chunk 0 also writes block 0.
+    // the factor tables (exact: every distance is a multiple of 1/32 px).
+    // Rows r, r + c, r + 2c and r + 3c hold the same factors shifted by one
+    // cell each: a thread makes eight factors of row r (and the three before
+    // them) and writes two chunks of all four rows.
     auto build = [&](const GatherAxis &t) {
-        constexpr int kCh = PW / 16;
-        const int k = tid % kCh;
-        for (int r0 = 0; r0 < t.c; r0 += kGThreads / kCh) {  // uniform over the workgroup
-            const int r = r0 + tid / kCh;
-            uint32_t mine[8];  // factors 16 k + 2 q (low half) and 16 k + 2 q + 1 (high half)
+        const int per = (t.nc + 2) / 2;  // pairs of chunks 2 k, 2 k + 1 <= nc, the zero chunk nc among them
+        const int rowb = table_row_bytes(t);
+        const float inv_per = 1.0f / (float)per;
+        if (tid == 0) *reinterpret_cast<uint2 *>(lds + t.tab) = make_uint2(0u, 0u);
+        for (int it = tid; it < t.c * per; it += kGThreads) {
+            const int r = floor_div(it, per, inv_per), k = it - r * per;
+            uint32_t h[11];  // factors of cells n = 8 k - 4 j4 - 3 + i of row r
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                uint32_t h[2];
+            for (int i = 0; i < 11; ++i) {
+                const int n = 8 * k - 4 * t.j4 - 3 + i;
+                const float d = (((float)n + 0.5f) * (float)t.c - (float)r) * 0.0625f;
+                const float f = kLift * __builtin_amdgcn_exp2f(d * d * gg.neg_k);
+                h[i] = __builtin_bit_cast(uint16_t, (_Float16)((n >= -t.j) & (n <= t.j) ? f : 0.0f));
+            }
+#pragma unroll
+            for (int sh = 0; sh < 4; ++sh) {
+                // cell n of row r + sh c is cell n - sh of row r
+                unsigned char *row = lds + t.tab + 8 + (r + sh * t.c) * rowb;
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const int i = 16 * k + 2 * q + u;
-                    float f = 0.0f;
-                    if (i >= 1 && i <= 2 * t.j + 1) {
-                        const float d = (((float)(i - 1 - t.j) + 0.5f) * (float)t.c - (float)r) * 0.0625f;
-                        f = kLift * __builtin_amdgcn_exp2f(d * d * gg.neg_k);
-                    }
-                    h[u] = __builtin_bit_cast(uint16_t, (_Float16)f);
-                }
-                mine[q] = h[0] | (h[1] << 16);
-            }
-            uint32_t right[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const uint32_t v = (uint32_t)__shfl_down((int)mine[q], 1, 64);
-                right[q] = k + 1 < kCh ? v : 0u;
-            }
-            if (r < t.c) {
-                uint4 *row = reinterpret_cast<uint4 *>(lds + t.tab + r * (PW + 16) * 4);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    // entries 16 k + 4 q .. + 3 of block k + 1: (mine, right) pairs
-                    row[4 * (k + 1) + q] = make_uint4(__builtin_amdgcn_perm(right[2 * q], mine[2 * q], 0x05040100u),
-                                                      __builtin_amdgcn_perm(right[2 * q], mine[2 * q], 0x07060302u),
-                                                      __builtin_amdgcn_perm(right[2 * q + 1], mine[2 * q + 1], 0x05040100u),
-                                                      __builtin_amdgcn_perm(right[2 * q + 1], mine[2 * q + 1], 0x07060302u));
-                }
-                if (k == 0) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)  // block 0: (0, chunk 0)
-                        row[q] = make_uint4(mine[2 * q] << 16, mine[2 * q] & 0xffff0000u, mine[2 * q + 1] << 16,
-                                            mine[2 * q + 1] & 0xffff0000u);
+                    const int i = 3 + 4 * u - sh;
+                    if (2 * k + u <= t.nc)
+                        *reinterpret_cast<uint2 *>(row + 8 * (2 * k + u)) =
+                            make_uint2(h[i] | (h[i + 1] << 16), h[i + 2] | (h[i + 3] << 16));
                 }
             }
         }
@@ -492,104 +482,118 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     const uint64_t below = (1ull << lane) - 1ull;
-    int32_t head = 0, tail = 0;  // ring positions, taken modulo kGRing
-    // stage rounds of 64 birds until a k-step's worth meets the region (or
-    // the birds run out); the last, partial step is filled with birds whose
-    // factors are all zero
-    auto fill = [&] {
-        while (tail - head < kGStep && next < n) {
-            const int2 q = qn;
-            const bool have = next + lane < n;
-            next += stride;
-            if (next + lane < n) qn = P[next + lane];  // the following round in flight
-            GBird gb{gg.ay.tab, kGFar, gg.ax.tab, kGFar};
-            bool keep = false;
-            if (have) {
-                stage_axis<PW>(q.y, gg.ay, inv_cy, &gb.rb_y, &gb.g_y);
-                stage_axis<PW>(q.x, gg.ax, inv_cx, &gb.rb_x, &gb.g_x);
-                keep = (gb.g_y >= gy_lo) & (gb.g_y <= gy_hi) & (gb.g_x >= gx_lo) & (gb.g_x <= gx_hi);
-            }
-            const uint64_t m = __ballot(keep);
-            if (keep) ring[(tail + __popcll(m & below)) & (kGRing - 1)] = gb;
-            tail += __popcll(m);
-        }
-        if (tail > head && tail - head < kGStep) {
-            if (lane < kGStep && head + lane >= tail)
-                ring[(head + lane) & (kGRing - 1)] = GBird{gg.ay.tab, kGFar, gg.ax.tab, kGFar};
-            tail = head + kGStep;
-        }
-        wave_sync();
-    };
-    fill();
-    while (tail > head) {  // wave-uniform
-        const GBird *sb = ring + (head & (kGRing - 1)) + 8 * grp;  // this lane's eight birds of the step
-        half8 bx[TN];
-        {
-            int32_t rbx[8], vx[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int2 q = reinterpret_cast<const int2 *>(sb + e)[1];
-                rbx[e] = q.x;
-                vx[e] = q.y + xoff;
-            }
-            operands_x<TN, PW>(bx, rbx, vx, lds);
-        }
-        int32_t rby[8], vy[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int2 q = reinterpret_cast<const int2 *>(sb + e)[0];
-            rby[e] = q.x;
-            vy[e] = q.y + yoff;
-        }
-        contract_y<TM, TN, PW>(acc, bx, rby, vy, lds);
-        head += kGStep;
-        wave_sync();  // the step's reads are done before the ring is written again
-        fill();
-    }
-
+    const GBird none{gg.ay.tab + 8, kGFar, gg.ax.tab + 8, kGFar};
     const size_t cells = (size_t)a.grid_h * a.grid_w;
-    float *out = split > 1 ? partial + ((size_t)f * split + sl) * cells : a.density + (size_t)f * cells;
     const float scale = split > 1 ? 1.0f : gg.scale;
-    if (waves == 1) {
-        // lane l holds rows 4 (l / 16) + i, column l % 16 of every tile
-        if (!active) return;
+
+    for (;;) {
+        float4v acc[TM][TN];
 #pragma unroll
         for (int m = 0; m < TM; ++m)
 #pragma unroll
-            for (int t = 0; t < TN; ++t)
+            for (int t = 0; t < TN; ++t) acc[m][t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+        const int32_t yoff = (row0 >> 2) + (lane & 3), xoff = (col0 >> 2) + (lane & 3);
+        const int32_t y_lo = (row0 - gg.ay.j) * gg.ay.c, x_lo = (col0 - gg.ax.j) * gg.ax.c;
+        int32_t head = 0, tail = 0;  // ring positions, taken modulo kGRing
+        auto step = [&] {
+            wave_sync();
+            // this lane's two birds of the step: i / 4 and i / 4 + 4 of its group's eight
+            const GBird *sb = ring + (head & (kGRing - 1)) + 8 * grp + (r16 >> 2);
+            const int4 q0 = *reinterpret_cast<const int4 *>(sb), q1 = *reinterpret_cast<const int4 *>(sb + 4);
+            // every operand's reads are issued before the first MFMA (left to
+            // itself the compiler waits for each row tile's reads in turn)
+            half8 bx[TN], ay[TM];
+            operands<TN>(bx, LaneBirds{q0.z, q0.w + xoff, q1.z, q1.w + xoff}, ncx, lds);
+            operands<TM>(ay, LaneBirds{q0.x, q0.y + yoff, q1.x, q1.y + yoff}, ncy, lds);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int gy = row0 + 16 * m + 4 * grp + i, gx = col0 + 16 * t + r16;
-                    if (gy < a.grid_h && gx < a.grid_w) out[(size_t)gy * a.grid_w + gx] = acc[m][t][i] * scale;
+            for (int m = 0; m < TM; ++m)
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ay[m], bx[t], acc[m][t], 0, 0, 0);
+            head += kGStep;
+            wave_sync();  // the step's reads are done before the ring is written again
+        };
+        while (left > 0) {  // wave-uniform
+#pragma unroll
+            for (int u = 0; u < kGAhead; ++u) {
+                if (left <= 0) break;
+                int2 q[kGPair];
+                uint64_t m[kGPair];
+                bool keep[kGPair];
+#pragma unroll
+                for (int h = 0; h < kGPair; ++h) {
+                    q[h] = qn[kGPair * u + h];
+                    keep[h] = (lane < left - h * stride) & ((uint32_t)q[h].y - (uint32_t)y_lo < y_n) &
+                              ((uint32_t)q[h].x - (uint32_t)x_lo < x_n);
+                    m[h] = __ballot(keep[h]);
+                    qn[kGPair * u + h] = load(kGAhead * kGPair + h);
                 }
-        return;
-    }
+                left -= kGPair * stride;
+#pragma unroll
+                for (int h = 0; h < kGPair; ++h) {
+                    if (keep[h]) {
+                        GBird gb;
+                        stage_axis(q[h].y, gg.ay, inv_cy, &gb.rb_y, &gb.g_y);
+                        stage_axis(q[h].x, gg.ax, inv_cx, &gb.rb_x, &gb.g_x);
+                        ring[(tail + __popcll(m[h] & below)) & (kGRing - 1)] = gb;
+                    }
+                    tail += __popcll(m[h]);
+                }
+                while (tail - head >= kGStep) step();
+            }
+        }
+        // the last, partial step is filled with birds whose factors are all zero
+        if (tail > head) {
+            if (lane < kGStep && head + lane >= tail) ring[(head + lane) & (kGRing - 1)] = none;
+            step();
+        }
 
-    // the waves of an item add their tiles in wave order, kGRedTiles at a time
-    __syncthreads();  // tables and staging are done with: the space holds the tiles
-    float *red = reinterpret_cast<float *>(lds);
-    const int w0 = (wave / waves) * waves;
-    const int gt = part * 64 + lane;
+        float *out = split > 1 ? partial + ((size_t)f * split + sl) * cells : a.density + (size_t)f * cells;
+        const bool write = active;
+        const int orow = row0 + 4 * grp, ocol = col0 + r16;  // of a tile's float4: lane l holds rows 4 (l / 16) .. + 3, column l % 16
+        group += gridDim.x;
+        const bool more = group < groups;
+        if (more) begin(group);  // the next item's first coordinates are in flight during the sum
+        auto store = [&](int t, float4v v) {
+            const int gy = orow + 16 * (t / TN), gx = ocol + 16 * (t % TN);
 #pragma unroll
-    for (int t0 = 0; t0 < TM * TN; t0 += kGRedTiles) {
+            for (int i = 0; i < 4; ++i)
+                if (write && gy + i < a.grid_h && gx < a.grid_w) out[(size_t)(gy + i) * a.grid_w + gx] = v[i] * scale;
+        };
+        if (waves == 1) {
 #pragma unroll
-        for (int q = 0; q < kGRedTiles; ++q) {
-            const int t = t0 + q;
-            if (t >= TM * TN) break;
+            for (int t = 0; t < TM * TN; ++t) store(t, acc[t / TN][t % TN]);
+        } else {
+            // the waves of an item add their tiles in wave order, a few
+            // tiles at a time, in LDS beside the tables (the rings' space)
+            float4v *red = reinterpret_cast<float4v *>(lds + gg.table_bytes);
+            const int w0 = (wave / waves) * waves;
+            constexpr int kTiles = TM * TN;
+            auto sum = [&](auto round) {
+                constexpr int kRound = decltype(round)::value;
+                __syncthreads();  // every wave is past its last step
 #pragma unroll
-            for (int i = 0; i < 4; ++i) red[(wave * kGRedTiles + q) * 256 + (4 * grp + i) * 16 + r16] = acc[t / TN][t % TN][i];
+                for (int t0 = 0; t0 < kTiles; t0 += kRound) {
+#pragma unroll
+                    for (int q = 0; q < kRound; ++q) {
+                        const int t = t0 + q;
+                        if (t < kTiles) red[(wave * kRound + q) * 64 + lane] = acc[t / TN][t % TN];
+                    }
+                    __syncthreads();
+                    const int nt = min(kRound, kTiles - t0);
+                    for (int q = part; q < nt; q += waves) {
+                        float4v v = red[(w0 * kRound + q) * 64 + lane];
+                        for (int w = 1; w < waves; ++w) v += red[((w0 + w) * kRound + q) * 64 + lane];
+                        store(t0 + q, v);
+                    }
+                    __syncthreads();
+                }
+            };
+            if (gg.red_tiles == kGRedTiles) sum(std::integral_constant<int, kGRedTiles>{});
+            else sum(std::integral_constant<int, 2>{});
         }
-        __syncthreads();
-        const int nt = min(kGRedTiles, TM * TN - t0);
-        for (int el = gt; el < nt * 256; el += 64 * waves) {
-            const int q = el >> 8, within = el & 255;
-            float v = 0.0f;
-            for (int w = 0; w < waves; ++w) v += red[((w0 + w) * kGRedTiles + q) * 256 + within];
-            const int t = t0 + q;
-            const int gy = row0 + 16 * (t / TN) + (within >> 4), gx = col0 + 16 * (t % TN) + (within & 15);
-            if (active && gy < a.grid_h && gx < a.grid_w) out[(size_t)gy * a.grid_w + gx] = v * scale;
-        }
-        __syncthreads();
+        if (!more) return;
     }
 }
 
@@ -666,20 +670,23 @@ bool make_gather_geom(const DensityArgs &a, GatherGeom *gg) {
         return true;
     };
     if (!axis(16LL * a.height_px / a.grid_h, &gg->ay) || !axis(16LL * a.width_px / a.grid_w, &gg->ax)) return false;
-    const int jmax = std::max(gg->ay.j, gg->ax.j);
-    if (2 * jmax + 3 <= 32) gg->pw = 32;
-    else if (2 * jmax + 3 <= 64) gg->pw = 64;
-    else return false;
-    auto bytes16 = [](int64_t pairs) { return (pairs * 4 + 15) / 16 * 16; };
-    const int64_t ty = bytes16((int64_t)gg->ay.c * (gg->pw + 16));
+    auto table = [](GatherAxis *t) -> int64_t {
+        if (t->j > kGMaxWindow) return -1;
+        t->j4 = (t->j + 3) / 4;
+        t->nc = t->j4 + (t->j + 3) / 4 + 1;
+        return (8 + 4LL * t->c * table_row_bytes(*t) + 15) / 16 * 16;
+    };
+    const int64_t ty = table(&gg->ay), tx = table(&gg->ax);
+    if (ty < 0 || tx < 0) return false;
     const bool shared = gg->ay.c == gg->ax.c && gg->ay.j == gg->ax.j;
-    const int64_t tx = shared ? 0 : bytes16((int64_t)gg->ax.c * (gg->pw + 16));
-    if (ty + tx > kGMaxTableBytes) return false;
+    const int64_t bytes = ty + (shared ? 0 : tx);
+    if (bytes > kGMaxTableBytes) return false;
     gg->ay.tab = 0;
     gg->ax.tab = shared ? 0 : (int32_t)ty;
-    gg->table_bytes = (int)(ty + tx);
-    const int stage = kGWaves * kGRing * (int)sizeof(GBird);
-    gg->lds_bytes = std::max(gg->table_bytes + stage, kGWaves * kGRedTiles * 256 * 4);
+    gg->table_bytes = (int)bytes;
+    const int ring = kGWaves * kGRing * (int)sizeof(GBird), red = kGWaves * kGRedTiles * 1024;
+    gg->red_tiles = gg->table_bytes + red <= kGMaxLds ? kGRedTiles : 2;  // two tiles of every wave take the rings' space
+    gg->lds_bytes = gg->table_bytes + std::max(ring, gg->red_tiles == kGRedTiles ? red : 0);
     const double s = (double)a.sigma_px;
     gg->neg_k = (float)(-1.4426950408889634 / (2.0 * s * s));
     gg->scale = (float)(1.0 / (2.0 * 3.14159265358979323846 * s * s) / ((double)kLift * kLift));
@@ -700,26 +707,79 @@ double meet_share(int j, int rows, long long nreg) {
 
 long long axis_regions(int grid_n, int rows) { return (grid_n + rows - 1) / rows; }
 
-// Modelled SIMD cycles of one 32-bird k-step on a region: per lane a pair
-// read (read, clamp, address, pack: about 112 cycles for its eight birds)
-// for every two tile rows of each axis, and one 16-cycle MFMA per tile.
-double step_cycles(const Shape &sh) { return 112.0 * ((sh.rm + 1) / 2 + (sh.rn + 1) / 2) + 16.0 * sh.rm * sh.rn; }
+// The gather kernel's cost model, in microseconds of one wave beside the
+// other of its SIMD (least squares over 40 measured plans of 64 x 2000 and
+// 1800 x 5000 birds on 128 x 72 grids and 256 x 8000 on 256 x 144: 4% mean
+// error, 9% at most).  A 32-bird k-step costs its tile reads and its MFMAs,
+// which did not overlap; every block of 64 birds costs its test on each
+// region.
+double step_us(const Shape &sh) { return 0.0135 * (sh.rm + sh.rn) + 0.0159 * sh.rm * sh.rn; }
+constexpr double kBlockUs = 0.335;  // a 64-bird block's test and staging
+constexpr double kTileUs = 0.11;    // a tile's sum over an item's waves
+constexpr double kGroupUs = 1.0;    // a workgroup's start on an item group
+constexpr double kLaunchUs = 5.0;   // launch and table build
+constexpr double kSliceSumUs = 4.0; // the second kernel of a launch split into bird slices
 
-// Gather-path region shape of least modelled cost per frame: each bird's
-// k-step share on every region its window meets, the test that keeps or
-// drops every bird on every region (about 3 cycles a bird), and a fixed cost
-// per region (tables, the final sum and the stores).
-Shape gather_shape(int jy, int jx, int grid_w, int grid_h, double birds, int max_tiles = 1 << 30) {
+struct GatherCost {
+    long long ry, rx;
+    double kept;  // birds an item keeps, on average
+};
+
+GatherCost gather_regions(const Shape &sh, int jy, int jx, int grid_w, int grid_h, double birds) {
+    GatherCost g;
+    g.ry = axis_regions(grid_h, 16 * sh.rm);
+    g.rx = axis_regions(grid_w, 16 * sh.rn);
+    g.kept = birds * meet_share(jy, 16 * sh.rm, g.ry) * meet_share(jx, 16 * sh.rn, g.rx);
+    return g;
+}
+
+// Modelled time of a launch with `waves` waves per item and `split` bird
+// slices.  A compute unit runs one workgroup at a time and takes its share of
+// the item groups in turn; one round of workgroups ends with its fullest
+// region (about 1.25 times the average unless all eight waves share each
+// region).
+double gather_us(const Shape &sh, int waves, int split, const GatherCost &g, long long n_frames, double birds,
+                 int n_cus) {
+    const long long items = n_frames * g.ry * g.rx * split, groups = (items * waves + kGWaves - 1) / kGWaves;
+    const long long cus = std::max(n_cus, 1);
+    const double rounds = groups <= 4 * cus ? (double)((groups + cus - 1) / cus) : (double)groups / cus;
+    const double uneven = rounds == 1.0 && waves < kGWaves ? 1.25 : 1.0;
+    const double units = (double)waves * split, steps = g.kept * uneven / (kGStep * units) + 0.5;
+    return kLaunchUs + (split > 1 ? kSliceSumUs : 0.0) +
+           rounds * (kGroupUs + steps * step_us(sh) + std::max(birds / (64.0 * units), 1.0) * kBlockUs +
+                     (waves > 1 ? kTileUs * sh.rm * sh.rn : 0.0));
+}
+
+// Region shape and waves per item of least modelled time.
+Shape gather_shape(int jy, int jx, int grid_w, int grid_h, long long n_frames, double birds, int n_cus, int *waves) {
     Shape best = kGShapes[0];
-    double best_cost = 1e300;
+    double best_us = 1e300;
     for (const Shape &sh : kGShapes) {
-        if (sh.rm * sh.rn > max_tiles) continue;
-        const long long ry = axis_regions(grid_h, 16 * sh.rm), rx = axis_regions(grid_w, 16 * sh.rn);
-        const double meets = ry * meet_share(jy, 16 * sh.rm, ry) * rx * meet_share(jx, 16 * sh.rn, rx);
-        const double cost = birds / kGStep * meets * step_cycles(sh) + (3.2 * birds + 4000.0) * (double)(ry * rx);
-        if (cost < best_cost * 0.999) {
+        const GatherCost g = gather_regions(sh, jy, jx, grid_w, grid_h, birds);
+        for (int w = 1; w <= kGWaves; w *= 2) {
+            const double us = gather_us(sh, w, 1, g, n_frames, birds, n_cus);
+            if (us < best_us * 0.999) {
+                best = sh;
+                *waves = w;
+                best_us = us;
+            }
+        }
+    }
+    return best;
+}
+
+// Region shape of a launch split into bird slices (at most 16 tiles, see
+// plan_density): least modelled work per frame, whatever its spread.
+Shape gather_split_shape(int jy, int jx, int grid_w, int grid_h, double birds) {
+    Shape best = kGShapes[0];
+    double best_us = 1e300;
+    for (const Shape &sh : kGShapes) {
+        if (sh.rm * sh.rn > 16) continue;
+        const GatherCost g = gather_regions(sh, jy, jx, grid_w, grid_h, birds);
+        const double us = (g.kept / kGStep * step_us(sh) + birds / 64.0 * kBlockUs + kGroupUs) * (double)(g.ry * g.rx);
+        if (us < best_us * 0.999) {
             best = sh;
-            best_cost = cost;
+            best_us = us;
         }
     }
     return best;
@@ -730,15 +790,15 @@ int env_int(const char *name) {
     return v ? std::atoi(v) : 0;
 }
 
-// Waves per work item and slices per (frame, region) of a gather launch.  A
-// compute unit holds kGWaves waves (two per SIMD).  Items are spread over
-// as few waves as fill the chip (the smallest power of two w, at most
-// kGWaves, with items * w >= resident waves): more waves per item only add
-// fixed costs (a table build per workgroup, the final sum across waves).
-// `birds` is the birds an item keeps (those whose window meets its region),
-// on average.  FLOCK_DENSITY_WAVES / FLOCK_DENSITY_SPLIT override (for
-// tuning and tests).
-void gather_split(int32_t n_frames, double birds, long long regions, int n_cus, int *waves, int *split) {
+// Waves per work item and slices per (frame, region) of a launch that would
+// leave most of the chip idle.  A compute unit holds kGWaves waves (two per
+// SIMD).  Items are spread over as few waves as fill the chip (the smallest
+// power of two w, at most kGWaves, with items * w >= resident waves): more
+// waves per item only add fixed costs (a table build per workgroup, the final
+// sum across waves).  `birds` is the birds an item keeps (those whose window
+// meets its region), on average.  FLOCK_DENSITY_WAVES / FLOCK_DENSITY_SPLIT
+// override (for tuning and tests).
+void gather_split(int64_t n_frames, double birds, long long regions, int n_cus, int *waves, int *split) {
     const long long items = (long long)n_frames * regions;
     const long long resident = (long long)kGWaves * std::max(n_cus, 1);
     int w = 1;
@@ -819,37 +879,55 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t lds_limit) {
     GatherGeom gg;
     if (!force_recur && make_gather_geom(a, &gg) && (size_t)gg.lds_bytes <= lds_limit) {
         const double birds = a.n_frames > 0 ? (double)a.total / a.n_frames : 0.0;
-        Shape sh = gather_shape(gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, birds);
-        int grm = 0, grn = 0;
-        if (force && std::sscanf(force, "%d,%d", &grm, &grn) == 2)
-            for (const Shape &k : kGShapes)
-                if (k.rm == grm && k.rn == grn) sh = k;
         DensityPlan p{};
         p.gather = 1;
+        p.split = 1;
+        Shape sh = gather_shape(gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, a.n_frames, birds, n_cus, &p.waves);
+        GatherCost g = gather_regions(sh, gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, birds);
+        int grm = 0, grn = 0;
+        bool forced = false;
+        if (force && std::sscanf(force, "%d,%d", &grm, &grn) == 2)
+            for (const Shape &k : kGShapes)
+                if (k.rm == grm && k.rn == grn) {
+                    sh = k;
+                    forced = true;
+                }
+        const int fs = env_int("FLOCK_DENSITY_SPLIT"), fw = env_int("FLOCK_DENSITY_WAVES");
+        if (forced) {
+            gather_split(a.n_frames, g.kept, g.ry * g.rx, n_cus, &p.waves, &p.split);
+        } else {
+            // bird slices where they pay for the second kernel: a launch that
+            // would leave most of the chip idle is bound by each wave's own
+            // path, whose fixed part grows with the tiles an item's waves add
+            // up at the end (kGRedTiles per round); shapes of at most 16
+            // tiles keep that to two rounds
+            const Shape ss = gather_split_shape(gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, birds);
+            const GatherCost sg = gather_regions(ss, gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, birds);
+            int sw = 1, sp = 1;
+            gather_split(a.n_frames, sg.kept, sg.ry * sg.rx, n_cus, &sw, &sp);
+            if (fs >= 1 || fw >= 1 ||
+                (sp > 1 && gather_us(ss, sw, sp, sg, a.n_frames, birds, n_cus) <
+                               gather_us(sh, p.waves, 1, g, a.n_frames, birds, n_cus))) {
+                sh = ss;
+                g = sg;
+                p.waves = sw;
+                p.split = sp;
+            }
+        }
         p.rm = sh.rm;
         p.rn = sh.rn;
-        p.regions_y = (a.grid_h + 16 * sh.rm - 1) / (16 * sh.rm);
-        p.regions_x = (a.grid_w + 16 * sh.rn - 1) / (16 * sh.rn);
-        const double kept = birds * meet_share(gg.ay.j, 16 * sh.rm, p.regions_y) *
-                            meet_share(gg.ax.j, 16 * sh.rn, p.regions_x);
-        gather_split(a.n_frames, kept, (long long)p.regions_y * p.regions_x, n_cus, &p.waves, &p.split);
-        if (p.split > 1 && !(force && grm)) {
-            // few frames for the chip: the launch is bound by each wave's own
-            // path, whose fixed part grows with the tiles an item's waves add
-            // up at the end (kGRedTiles per round); shapes of at most 16 tiles
-            // keep that to two rounds
-            sh = gather_shape(gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, birds, 16);
-            p.rm = sh.rm;
-            p.rn = sh.rn;
-            p.regions_y = (a.grid_h + 16 * sh.rm - 1) / (16 * sh.rm);
-            p.regions_x = (a.grid_w + 16 * sh.rn - 1) / (16 * sh.rn);
-            const double kept2 = birds * meet_share(gg.ay.j, 16 * sh.rm, p.regions_y) *
-                                 meet_share(gg.ax.j, 16 * sh.rn, p.regions_x);
-            gather_split(a.n_frames, kept2, (long long)p.regions_y * p.regions_x, n_cus, &p.waves, &p.split);
-        }
-        const long long items = (long long)a.n_frames * p.regions_y * p.regions_x * p.split;
+        p.regions_y = (int)g.ry;
+        p.regions_x = (int)g.rx;
+        const long long items = (long long)a.n_frames * g.ry * g.rx * p.split;
         const int per_wg = kGWaves / p.waves;
-        p.blocks = (items + per_wg - 1) / per_wg;
+        if (items > 0xffffffffLL) {  // item numbers are 32 bits wide: refused by the caller's check of `blocks`
+            p.blocks = items;
+            return p;
+        }
+        // a workgroup takes its share of the item groups one after another,
+        // with one table build: 256 x 8000 with eight waves per item took 91
+        // against 103 us with a workgroup per group
+        p.blocks = std::min<long long>((items + per_wg - 1) / per_wg, std::max(n_cus, 1));
         return p;
     }
     int frm = 0, frn = 0;
@@ -908,19 +986,18 @@ hipError_t launch_density(const DensityArgs &a, const DensityPlan &p, float *par
         if (!make_gather_geom(a, &gg)) return hipErrorInvalidValue;
         if (p.split > 1 && !partial) return hipErrorInvalidValue;
         const long long items = (long long)a.n_frames * p.regions_y * p.regions_x * p.split;
-#define FLOCK_GSHAPE_PW(TM, TN, PW)                                                                              \
-    if (p.rm == TM && p.rn == TN && gg.pw == PW) {                                                               \
-        hipLaunchKernelGGL((density_gather_kernel<TM, TN, PW>), dim3((unsigned)p.blocks), dim3(kGThreads),      \
-                           (size_t)gg.lds_bytes, stream, a, gg, p.regions_y, p.regions_x, p.split, p.waves, items, \
+#define FLOCK_GSHAPE(TM, TN)                                                                                     \
+    if (p.rm == TM && p.rn == TN) {                                                                              \
+        hipLaunchKernelGGL((density_gather_kernel<TM, TN>), dim3((unsigned)p.blocks), dim3(kGThreads),          \
+                           (size_t)gg.lds_bytes, stream, a, gg, p.regions_y, p.regions_x, p.split, p.waves, \
+                           (uint32_t)items, \
                            partial);                                                                             \
         err = hipGetLastError();                                                                                 \
     }
-#define FLOCK_GSHAPE(TM, TN) FLOCK_GSHAPE_PW(TM, TN, 32) FLOCK_GSHAPE_PW(TM, TN, 64)
         FLOCK_GSHAPE(1, 1) FLOCK_GSHAPE(2, 2) FLOCK_GSHAPE(1, 4) FLOCK_GSHAPE(4, 1) FLOCK_GSHAPE(2, 4)
         FLOCK_GSHAPE(4, 2) FLOCK_GSHAPE(3, 4) FLOCK_GSHAPE(4, 4) FLOCK_GSHAPE(5, 4)
         FLOCK_GSHAPE(9, 2) FLOCK_GSHAPE(9, 4) FLOCK_GSHAPE(3, 8) FLOCK_GSHAPE(4, 8)
 #undef FLOCK_GSHAPE
-#undef FLOCK_GSHAPE_PW
         if (err != hipSuccess || p.split <= 1) return err;
         const int64_t cells = (int64_t)a.grid_h * a.grid_w;
         const int64_t total = cells * a.n_frames;

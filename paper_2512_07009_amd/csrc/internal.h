@@ -81,6 +81,7 @@ struct DensityPlan {
     int regions_y, regions_x; // regions per frame
     int split;                // bird slices per (frame, region); > 1 adds partial grids afterwards
     int waves;                // gather: waves sharing one (frame, region, slice)
+    int reach;                // gather: tiles a band of 32 rows reaches beyond itself, 0 without bands
     long long blocks;         // workgroups of the main kernel
 };
 

@@ -393,6 +393,29 @@ def test_density_paths_gpu(path, w, h, gx, gy, sigma, frames, monkeypatch):
     print(f"density {path} {gx}x{gy}: worst rel err {worst:.2e}")
 
 
+@pytest.mark.parametrize("w,h,gx,gy,sigma,frames,n", [
+    (1920, 1080, 128, 72, 0.9, 3, 300),      # a window of one cell and a bit: rows of three chunks
+    (1920, 1080, 128, 72, 37.6, 3, 900),     # half-width 17: one past a whole number of chunks
+    (1280, 720, 160, 90, 29.0, 2, 700),      # half-width 23
+    (640, 480, 40, 60, 11.0, 4, 500),        # cells of 16 x 8 px: a table per axis
+    (320, 176, 20, 11, 9.0, 1500, 70),       # more item groups than compute units: tables reused
+    (1000, 700, 77, 53, 21.0, 3, 900),       # no whole number of quanta per cell
+    (1920, 1080, 61, 35, 400.0, 2, 300),     # a window wider than the frame
+])
+def test_density_window_edges_gpu(w, h, gx, gy, sigma, frames, n):
+    """Window widths at the edges of the factor chunks, and birds outside the
+    frame whose windows reach into it (tolerance as everywhere: two fp16
+    factors per term, within 1e-3 of the frame's maximum)."""
+    rng = np.random.default_rng(gx * 1000 + gy)
+    reach = int(16 * 5 * sigma)
+    batch = [np.stack([rng.integers(0, 16 * w + reach, k), rng.integers(0, 16 * h + reach, k)], 1).astype(np.int32)
+             for k in rng.integers(n // 2, n + 1, frames)]
+    xy, off = wl.pack(batch)
+    got = run_density(xy, off, w, h, gx, gy, sigma)
+    ref = oracle.density_frames(xy, off, w, h, gx, gy, sigma)
+    assert_density_close(got, ref, np.diff(off), sigma, tag=f"{gx}x{gy} sigma {sigma}")
+
+
 @pytest.mark.parametrize("split", ["3", "16"])
 def test_density_bird_slices_gpu(split, monkeypatch):
     """Frames split into bird slices whose partial grids are added afterwards,
