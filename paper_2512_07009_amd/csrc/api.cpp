@@ -346,14 +346,13 @@ flock_status density_run(const int32_t *xy, const int32_t *offsets, int32_t n_fr
     a.offsets = offsets;
     a.n_frames = n_frames;
     a.total = total;
-    a.max_frame_points = max_frame_points;
     a.width_px = width_px;
     a.height_px = height_px;
     a.grid_w = grid_w;
     a.grid_h = grid_h;
     a.sigma_px = sigma_px;
     a.density = density;
-    const flock::DensityPlan plan = flock::plan_density(a, dev->n_cus, dev->lds_per_block);
+    const flock::DensityPlan plan = flock::plan_density(a, dev->n_cus);
     if (plan.blocks > 0x7fffffffLL) return fail(FLOCK_EUNSUPPORTED, "batch too large for one launch");
     // a split launch keeps partial grids in the workspace
     const size_t need = plan.split > 1 ? (size_t)n_frames * plan.split * (size_t)grid_w * grid_h * sizeof(float) : 0;

@@ -38,13 +38,15 @@
 // batches with few (frame, region) pairs also split frames into bird slices
 // whose partial grids a second kernel adds in slice order.
 //
-// Recurrence path (any other grid).  Each workgroup generates its factors
-// with a two-multiply recurrence along the window,
-//     F(d + h) = F(d) * R(d),   R(d + h) = R(d) * Q,
-//     R(d) = exp(-(2 d h + h^2) / (2 s^2)),  Q = exp(-h^2 / s^2),
-// started from exact exponentials at both ends of the window (two chains per
-// thread) and restarted every kRestart rows; when h > 2 s every factor is an
-// exact exponential.
+// Direct path (any other grid, and windows too wide for the tables).  The same
+// kernel, with the 32 birds of a k-step evaluated instead of looked up: each
+// lane takes one bird and axis, writes the factors of its window (or of the
+// whole region, where that is smaller) as exact exponentials into a row of its
+// wave's own LDS scratch, and the operands are read from there as above.
+// (Before, 128 birds at a time were written as columns of cleared LDS tiles by
+// a recurrence between barriers: 48 ragged frames of up to 3000 birds on a
+// 97 x 61 grid took 38 us, now 23.6.)  Bound by the exponentials, about 36
+// per lane and step at a window of 27 cells.
 //
 // Accuracy: a normal fp16 factor (f >= 2^-22) carries a relative rounding
 // error <= 2^-11 (plus a few fp32 ulps before the conversion); a subnormal
@@ -70,186 +72,10 @@
 namespace flock {
 namespace {
 
-// ---------------------------------------------------------------------------
-// Recurrence path
-// ---------------------------------------------------------------------------
-
-constexpr int kRThreads = 256;       // 4 waves
-constexpr int kRChunk = 128;         // birds per LDS chunk: one (bird, axis) window per thread
-constexpr int kRPitch = kRChunk + 8; // halves per LDS row (16-byte skew between rows)
-constexpr int kRestart = 16;         // rows between exact restarts of the recurrence
 constexpr float kCutSigmas = 6.0f;
 constexpr float kLift = 256.0f;      // factors are stored as fp16(kLift f)
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float float16v __attribute__((ext_vector_type(16)));
-
-struct Geometry {
-    float hx, hy;          // cell size, px
-    float inv_hx, inv_hy;
-    float neg_k;           // -log2(e) / (2 s^2): exp(-d^2/(2s^2)) = exp2(d^2 * neg_k)
-    float cut;             // window half-width, px
-    float scale;           // 1 / (2 pi s^2 kLift^2)
-    int recur_x, recur_y;  // recurrence usable along the axis (h <= 2 s)
-};
-
-template <int RM, int RN>
-struct RecurLayout {
-    static constexpr int kRowsY = 32 * RM;
-    static constexpr int kRowsX = 32 * RN;
-    static constexpr int kFactorBytes = (kRowsY + kRowsX) * kRPitch * 2;
-    static constexpr int kRedBytes = 4 * 32 * 33 * 4;  // one tile from each wave, padded rows
-    static constexpr int kBytes = kFactorBytes > kRedBytes ? kFactorBytes : kRedBytes;
-};
-
-// Write one bird's factors (times kLift) for rows [row0, row0 + nrows) of one
-// axis into a column of buf (row-major, kRPitch halves per row); rows outside
-// the window (6 s) are left as they are (cleared): their factors are below
-// exp(-18) = 1.5e-8 of the peak.
-__device__ __forceinline__ void fill_window(_Float16 *col, float pos, float h, float inv_h, int grid_n,
-                                            int row0, int nrows, float neg_k, float cut, bool recur) {
-    int lo = max((int)ceilf((pos - cut) * inv_h - 0.5f), row0);
-    int hi = min((int)floorf((pos + cut) * inv_h - 0.5f), min(row0 + nrows, grid_n) - 1);
-    if (!recur) {
-        for (int row = lo; row <= hi; ++row) {
-            const float d = ((float)row + 0.5f) * h - pos;
-            col[(row - row0) * kRPitch] = (_Float16)(kLift * __builtin_amdgcn_exp2f(d * d * neg_k));
-        }
-        return;
-    }
-    const float q = __builtin_amdgcn_exp2f(2.0f * h * h * neg_k);
-    // two chains: rows lo.. upward and rows hi.. downward, meeting in the middle
-    const int mid = (lo + hi) >> 1;
-    for (int base = lo, top = hi; base <= mid; base += kRestart, top -= kRestart) {
-        const float da = ((float)base + 0.5f) * h - pos;
-        const float db = ((float)top + 0.5f) * h - pos;
-        float fa = kLift * __builtin_amdgcn_exp2f(da * da * neg_k);
-        float ra = __builtin_amdgcn_exp2f((2.0f * da + h) * h * neg_k);
-        float fb = kLift * __builtin_amdgcn_exp2f(db * db * neg_k);
-        float rb = __builtin_amdgcn_exp2f((h - 2.0f * db) * h * neg_k);  // ratio going down
-        const int steps = min(kRestart, mid - base + 1);
-        for (int i = 0; i < steps; ++i) {
-            col[(base + i - row0) * kRPitch] = (_Float16)fa;
-            if (top - i > mid) col[(top - i - row0) * kRPitch] = (_Float16)fb;
-            fa *= ra;
-            ra *= q;
-            fb *= rb;
-            rb *= q;
-        }
-    }
-}
-
-template <int RM, int RN>
-__global__ __launch_bounds__(kRThreads) void density_recur_kernel(DensityArgs a, Geometry g, int regions_y,
-                                                           int regions_x) {
-    using L = RecurLayout<RM, RN>;
-    __shared__ __align__(16) unsigned char lds[L::kBytes];
-    _Float16 *fy = reinterpret_cast<_Float16 *>(lds);
-    _Float16 *fx = fy + L::kRowsY * kRPitch;
-
-    const int regions = regions_y * regions_x;
-    const int f = blockIdx.x / regions;
-    const int reg = blockIdx.x - f * regions;
-    const int gy0 = (reg / regions_x) * L::kRowsY;
-    const int gx0 = (reg % regions_x) * L::kRowsX;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-
-    const int32_t b = a.offsets[f];
-    const int32_t e = a.offsets[f + 1];
-    const bool ok = !(b < 0 || e < b || e > a.total);
-    const int32_t n = ok ? e - b : 0;
-    const int2 *P = reinterpret_cast<const int2 *>(a.xy) + b;
-
-    float16v acc[RM][RN];
-#pragma unroll
-    for (int m = 0; m < RM; ++m)
-#pragma unroll
-        for (int t = 0; t < RN; ++t)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) acc[m][t][j] = 0.0f;
-
-    const int r32 = lane & 31;
-    const int kq = (lane >> 5) * 8;
-    // thread -> (bird k of the chunk, axis); the bird is fetched one chunk ahead
-    const int k = tid & (kRChunk - 1);
-    const bool yaxis = tid < kRChunk;
-    int2 p = make_int2(0, 0);
-    if (k < n) p = P[k];
-    for (int32_t k0 = 0; k0 < n; k0 += kRChunk) {
-        // clear both factor tiles (16-byte stores)
-        {
-            uint4 *z = reinterpret_cast<uint4 *>(lds);
-            constexpr int nz = L::kFactorBytes / 16;
-            const uint4 zero = make_uint4(0, 0, 0, 0);
-#pragma unroll 4
-            for (int i = tid; i < nz; i += kRThreads) z[i] = zero;
-        }
-        const int2 pc = p;
-        if (k0 + kRChunk + k < n) p = P[k0 + kRChunk + k];
-        __syncthreads();
-        if (k0 + k < n) {
-            if (yaxis)
-                fill_window(fy + k, (float)pc.y * 0.0625f, g.hy, g.inv_hy, a.grid_h, gy0, L::kRowsY,
-                            g.neg_k, g.cut, g.recur_y);
-            else
-                fill_window(fx + k, (float)pc.x * 0.0625f, g.hx, g.inv_hx, a.grid_w, gx0, L::kRowsX,
-                            g.neg_k, g.cut, g.recur_x);
-        }
-        __syncthreads();
-        // this wave's 32 birds of the chunk: two k-steps of 16
-#pragma unroll
-        for (int ks = 0; ks < 32; ks += 16) {
-            const int kk = wave * 32 + ks + kq;
-            half8 bx[RN];
-#pragma unroll
-            for (int t = 0; t < RN; ++t)
-                bx[t] = *reinterpret_cast<const half8 *>(fx + (t * 32 + r32) * kRPitch + kk);
-#pragma unroll
-            for (int m = 0; m < RM; ++m) {
-                const half8 ay = *reinterpret_cast<const half8 *>(fy + (m * 32 + r32) * kRPitch + kk);
-#pragma unroll
-                for (int t = 0; t < RN; ++t)
-                    acc[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ay, bx[t], acc[m][t], 0, 0, 0);
-            }
-        }
-        __syncthreads();
-    }
-
-    // Sum the four waves' tiles in a fixed order and store.  Lane l of a wave
-    // holds column (l & 31) and rows 8*(j/4) + 4*(l/32) + (j%4), j = 0..15.
-    float *red = reinterpret_cast<float *>(lds);
-    float *out = a.density + (size_t)f * a.grid_h * a.grid_w;
-#pragma unroll
-    for (int m = 0; m < RM; ++m) {
-#pragma unroll
-        for (int t = 0; t < RN; ++t) {
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int row = 8 * (j >> 2) + 4 * (lane >> 5) + (j & 3);
-                red[(wave * 32 + row) * 33 + r32] = acc[m][t][j];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int el = tid + i * kRThreads;  // 0..1023 over the 32x32 tile
-                const int row = el >> 5, colx = el & 31;
-                const float s = ((red[row * 33 + colx] + red[(32 + row) * 33 + colx]) +
-                                 red[(64 + row) * 33 + colx]) + red[(96 + row) * 33 + colx];
-                const int gy = gy0 + m * 32 + row;
-                const int gx = gx0 + t * 32 + colx;
-                if (ok && gy < a.grid_h && gx < a.grid_w) out[(size_t)gy * a.grid_w + gx] = s * g.scale;
-            }
-            __syncthreads();
-        }
-    }
-}
-
-
-// ---------------------------------------------------------------------------
-// Gather path
-// ---------------------------------------------------------------------------
 
 constexpr int kGWaves = 8;                 // waves per workgroup (two per SIMD)
 constexpr int kGThreads = 64 * kGWaves;
@@ -260,8 +86,8 @@ constexpr int kGAhead = 2;                 // pairs of blocks loaded ahead
 constexpr int kGRing = 256;                // staged birds per wave (one k-step left over + one pair of blocks)
 constexpr int kGMaxLds = 159 * 1024;        // of a compute unit's 160 KiB
 constexpr int kGMaxTableBytes = kGMaxLds - kGWaves * kGRing * 16;  // both factor tables
-constexpr int kGMaxWindow = 30;             // window half-width, cells
 constexpr int kGMinWaveBirds = 32;         // kept birds per wave, at least, when a launch splits frames
+constexpr int32_t kGNone = INT_MIN;         // direct path: coordinate of a padding bird
 constexpr int32_t kGFar = 1 << 28;         // bird term that clamps every cell to a zero chunk
 
 typedef float float4v __attribute__((ext_vector_type(4)));
@@ -274,24 +100,25 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 // with a zero chunk, and one more lies before row 0, so that both neighbours
 // of a row's chunks are zeros.
 struct GatherAxis {
-    int32_t c;      // quanta per cell
+    int32_t c;      // quanta per cell (table path)
     int32_t j;      // window half-width, cells
     int32_t j4;     // chunks before the bird's own group: ceil(j / 4)
-    int32_t nc;     // chunks per row: j4 + (j + 3) / 4 + 1
+    int32_t nc;     // chunks of a window: 2 j4 + 1
     int32_t tab;    // byte offset of the table (its leading zero chunk) in LDS
+    float h, inv_h; // cell size, px (direct path)
 };
 
 struct GatherGeom {
     GatherAxis ay, ax;
     float neg_k;      // -log2(e) / (2 s^2), px^-2
     float scale;      // 1 / (2 pi s^2 kLift^2)
-    int table_bytes;  // the tables (one when both axes agree), 16-byte aligned
+    int table_bytes;  // the tables (one when both axes agree), or the waves' factor scratch; 16-byte aligned
     int red_tiles;    // tiles per round of the cross-wave sum: kGRedTiles, or 2 beside large tables
     int lds_bytes;
 };
 
 // One bird as a lane reads it: per axis the byte offset of its table row and
-// j4 - Q, Q its cell group.
+// j4 - Q, Q its cell group (on the direct path its coordinate, and unused).
 struct GBird {
     int32_t rb_y, g_y, rb_x, g_x;
 };
@@ -377,7 +204,7 @@ __device__ __forceinline__ void operands(half8 (&op)[T], const LaneBirds &b, int
 // ranks), and runs a k-step whenever 32 are staged; the last step is padded
 // with birds whose factors are all zero.  No barrier is needed until the
 // final sum.
-template <int TM, int TN>
+template <int TM, int TN, bool DIRECT>
 __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) void density_gather_kernel(
     DensityArgs a, GatherGeom gg, int regions_y, int regions_x, int split, int waves, uint32_t items, float *partial) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -396,13 +223,24 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
     GBird *ring = reinterpret_cast<GBird *>(lds + gg.table_bytes) + wave * kGRing;
     const float inv_cy = 1.0f / (float)(4 * gg.ay.c), inv_cx = 1.0f / (float)(4 * gg.ax.c);
     const int r16 = lane & 15, grp = lane >> 4;
-    const int32_t ncy = gg.ay.nc, ncx = gg.ax.nc;
+    // direct path: a factor row holds the bird's window, or all of the
+    // region's chunks where those are fewer
+    const bool whole_y = DIRECT && gg.ay.nc >= 4 * TM, whole_x = DIRECT && gg.ax.nc >= 4 * TN;
+    const int32_t ncy = whole_y ? 4 * TM : gg.ay.nc, ncx = whole_x ? 4 * TN : gg.ax.nc;
     // a bird in cell G meets rows [row0, row0 + 16 TM) when
     // row0 - j <= G <= row0 + 16 TM - 1 + j, i.e. when its quantum q lies in
     // [(row0 - j) c, (row0 + 16 TM + j) c)  (below 2^31: c (grid + 2 j) is
-    // 16 times the frame's extent and two windows)
-    const uint32_t y_n = (uint32_t)(16 * TM + 2 * gg.ay.j) * (uint32_t)gg.ay.c;
-    const uint32_t x_n = (uint32_t)(16 * TN + 2 * gg.ax.j) * (uint32_t)gg.ax.c;
+    // 16 times the frame's extent and two windows); the direct path's bounds
+    // are the same in px, a quantum wider for their rounding and clamped
+    auto low = [](const GatherAxis &t, int first) {
+        if (!DIRECT) return (first - t.j) * t.c;
+        return (int32_t)fminf(fmaxf((float)(first - t.j) * t.h * 16.0f - 1.0f, -33554432.0f), 33554432.0f);
+    };
+    auto span = [](const GatherAxis &t, int rows, int first, int32_t lo) {
+        if (!DIRECT) return (uint32_t)(rows + 2 * t.j) * (uint32_t)t.c;
+        const float end = (float)(first + rows + t.j) * t.h * 16.0f + 2.0f;
+        return (uint32_t)((int32_t)fminf(fmaxf(end, -33554432.0f), 33554432.0f) - lo);
+    };
 
     // this wave's item, and its part of the item's birds: coordinates are
     // loaded kGAhead pairs of 64-bird blocks ahead
@@ -470,8 +308,18 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
             }
         }
     };
-    build(gg.ay);
-    if (gg.ax.tab != gg.ay.tab) build(gg.ax);
+    // the wave's scratch: a zero chunk, then 32 rows of ncy chunks and a zero
+    // chunk each, then 32 rows for x
+    const int rowy = 8 * (ncy + 1), rowx = 8 * (ncx + 1);
+    const int scratch_y = wave * (gg.table_bytes / kGWaves) + 8, scratch_x = scratch_y + 32 * rowy;
+    if constexpr (DIRECT) {
+        const uint2 zero = make_uint2(0u, 0u);
+        if (lane == 0) *reinterpret_cast<uint2 *>(lds + scratch_y - 8) = zero;
+        *reinterpret_cast<uint2 *>(lds + (lane < 32 ? scratch_y + (lane + 1) * rowy : scratch_x + (lane - 31) * rowx) - 8) = zero;
+    } else {
+        build(gg.ay);
+        if (gg.ax.tab != gg.ay.tab) build(gg.ax);
+    }
     __syncthreads();  // tables written
 
     // a wave's LDS accesses stay in program order; the fences keep the
@@ -482,7 +330,7 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     const uint64_t below = (1ull << lane) - 1ull;
-    const GBird none{gg.ay.tab + 8, kGFar, gg.ax.tab + 8, kGFar};
+    const GBird none = DIRECT ? GBird{kGNone, 0, kGNone, 0} : GBird{gg.ay.tab + 8, kGFar, gg.ax.tab + 8, kGFar};
     const size_t cells = (size_t)a.grid_h * a.grid_w;
     const float scale = split > 1 ? 1.0f : gg.scale;
 
@@ -493,18 +341,49 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
             for (int t = 0; t < TN; ++t) acc[m][t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
         const int32_t yoff = (row0 >> 2) + (lane & 3), xoff = (col0 >> 2) + (lane & 3);
-        const int32_t y_lo = (row0 - gg.ay.j) * gg.ay.c, x_lo = (col0 - gg.ax.j) * gg.ax.c;
+        const int32_t y_lo = low(gg.ay, row0), x_lo = low(gg.ax, col0);
+        const uint32_t y_n = span(gg.ay, 16 * TM, row0, y_lo), x_n = span(gg.ax, 16 * TN, col0, x_lo);
         int32_t head = 0, tail = 0;  // ring positions, taken modulo kGRing
         auto step = [&] {
             wave_sync();
-            // this lane's two birds of the step: i / 4 and i / 4 + 4 of its group's eight
-            const GBird *sb = ring + (head & (kGRing - 1)) + 8 * grp + (r16 >> 2);
-            const int4 q0 = *reinterpret_cast<const int4 *>(sb), q1 = *reinterpret_cast<const int4 *>(sb + 4);
             // every operand's reads are issued before the first MFMA (left to
             // itself the compiler waits for each row tile's reads in turn)
             half8 bx[TN], ay[TM];
-            operands<TN>(bx, LaneBirds{q0.z, q0.w + xoff, q1.z, q1.w + xoff}, ncx, lds);
-            operands<TM>(ay, LaneBirds{q0.x, q0.y + yoff, q1.x, q1.y + yoff}, ncy, lds);
+            const int bird = 8 * grp + (r16 >> 2);  // this lane's two birds of the step: i / 4 and i / 4 + 4 of its group's eight
+            if constexpr (DIRECT) {
+                // lane l: bird l % 32, axis y for l < 32, else x
+                const bool isx = lane >= 32;
+                const GBird e = ring[(head + (lane & 31)) & (kGRing - 1)];
+                const int32_t q = isx ? e.rb_x : e.rb_y;
+                const float h = isx ? gg.ax.h : gg.ay.h;
+                const float pos = q == kGNone ? 1.0e15f : (float)q * 0.0625f;  // far off: every factor 0
+                int first = isx ? col0 >> 2 : row0 >> 2;  // the row's first chunk, in chunks of the grid
+                if (!(isx ? whole_x : whole_y))
+                    first = ((int)floorf(pos * (isx ? gg.ax.inv_h : gg.ay.inv_h)) >> 2) - (isx ? gg.ax.j4 : gg.ay.j4);
+                unsigned char *row = lds + (isx ? scratch_x + (lane - 32) * rowx : scratch_y + lane * rowy);
+                const int nc = isx ? ncx : ncy;
+                float cell = (float)(4 * first) + 0.5f;
+                for (int k = 0; k < nc; ++k, cell += 4.0f) {
+                    half4 f;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float d = fmaf(cell + (float)i, h, -pos);
+                        f[i] = (_Float16)__builtin_amdgcn_exp2f(fmaf(d * d, gg.neg_k, 8.0f));  // 2^8 = kLift
+                    }
+                    *reinterpret_cast<half4 *>(row + 8 * k) = f;
+                }
+                wave_sync();
+                const int fy0 = __shfl(first, bird, 64), fy1 = __shfl(first, bird + 4, 64);
+                const int fx0 = __shfl(first, bird + 32, 64), fx1 = __shfl(first, bird + 36, 64);
+                const int ry = scratch_y + bird * rowy, rx = scratch_x + bird * rowx;
+                operands<TN>(bx, LaneBirds{rx, xoff - fx0, rx + 4 * rowx, xoff - fx1}, ncx, lds);
+                operands<TM>(ay, LaneBirds{ry, yoff - fy0, ry + 4 * rowy, yoff - fy1}, ncy, lds);
+            } else {
+                const GBird *sb = ring + (head & (kGRing - 1)) + bird;
+                const int4 q0 = *reinterpret_cast<const int4 *>(sb), q1 = *reinterpret_cast<const int4 *>(sb + 4);
+                operands<TN>(bx, LaneBirds{q0.z, q0.w + xoff, q1.z, q1.w + xoff}, ncx, lds);
+                operands<TM>(ay, LaneBirds{q0.x, q0.y + yoff, q1.x, q1.y + yoff}, ncy, lds);
+            }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int m = 0; m < TM; ++m)
@@ -533,9 +412,11 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
                 for (int h = 0; h < kGPair; ++h) {
                     if (keep[h]) {
-                        GBird gb;
-                        stage_axis(q[h].y, gg.ay, inv_cy, &gb.rb_y, &gb.g_y);
-                        stage_axis(q[h].x, gg.ax, inv_cx, &gb.rb_x, &gb.g_x);
+                        GBird gb{q[h].y, 0, q[h].x, 0};
+                        if constexpr (!DIRECT) {
+                            stage_axis(q[h].y, gg.ay, inv_cy, &gb.rb_y, &gb.g_y);
+                            stage_axis(q[h].x, gg.ax, inv_cx, &gb.rb_x, &gb.g_x);
+                        }
                         ring[(tail + __popcll(m[h] & below)) & (kGRing - 1)] = gb;
                     }
                     tail += __popcll(m[h]);
@@ -618,84 +499,70 @@ __global__ __launch_bounds__(256) void density_reduce_kernel(float *density, con
     }
 }
 
-template <int RM, int RN>
-hipError_t launch_recur(const DensityArgs &a, const Geometry &g, const DensityPlan &p, hipStream_t stream) {
-    const long long blocks = (long long)a.n_frames * p.regions_y * p.regions_x;
-    hipLaunchKernelGGL((density_recur_kernel<RM, RN>), dim3((unsigned)blocks), dim3(kRThreads), 0, stream, a, g,
-                       p.regions_y, p.regions_x);
-    return hipGetLastError();
-}
-
 struct Shape {
     int rm, rn;
 };
-// instantiated region shapes of the recurrence path (tiles of 32 x 32; at
-// most 12 tiles per region)
-constexpr Shape kShapes[] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {1, 4}, {3, 2},
-                             {2, 4}, {3, 4}, {4, 2}, {5, 2}, {4, 1}, {5, 1}};
-// instantiated region shapes of the gather path (tiles of 16 x 16; at most 36
+// instantiated region shapes (tiles of 16 x 16; at most 36
 // tiles per region, so that the accumulators and operands fit the registers
 // of two waves per SIMD without spilling)
+constexpr int kDirectTiles = 32;  // the direct path's registers hold this many
 constexpr Shape kGShapes[] = {{1, 1}, {2, 2}, {1, 4}, {4, 1}, {2, 4}, {4, 2}, {3, 4},
                               {4, 4}, {5, 4}, {9, 2}, {9, 4}, {3, 8}, {4, 8}};
 
-Geometry make_geometry(const DensityArgs &a) {
-    Geometry g;
-    const double s = (double)a.sigma_px;
-    const double hx = (double)a.width_px / a.grid_w, hy = (double)a.height_px / a.grid_h;
-    g.hx = (float)hx;
-    g.hy = (float)hy;
-    g.inv_hx = (float)(1.0 / hx);
-    g.inv_hy = (float)(1.0 / hy);
-    g.neg_k = (float)(-1.4426950408889634 / (2.0 * s * s));
-    g.cut = (float)(kCutSigmas * s);
-    g.scale = (float)(1.0 / (2.0 * 3.14159265358979323846 * s * s) / ((double)kLift * kLift));
-    g.recur_x = hx <= 2.0 * s;
-    g.recur_y = hy <= 2.0 * s;
-    return g;
-}
-
-// Factor-table geometry of the gather path; false when it does not apply (a
-// cell is not a whole number of quanta, or the tables exceed their budget).
-bool make_gather_geom(const DensityArgs &a, GatherGeom *gg) {
-    if ((16LL * a.height_px) % a.grid_h != 0 || (16LL * a.width_px) % a.grid_w != 0) return false;
-    const double cut_q = 16.0 * kCutSigmas * (double)a.sigma_px;  // window half-width, quanta
-    auto axis = [&](int64_t c, GatherAxis *t) {
-        if (c < 1 || c > (1 << 20)) return false;
-        // cells G + n with |n| <= j cover every cell centre within cut_q of the bird
-        const double jd = std::ceil(cut_q / (double)c) + 1.0;
-        if (jd > 64.0) return false;
-        t->c = (int32_t)c;
-        t->j = (int32_t)jd;
-        return true;
-    };
-    if (!axis(16LL * a.height_px / a.grid_h, &gg->ay) || !axis(16LL * a.width_px / a.grid_w, &gg->ax)) return false;
-    auto table = [](GatherAxis *t) -> int64_t {
-        if (t->j > kGMaxWindow) return -1;
-        t->j4 = (t->j + 3) / 4;
-        t->nc = t->j4 + (t->j + 3) / 4 + 1;
-        return (8 + 4LL * t->c * table_row_bytes(*t) + 15) / 16 * 16;
-    };
-    const int64_t ty = table(&gg->ay), tx = table(&gg->ax);
-    if (ty < 0 || tx < 0) return false;
-    const bool shared = gg->ay.c == gg->ax.c && gg->ay.j == gg->ax.j;
-    const int64_t bytes = ty + (shared ? 0 : tx);
-    if (bytes > kGMaxTableBytes) return false;
-    gg->ay.tab = 0;
-    gg->ax.tab = shared ? 0 : (int32_t)ty;
-    gg->table_bytes = (int)bytes;
+// LDS beside the tables or scratch: the rings, whose space also holds the
+// cross-wave sum's tiles.
+void gather_lds(GatherGeom *gg) {
     const int ring = kGWaves * kGRing * (int)sizeof(GBird), red = kGWaves * kGRedTiles * 1024;
     gg->red_tiles = gg->table_bytes + red <= kGMaxLds ? kGRedTiles : 2;  // two tiles of every wave take the rings' space
     gg->lds_bytes = gg->table_bytes + std::max(ring, gg->red_tiles == kGRedTiles ? red : 0);
+}
+
+// Window of an axis of n cells over `extent` px: every cell centre within the
+// cut of a bird lies at most j cells from the bird's own.
+void gather_window(GatherAxis *t, int extent, int n, double sigma) {
+    const double h = (double)extent / n;
+    t->h = (float)h;
+    t->inv_h = (float)(1.0 / h);
+    t->j = (int32_t)std::min(std::ceil((double)kCutSigmas * sigma / h) + 1.0, 8192.0);
+    t->j4 = (t->j + 3) / 4;
+    t->nc = 2 * t->j4 + 1;
+}
+
+// Geometry of a launch.  Tables where a cell is a whole number of quanta on
+// both axes and they fit beside the rings; else the direct path, whose scratch
+// depends on the region shape (direct_lds).  FLOCK_DENSITY_PATH=recur takes
+// the direct path for every grid (for tests).
+bool gather_geom(const DensityArgs &a, GatherGeom *gg) {
     const double s = (double)a.sigma_px;
+    gather_window(&gg->ay, a.height_px, a.grid_h, s);
+    gather_window(&gg->ax, a.width_px, a.grid_w, s);
     gg->neg_k = (float)(-1.4426950408889634 / (2.0 * s * s));
     gg->scale = (float)(1.0 / (2.0 * 3.14159265358979323846 * s * s) / ((double)kLift * kLift));
+    gg->ay.c = gg->ax.c = 0;
+    gg->ay.tab = gg->ax.tab = 0;
+    const char *path = std::getenv("FLOCK_DENSITY_PATH");
+    if (path && std::strcmp(path, "recur") == 0) return false;
+    if ((16LL * a.height_px) % a.grid_h != 0 || (16LL * a.width_px) % a.grid_w != 0) return false;
+    const int64_t cy = 16LL * a.height_px / a.grid_h, cx = 16LL * a.width_px / a.grid_w;
+    auto bytes = [](int64_t c, const GatherAxis &t) { return (8 + 4 * c * table_row_bytes(t) + 15) / 16 * 16; };
+    if (cy > kGMaxTableBytes || cx > kGMaxTableBytes) return false;
+    const bool shared = cy == cx && gg->ay.j == gg->ax.j;
+    const int64_t ty = bytes(cy, gg->ay), all = ty + (shared ? 0 : bytes(cx, gg->ax));
+    if (all > kGMaxTableBytes) return false;
+    gg->ay.c = (int32_t)cy;
+    gg->ax.c = (int32_t)cx;
+    gg->ax.tab = shared ? 0 : (int32_t)ty;
+    gg->table_bytes = (int)all;
+    gather_lds(gg);
     return true;
 }
 
-long long shape_regions(const Shape &sh, int tile, int grid_w, int grid_h) {
-    return ((grid_h + (long long)tile * sh.rm - 1) / ((long long)tile * sh.rm)) *
-           ((grid_w + (long long)tile * sh.rn - 1) / ((long long)tile * sh.rn));
+// The direct path's scratch for regions of rm x rn tiles (at most 52 chunks
+// per bird for the instantiated shapes: 13 KiB per wave).
+void direct_lds(GatherGeom *gg, int rm, int rn) {
+    const int chunks = std::min(gg->ay.nc, 4 * rm) + std::min(gg->ax.nc, 4 * rn) + 2;
+    gg->table_bytes = kGWaves * ((8 + 32 * 8 * chunks + 15) / 16 * 16);
+    gather_lds(gg);
 }
 
 // Share of a frame's birds whose window of 2 j + 1 cells meets one region
@@ -713,23 +580,29 @@ long long axis_regions(int grid_n, int rows) { return (grid_n + rows - 1) / rows
 // error, 9% at most).  A 32-bird k-step costs its tile reads and its MFMAs,
 // which did not overlap; every block of 64 birds costs its test on each
 // region.
-double step_us(const Shape &sh) { return 0.0135 * (sh.rm + sh.rn) + 0.0159 * sh.rm * sh.rn; }
+constexpr double kChunkUs = 0.113;  // four factors per lane on the direct path
 constexpr double kBlockUs = 0.335;  // a 64-bird block's test and staging
 constexpr double kTileUs = 0.11;    // a tile's sum over an item's waves
 constexpr double kGroupUs = 1.0;    // a workgroup's start on an item group
 constexpr double kLaunchUs = 5.0;   // launch and table build
 constexpr double kSliceSumUs = 4.0; // the second kernel of a launch split into bird slices
 
+// A step of the direct path also makes its factors, by the longer of a lane's
+// two axes.
+double step_us(const Shape &sh, const GatherGeom &gg) {
+    const double us = 0.0135 * (sh.rm + sh.rn) + 0.0159 * sh.rm * sh.rn;
+    return gg.ay.c ? us : us + kChunkUs * std::max(std::min(gg.ay.nc, 4 * sh.rm), std::min(gg.ax.nc, 4 * sh.rn));
+}
 struct GatherCost {
     long long ry, rx;
     double kept;  // birds an item keeps, on average
 };
 
-GatherCost gather_regions(const Shape &sh, int jy, int jx, int grid_w, int grid_h, double birds) {
+GatherCost gather_regions(const Shape &sh, const GatherGeom &gg, int grid_w, int grid_h, double birds) {
     GatherCost g;
     g.ry = axis_regions(grid_h, 16 * sh.rm);
     g.rx = axis_regions(grid_w, 16 * sh.rn);
-    g.kept = birds * meet_share(jy, 16 * sh.rm, g.ry) * meet_share(jx, 16 * sh.rn, g.rx);
+    g.kept = birds * meet_share(gg.ay.j, 16 * sh.rm, g.ry) * meet_share(gg.ax.j, 16 * sh.rn, g.rx);
     return g;
 }
 
@@ -738,26 +611,28 @@ GatherCost gather_regions(const Shape &sh, int jy, int jx, int grid_w, int grid_
 // the item groups in turn; one round of workgroups ends with its fullest
 // region (about 1.25 times the average unless all eight waves share each
 // region).
-double gather_us(const Shape &sh, int waves, int split, const GatherCost &g, long long n_frames, double birds,
-                 int n_cus) {
+double gather_us(const Shape &sh, int waves, int split, const GatherGeom &gg, const GatherCost &g,
+                 long long n_frames, double birds, int n_cus) {
     const long long items = n_frames * g.ry * g.rx * split, groups = (items * waves + kGWaves - 1) / kGWaves;
     const long long cus = std::max(n_cus, 1);
     const double rounds = groups <= 4 * cus ? (double)((groups + cus - 1) / cus) : (double)groups / cus;
     const double uneven = rounds == 1.0 && waves < kGWaves ? 1.25 : 1.0;
     const double units = (double)waves * split, steps = g.kept * uneven / (kGStep * units) + 0.5;
     return kLaunchUs + (split > 1 ? kSliceSumUs : 0.0) +
-           rounds * (kGroupUs + steps * step_us(sh) + std::max(birds / (64.0 * units), 1.0) * kBlockUs +
+           rounds * (kGroupUs + steps * step_us(sh, gg) + std::max(birds / (64.0 * units), 1.0) * kBlockUs +
                      (waves > 1 ? kTileUs * sh.rm * sh.rn : 0.0));
 }
 
 // Region shape and waves per item of least modelled time.
-Shape gather_shape(int jy, int jx, int grid_w, int grid_h, long long n_frames, double birds, int n_cus, int *waves) {
+Shape gather_shape(const GatherGeom &gg, int grid_w, int grid_h, long long n_frames, double birds, int n_cus,
+                   int *waves) {
     Shape best = kGShapes[0];
     double best_us = 1e300;
     for (const Shape &sh : kGShapes) {
-        const GatherCost g = gather_regions(sh, jy, jx, grid_w, grid_h, birds);
+        if (!gg.ay.c && sh.rm * sh.rn > kDirectTiles) continue;
+        const GatherCost g = gather_regions(sh, gg, grid_w, grid_h, birds);
         for (int w = 1; w <= kGWaves; w *= 2) {
-            const double us = gather_us(sh, w, 1, g, n_frames, birds, n_cus);
+            const double us = gather_us(sh, w, 1, gg, g, n_frames, birds, n_cus);
             if (us < best_us * 0.999) {
                 best = sh;
                 *waves = w;
@@ -770,13 +645,13 @@ Shape gather_shape(int jy, int jx, int grid_w, int grid_h, long long n_frames, d
 
 // Region shape of a launch split into bird slices (at most 16 tiles, see
 // plan_density): least modelled work per frame, whatever its spread.
-Shape gather_split_shape(int jy, int jx, int grid_w, int grid_h, double birds) {
+Shape gather_split_shape(const GatherGeom &gg, int grid_w, int grid_h, double birds) {
     Shape best = kGShapes[0];
     double best_us = 1e300;
     for (const Shape &sh : kGShapes) {
         if (sh.rm * sh.rn > 16) continue;
-        const GatherCost g = gather_regions(sh, jy, jx, grid_w, grid_h, birds);
-        const double us = (g.kept / kGStep * step_us(sh) + birds / 64.0 * kBlockUs + kGroupUs) * (double)(g.ry * g.rx);
+        const GatherCost g = gather_regions(sh, gg, grid_w, grid_h, birds);
+        const double us = (g.kept / kGStep * step_us(sh, gg) + birds / 64.0 * kBlockUs + kGroupUs) * (double)(g.ry * g.rx);
         if (us < best_us * 0.999) {
             best = sh;
             best_us = us;
@@ -798,7 +673,14 @@ int env_int(const char *name) {
 // sum across waves).  `birds` is the birds an item keeps (those whose window
 // meets its region), on average.  FLOCK_DENSITY_WAVES / FLOCK_DENSITY_SPLIT
 // override (for tuning and tests).
-void gather_split(int64_t n_frames, double birds, long long regions, int n_cus, int *waves, int *split) {
+struct GatherForce {
+    int waves, split;  // 0: not forced
+};
+
+GatherForce gather_force() { return {env_int("FLOCK_DENSITY_WAVES"), env_int("FLOCK_DENSITY_SPLIT")}; }
+
+void gather_split(int64_t n_frames, double birds, long long regions, int n_cus, const GatherForce &force, int *waves,
+                  int *split) {
     const long long items = (long long)n_frames * regions;
     const long long resident = (long long)kGWaves * std::max(n_cus, 1);
     int w = 1;
@@ -812,9 +694,8 @@ void gather_split(int64_t n_frames, double birds, long long regions, int n_cus, 
         sp = std::min<long long>(sp, std::max<long long>(1, (long long)(birds / (w * kGMinWaveBirds))));
         sp = std::min<long long>(sp, 64);
     }
-    const int fw = env_int("FLOCK_DENSITY_WAVES"), fs = env_int("FLOCK_DENSITY_SPLIT");
-    if (fw == 1 || fw == 2 || fw == 4 || fw == 8) w = fw;
-    if (fs >= 1 && fs <= 64) sp = fs;
+    if (force.waves == 1 || force.waves == 2 || force.waves == 4 || force.waves == 8) w = force.waves;
+    if (force.split >= 1 && force.split <= 64) sp = force.split;
     *waves = w;
     *split = (int)sp;
 }
@@ -853,167 +734,107 @@ size_t density_workspace_bytes(int32_t n_frames, int32_t total, int32_t grid_w, 
     // not know: bound the split over every shape, with every bird kept (a
     // split only shrinks when an item keeps fewer birds)
     const double birds = (double)total / n_frames;
+    const GatherForce force = gather_force();
     int most = 1;
     for (const Shape &sh : kGShapes) {
         int waves = 1, split = 1;
-        gather_split(n_frames, birds, shape_regions(sh, 16, grid_w, grid_h), n_cus, &waves, &split);
+        gather_split(n_frames, birds, axis_regions(grid_h, 16 * sh.rm) * axis_regions(grid_w, 16 * sh.rn), n_cus, force,
+                     &waves, &split);
         most = std::max(most, split);
     }
     if (most <= 1) return 0;
     return (size_t)n_frames * most * (size_t)grid_w * grid_h * sizeof(float);
 }
 
-// Gather path whenever its tables apply; otherwise the recurrence path, whose
-// region per workgroup comes from a small cost model: per bird a region costs
-// its matrix-core time (RM*RN/2 cycles), the factor rows its windows cover and
-// its tile clearing; workgroups spread over the compute units, and a launch
-// never finishes before one workgroup does.
-// FLOCK_DENSITY_PATH="recur" forces the recurrence path and
-// FLOCK_DENSITY_SHAPE="rm,rn" its region shape (for tuning).
-DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t lds_limit) {
-    const int tiles_y = (a.grid_h + 31) / 32;
-    const int tiles_x = (a.grid_w + 31) / 32;
+// The launch plan of either path: region shape, waves per item and bird slices
+// of least modelled time.  FLOCK_DENSITY_SHAPE="rm,rn" forces the region shape
+// (for tuning).
+DensityPlan plan_density(const DensityArgs &a, int n_cus) {
     const char *force = std::getenv("FLOCK_DENSITY_SHAPE");
-    const char *path = std::getenv("FLOCK_DENSITY_PATH");
-    const bool force_recur = path && std::strcmp(path, "recur") == 0;
     GatherGeom gg;
-    if (!force_recur && make_gather_geom(a, &gg) && (size_t)gg.lds_bytes <= lds_limit) {
-        const double birds = a.n_frames > 0 ? (double)a.total / a.n_frames : 0.0;
-        DensityPlan p{};
-        p.gather = 1;
-        p.split = 1;
-        Shape sh = gather_shape(gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, a.n_frames, birds, n_cus, &p.waves);
-        GatherCost g = gather_regions(sh, gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, birds);
-        int grm = 0, grn = 0;
-        bool forced = false;
-        if (force && std::sscanf(force, "%d,%d", &grm, &grn) == 2)
-            for (const Shape &k : kGShapes)
-                if (k.rm == grm && k.rn == grn) {
-                    sh = k;
-                    forced = true;
-                }
-        const int fs = env_int("FLOCK_DENSITY_SPLIT"), fw = env_int("FLOCK_DENSITY_WAVES");
-        if (forced) {
-            gather_split(a.n_frames, g.kept, g.ry * g.rx, n_cus, &p.waves, &p.split);
-        } else {
-            // bird slices where they pay for the second kernel: a launch that
-            // would leave most of the chip idle is bound by each wave's own
-            // path, whose fixed part grows with the tiles an item's waves add
-            // up at the end (kGRedTiles per round); shapes of at most 16
-            // tiles keep that to two rounds
-            const Shape ss = gather_split_shape(gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, birds);
-            const GatherCost sg = gather_regions(ss, gg.ay.j, gg.ax.j, a.grid_w, a.grid_h, birds);
-            int sw = 1, sp = 1;
-            gather_split(a.n_frames, sg.kept, sg.ry * sg.rx, n_cus, &sw, &sp);
-            if (fs >= 1 || fw >= 1 ||
-                (sp > 1 && gather_us(ss, sw, sp, sg, a.n_frames, birds, n_cus) <
-                               gather_us(sh, p.waves, 1, g, a.n_frames, birds, n_cus))) {
-                sh = ss;
-                g = sg;
-                p.waves = sw;
-                p.split = sp;
+    gather_geom(a, &gg);
+    const double birds = a.n_frames > 0 ? (double)a.total / a.n_frames : 0.0;
+    DensityPlan p{};
+    p.split = 1;
+    Shape sh = gather_shape(gg, a.grid_w, a.grid_h, a.n_frames, birds, n_cus, &p.waves);
+    GatherCost g = gather_regions(sh, gg, a.grid_w, a.grid_h, birds);
+    int grm = 0, grn = 0;
+    bool forced = false;
+    if (force && std::sscanf(force, "%d,%d", &grm, &grn) == 2)
+        for (const Shape &k : kGShapes)
+            if (k.rm == grm && k.rn == grn && (gg.ay.c || grm * grn <= kDirectTiles)) {
+                sh = k;
+                g = gather_regions(sh, gg, a.grid_w, a.grid_h, birds);
+                forced = true;
             }
+    const GatherForce over = gather_force();
+    if (forced) {
+        gather_split(a.n_frames, g.kept, g.ry * g.rx, n_cus, over, &p.waves, &p.split);
+    } else {
+        // bird slices where they pay for the second kernel: a launch that
+        // would leave most of the chip idle is bound by each wave's own
+        // path, whose fixed part grows with the tiles an item's waves add
+        // up at the end (kGRedTiles per round); shapes of at most 16
+        // tiles keep that to two rounds
+        const Shape ss = gather_split_shape(gg, a.grid_w, a.grid_h, birds);
+        const GatherCost sg = gather_regions(ss, gg, a.grid_w, a.grid_h, birds);
+        int sw = 1, sp = 1;
+        gather_split(a.n_frames, sg.kept, sg.ry * sg.rx, n_cus, over, &sw, &sp);
+        if (over.split >= 1 || over.waves >= 1 ||
+            (sp > 1 && gather_us(ss, sw, sp, gg, sg, a.n_frames, birds, n_cus) <
+                           gather_us(sh, p.waves, 1, gg, g, a.n_frames, birds, n_cus))) {
+            sh = ss;
+            g = sg;
+            p.waves = sw;
+            p.split = sp;
         }
-        p.rm = sh.rm;
-        p.rn = sh.rn;
-        p.regions_y = (int)g.ry;
-        p.regions_x = (int)g.rx;
-        const long long items = (long long)a.n_frames * g.ry * g.rx * p.split;
-        const int per_wg = kGWaves / p.waves;
-        if (items > 0xffffffffLL) {  // item numbers are 32 bits wide: refused by the caller's check of `blocks`
-            p.blocks = items;
-            return p;
-        }
-        // a workgroup takes its share of the item groups one after another,
-        // with one table build: 256 x 8000 with eight waves per item took 91
-        // against 103 us with a workgroup per group
-        p.blocks = std::min<long long>((items + per_wg - 1) / per_wg, std::max(n_cus, 1));
+    }
+    p.rm = sh.rm;
+    p.rn = sh.rn;
+    p.regions_y = (int)g.ry;
+    p.regions_x = (int)g.rx;
+    const long long items = (long long)a.n_frames * g.ry * g.rx * p.split;
+    const int per_wg = kGWaves / p.waves;
+    if (items > 0xffffffffLL) {  // item numbers are 32 bits wide: refused by the caller's check of `blocks`
+        p.blocks = items;
         return p;
     }
-    int frm = 0, frn = 0;
-    if (force && std::sscanf(force, "%d,%d", &frm, &frn) == 2) {
-        bool known = false;
-        for (const Shape &sh : kShapes) known |= sh.rm == frm && sh.rn == frn;
-        if (!known) frm = frn = 0;
-    }
-    DensityPlan best{};
-    best.rm = best.rn = 1;
-    best.split = best.waves = 1;
-    if (frm) {
-        best.rm = frm;
-        best.rn = frn;
-        best.regions_y = (tiles_y + frm - 1) / frm;
-        best.regions_x = (tiles_x + frn - 1) / frn;
-        best.blocks = (long long)a.n_frames * best.regions_y * best.regions_x;
-        return best;
-    }
-    const double s = (double)a.sigma_px;
-    const double hx = (double)a.width_px / a.grid_w, hy = (double)a.height_px / a.grid_h;
-    const double lx = std::min(2.0 * kCutSigmas * s / hx + 1.0, (double)a.grid_w);
-    const double ly = std::min(2.0 * kCutSigmas * s / hy + 1.0, (double)a.grid_h);
-    const double birds = a.n_frames > 0 ? (double)a.total / a.n_frames : 0.0;
-    double best_t = 1e300;
-    for (const Shape &sh : kShapes) {
-        if (sh.rm > tiles_y && sh.rm > 1) continue;
-        if (sh.rn > tiles_x && sh.rn > 1) continue;
-        const int ry = (tiles_y + sh.rm - 1) / sh.rm, rx = (tiles_x + sh.rn - 1) / sh.rn;
-        const double rows_y = std::min(ly, 32.0 * sh.rm) * std::min(1.0, (32.0 * sh.rm + ly) / (32.0 * tiles_y));
-        const double rows_x = std::min(lx, 32.0 * sh.rn) * std::min(1.0, (32.0 * sh.rn + lx) / (32.0 * tiles_x));
-        const double per_bird = sh.rm * sh.rn * 0.5 + (rows_x + rows_y) / 11.0 + (sh.rm + sh.rn) * 0.0625 + 0.5;
-        const double per_block = birds * per_bird + 2000.0;
-        const double blocks = (double)a.n_frames * ry * rx;
-        const double t = std::max(blocks * per_block / n_cus, per_block);
-        if (t < best_t * 0.999) {
-            best_t = t;
-            best.rm = sh.rm;
-            best.rn = sh.rn;
-            best.regions_y = ry;
-            best.regions_x = rx;
-        }
-    }
-    if (best.regions_y == 0) {
-        best.regions_y = tiles_y;
-        best.regions_x = tiles_x;
-    }
-    best.blocks = (long long)a.n_frames * best.regions_y * best.regions_x;
-    return best;
+    // a workgroup takes its share of the item groups one after another, with
+    // one table build: 256 x 8000 with eight waves per item took 91 against
+    // 103 us with a workgroup per group
+    p.blocks = std::min<long long>((items + per_wg - 1) / per_wg, std::max(n_cus, 1));
+    return p;
 }
 
 hipError_t launch_density(const DensityArgs &a, const DensityPlan &p, float *partial, hipStream_t stream) {
+    GatherGeom gg;
+    const bool tables = gather_geom(a, &gg);
+    if (!tables) direct_lds(&gg, p.rm, p.rn);
+    if (p.split > 1 && !partial) return hipErrorInvalidValue;
+    const uint32_t items = (uint32_t)((long long)a.n_frames * p.regions_y * p.regions_x * p.split);
     hipError_t err = hipErrorInvalidValue;
-    if (p.gather) {
-        GatherGeom gg;
-        if (!make_gather_geom(a, &gg)) return hipErrorInvalidValue;
-        if (p.split > 1 && !partial) return hipErrorInvalidValue;
-        const long long items = (long long)a.n_frames * p.regions_y * p.regions_x * p.split;
-#define FLOCK_GSHAPE(TM, TN)                                                                                     \
-    if (p.rm == TM && p.rn == TN) {                                                                              \
-        hipLaunchKernelGGL((density_gather_kernel<TM, TN>), dim3((unsigned)p.blocks), dim3(kGThreads),          \
-                           (size_t)gg.lds_bytes, stream, a, gg, p.regions_y, p.regions_x, p.split, p.waves, \
-                           (uint32_t)items, \
-                           partial);                                                                             \
-        err = hipGetLastError();                                                                                 \
+#define FLOCK_LAUNCH(TM, TN, DIRECT)                                                                              \
+    hipLaunchKernelGGL((density_gather_kernel<TM, TN, DIRECT>), dim3((unsigned)p.blocks), dim3(kGThreads),        \
+                       (size_t)gg.lds_bytes, stream, a, gg, p.regions_y, p.regions_x, p.split, p.waves, items, partial)
+#define FLOCK_GSHAPE(TM, TN)                                                                                      \
+    if (p.rm == TM && p.rn == TN) {                                                                               \
+        if (tables) FLOCK_LAUNCH(TM, TN, false);                                                                  \
+        else if (TM * TN <= kDirectTiles) FLOCK_LAUNCH(TM, TN, (TM * TN <= kDirectTiles));                         \
+        else return hipErrorInvalidValue;                                                                         \
+        err = hipGetLastError();                                                                                  \
     }
-        FLOCK_GSHAPE(1, 1) FLOCK_GSHAPE(2, 2) FLOCK_GSHAPE(1, 4) FLOCK_GSHAPE(4, 1) FLOCK_GSHAPE(2, 4)
-        FLOCK_GSHAPE(4, 2) FLOCK_GSHAPE(3, 4) FLOCK_GSHAPE(4, 4) FLOCK_GSHAPE(5, 4)
-        FLOCK_GSHAPE(9, 2) FLOCK_GSHAPE(9, 4) FLOCK_GSHAPE(3, 8) FLOCK_GSHAPE(4, 8)
+    FLOCK_GSHAPE(1, 1) FLOCK_GSHAPE(2, 2) FLOCK_GSHAPE(1, 4) FLOCK_GSHAPE(4, 1) FLOCK_GSHAPE(2, 4)
+    FLOCK_GSHAPE(4, 2) FLOCK_GSHAPE(3, 4) FLOCK_GSHAPE(4, 4) FLOCK_GSHAPE(5, 4)
+    FLOCK_GSHAPE(9, 2) FLOCK_GSHAPE(9, 4) FLOCK_GSHAPE(3, 8) FLOCK_GSHAPE(4, 8)
 #undef FLOCK_GSHAPE
-        if (err != hipSuccess || p.split <= 1) return err;
-        const int64_t cells = (int64_t)a.grid_h * a.grid_w;
-        const int64_t total = cells * a.n_frames;
-        const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 4096);
-        hipLaunchKernelGGL(density_reduce_kernel, dim3(blocks), dim3(256), 0, stream, a.density, partial, cells,
-                           total, p.split, gg.scale);
-        return hipGetLastError();
-    }
-    const Geometry g = make_geometry(a);
-#define FLOCK_SHAPE(RM, RN) \
-    if (p.rm == RM && p.rn == RN) return launch_recur<RM, RN>(a, g, p, stream);
-    FLOCK_SHAPE(1, 1) FLOCK_SHAPE(1, 2) FLOCK_SHAPE(2, 1) FLOCK_SHAPE(2, 2) FLOCK_SHAPE(1, 4)
-    FLOCK_SHAPE(3, 2) FLOCK_SHAPE(2, 4) FLOCK_SHAPE(3, 4) FLOCK_SHAPE(4, 2) FLOCK_SHAPE(5, 2)
-    FLOCK_SHAPE(4, 1) FLOCK_SHAPE(5, 1)
-#undef FLOCK_SHAPE
-    return err;
+#undef FLOCK_LAUNCH
+    if (err != hipSuccess || p.split <= 1) return err;
+    const int64_t cells = (int64_t)a.grid_h * a.grid_w;
+    const int64_t total = cells * a.n_frames;
+    const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 4096);
+    hipLaunchKernelGGL(density_reduce_kernel, dim3(blocks), dim3(256), 0, stream, a.density, partial, cells, total,
+                       p.split, gg.scale);
+    return hipGetLastError();
 }
 
 }  // namespace flock

@@ -67,7 +67,6 @@ struct DensityArgs {
     const int32_t *offsets;
     int32_t n_frames;
     int32_t total;
-    int32_t max_frame_points; // bound used to size the per-frame sort (0: no sort)
     int32_t width_px, height_px;
     int32_t grid_w, grid_h;
     float sigma_px;
@@ -75,17 +74,14 @@ struct DensityArgs {
 };
 
 struct DensityPlan {
-    int gather;               // 1: factor tables gathered into registers; 0: recurrence
-    int rm;                   // region height in tiles (16 rows gather, 32 recurrence)
-    int rn;                   // region width in tiles
+    int rm, rn;               // region height and width in tiles of 16 x 16 cells
     int regions_y, regions_x; // regions per frame
     int split;                // bird slices per (frame, region); > 1 adds partial grids afterwards
-    int waves;                // gather: waves sharing one (frame, region, slice)
-    int reach;                // gather: tiles a band of 32 rows reaches beyond itself, 0 without bands
+    int waves;                // waves sharing one (frame, region, slice)
     long long blocks;         // workgroups of the main kernel
 };
 
-DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t lds_limit);
+DensityPlan plan_density(const DensityArgs &a, int n_cus);
 // Workspace for the partial grids of a split launch (0 if none); depends on the
 // batch shape and grid only, and bounds every plan for that shape.
 size_t density_workspace_bytes(int32_t n_frames, int32_t total, int32_t grid_w, int32_t grid_h, int n_cus);
