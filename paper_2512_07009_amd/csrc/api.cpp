@@ -560,11 +560,29 @@ flock_status drinker_proximity_frames(const int32_t *xy, const int32_t *offsets,
     return FLOCK_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// One workgroup per frame where the grid's forest fits in LDS, with this many
+// component slots (0: the tiled kernels; FLOCK_HEATMAP_PATH=tiled takes them
+// for every grid).
+int heatmap_slots(int32_t grid_w, int32_t grid_h, const DeviceInfo &dev) {
+    const char *hp = std::getenv("FLOCK_HEATMAP_PATH");
+    if (hp && std::strcmp(hp, "tiled") == 0) return 0;
+    return flock::heatmap_frame_slots(grid_w, grid_h, dev.lds_per_block);
+}
+
+}  // namespace
+
+extern "C" {
+
 size_t heatmap_frames_workspace(int32_t n_frames, int32_t grid_w, int32_t grid_h) {
+    const DeviceInfo *dev = nullptr;
+    const bool known = device_info(&dev) == FLOCK_OK;
     g_error[0] = '\0';
-    // enough for either path (which one runs depends on the device's LDS)
-    return std::max(flock::heatmap_workspace_bytes(n_frames, grid_w, grid_h),
-                    flock::heatmap_frame_workspace_bytes(n_frames, grid_w, grid_h));
+    if (grid_w < 1 || grid_h < 1 || (known && heatmap_slots(grid_w, grid_h, *dev) > 0)) return 0;
+    return flock::heatmap_workspace_bytes(n_frames, grid_w, grid_h);
 }
 
 flock_status heatmap_frames(const float *density, int32_t n_frames, int32_t grid_w, int32_t grid_h,
@@ -597,13 +615,8 @@ flock_status heatmap_frames(const float *density, int32_t n_frames, int32_t grid
     flock_status st = device_info(&dev);
     if (st != FLOCK_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    // one workgroup per frame when the grid's forest fits in LDS
-    // (FLOCK_HEATMAP_PATH=tiled takes the tiled kernels for every grid)
-    const char *hp = std::getenv("FLOCK_HEATMAP_PATH");
-    const bool tiled = hp && std::strcmp(hp, "tiled") == 0;
-    const bool resident = !tiled && flock::heatmap_frame_lds_bytes(grid_w, grid_h) + 4096 <= dev->lds_per_block;
-    const size_t need = resident ? flock::heatmap_frame_workspace_bytes(n_frames, grid_w, grid_h)
-                                 : flock::heatmap_workspace_bytes(n_frames, grid_w, grid_h);
+    const int frame_slots = heatmap_slots(grid_w, grid_h, *dev);
+    const size_t need = frame_slots > 0 ? 0 : flock::heatmap_workspace_bytes(n_frames, grid_w, grid_h);
     if (workspace && workspace_bytes < need)
         return fail(FLOCK_ENOMEM, "workspace of %zu bytes < %zu needed", workspace_bytes, need);
     if (workspace && !aligned(workspace, 256)) return fail(FLOCK_EINVAL, "workspace must be 256-byte aligned");
@@ -628,7 +641,7 @@ flock_status heatmap_frames(const float *density, int32_t n_frames, int32_t grid
     a.degree = degree;
     a.comp_cells = comp_cells;
     a.comp_mass = comp_mass;
-    err = flock::launch_heatmap(a, ws, resident, s);
+    err = flock::launch_heatmap(a, ws, frame_slots, dev->n_cus, s);
     if (!workspace && need > 0) {
         const hipError_t ferr = hipFreeAsync(ws, s);
         if (err == hipSuccess) err = ferr;

@@ -14,10 +14,10 @@
 //                of the positive cells (0 when S = 0);
 //   degree       (sum of density over hot cells) / S (0 when S = 0).
 //
-// Design (HBM-bound: a few bytes per cell).  Grids whose int32 forest fits
-// in LDS (grid_w * grid_h <= about 39k cells) take heat_frame_kernel, one
-// workgroup per frame (described there).  Larger grids take four tiled
-// kernels:
+// Design.  Grids whose int32 forest fits in LDS with the kernel's bit words
+// and component slots (grid_w * grid_h <= about 38k cells) take
+// heat_frame_kernel, one workgroup per frame (described there).  Larger grids
+// take four tiled kernels:
 //   1. heat_tile_kernel, one 256-thread workgroup per 32 x 32 tile: loads the
 //      tile once, unites hot neighbours inside the tile in LDS (smallest
 //      index hooking), writes each hot cell's tile root (frame index) into
@@ -39,6 +39,7 @@
 
 #include <climits>
 #include <cmath>
+#include <type_traits>
 
 #include "cluster_common.h"
 #include "internal.h"
@@ -83,14 +84,28 @@ struct LnTable {
     double ln_c[kLnBuckets], inv_c[kLnBuckets];
 };
 
-// Filled by threads 0 .. kLnBuckets - 1; the caller syncs before use.
-__device__ __forceinline__ void ln_table_init(LnTable &t) {
-    const int k = threadIdx.x;
-    if (k < kLnBuckets) {
+// The table is a constant of the program: ln c = 2 atanh((c - 1) / (c + 1)) by
+// its series (z <= 1/3: the terms fall by 9 each, 20 of them pass below 2^-60).
+// Filling it with the library's log in every workgroup took about 1.5 us of
+// each.
+constexpr LnTable make_ln_table() {
+    LnTable t{};
+    for (int k = 0; k < kLnBuckets; ++k) {
         const double c = 1.0 + ((double)k + 0.5) / kLnBuckets;
-        t.ln_c[k] = log(c);
+        const double z = (c - 1.0) / (c + 1.0), z2 = z * z;
+        double sum = 0.0;
+        for (int i = 19; i >= 0; --i) sum = sum * z2 + 1.0 / (2 * i + 1);
+        t.ln_c[k] = 2.0 * z * sum;
         t.inv_c[k] = 1.0 / c;
     }
+    return t;
+}
+__device__ const LnTable kLnTable = make_ln_table();
+
+// Copied by the first 2 kLnBuckets threads; the caller syncs before use.
+__device__ __forceinline__ void ln_table_load(LnTable &t) {
+    const int k = threadIdx.x;
+    if (k < 2 * kLnBuckets) reinterpret_cast<double *>(&t)[k] = reinterpret_cast<const double *>(&kLnTable)[k];
 }
 
 __device__ __forceinline__ double ln_pos(float vf, const LnTable &t) {
@@ -126,7 +141,7 @@ __global__ __launch_bounds__(kHThreads) void heat_tile_kernel(HeatArgs a, TilePa
     __shared__ double s_red[3][kHThreads / 64];
     __shared__ uint32_t s_max[kHThreads / 64];
     __shared__ LnTable lnt;
-    ln_table_init(lnt);
+    ln_table_load(lnt);
     __syncthreads();
     const TileGeom t = tile_of(a, blockIdx.x);
     const int tid = threadIdx.x, lx = tid % kHT, ly0 = tid / kHT;
@@ -359,92 +374,171 @@ __global__ __launch_bounds__(256) void heat_mass_kernel(HeatArgs a, const int32_
     a.comp_mass[i] = ldexp((double)q, -shift[f]) * a.cell_area;
 }
 
-// The same for the frame-resident path, over each frame's list of label
-// cells only (one workgroup per frame).
-__global__ __launch_bounds__(256) void heat_root_mass_kernel(HeatArgs a, const int32_t *shift,
-                                                             const int32_t *roots) {
-    const int f = blockIdx.x;
-    const size_t cells = (size_t)a.grid_w * a.grid_h;
-    const int n = a.n_components[f];
-    const int sh = shift[f];
-    unsigned long long *CMu = reinterpret_cast<unsigned long long *>(a.comp_mass) + (size_t)f * cells;
-    double *CM = a.comp_mass + (size_t)f * cells;
-    for (int t = threadIdx.x; t < n; t += 256) {
-        const int32_t c = roots[(size_t)f * cells + t];
-        CM[c] = ldexp((double)CMu[c], -sh) * a.cell_area;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Frame-resident path: one workgroup per frame, the whole grid's forest in LDS
 // ---------------------------------------------------------------------------
 
-constexpr int kFThreads = 1024;
-constexpr int kFWaves = kFThreads / 64;
 
-// Inclusive prefix sum over the wave (64-bit values).
+// v of the lane `SHIFT` lanes below in the row of 16 (DPP control CTRL), 0
+// where there is none.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_or_zero(unsigned long long v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, false);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// Inclusive prefix sum over the wave (64-bit values), by DPP: shifts of 1, 2,
+// 4 and 8 lanes within the rows of 16, then the last lane of a row broadcast
+// to the next row (rows 1 and 3), and of the lower half to the upper.
 __device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned long long t = __shfl_up(v, o, 64);
-        if (lane >= o) v += t;
-    }
+    v += dpp_or_zero<0x111, 0xf>(v);
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    v += dpp_or_zero<0x142, 0xa>(v);
+    v += dpp_or_zero<0x143, 0xc>(v);
     return v;
 }
 
-// One frame per 1024-thread workgroup (grid_w * grid_h int32 parents in LDS):
-//   A. one coalesced pass over the grid: hot flags (parent = own index, -1
-//      cold), the partial sums, outputs cleared; a fixed-order block sum
-//      gives entropy, degree and the fixed-point scale;
-//   B. horizontal runs of hot cells, one row per wave at a time and 64 cells
-//      per ballot: every cell of a run points at the run's first cell;
-//   C. joins between consecutive rows, once per overlap: the vertical pair
-//      (c, c + w) unless the pair to its left already joins the same runs,
-//      and for the 8-neighbourhood a diagonal pair only where no edge-sharing
-//      path through c's row neighbour or the cell below exists;
-//   D. labels by read-only walks; per wave, runs of lanes with equal roots
-//      add their cells and fixed-point mass with one global atomic each;
-//      each root cell appends its index to the frame's list in the workspace.
-// heat_root_mass_kernel then converts the listed cells' mass (after the kernel
-// boundary every atomic is complete; a device-scope fence inside the kernel
-// would instead write back the L2 once per workgroup).
-__global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int32_t *shift, int32_t *roots) {
-    extern __shared__ int32_t P[];
+// Sum over the wave in the prefix sum's fixed order, in every lane.
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+    auto shifted = [](double x, auto ctrl, auto rows) {
+        return __longlong_as_double(
+            (long long)dpp_or_zero<decltype(ctrl)::value, decltype(rows)::value>((unsigned long long)__double_as_longlong(x)));
+    };
+    using std::integral_constant;
+    v += shifted(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});
+    v += shifted(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    v += shifted(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    v += shifted(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    v += shifted(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});
+    v += shifted(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// A value equal in every lane, as a scalar.
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32;
+}
+
+// LDS of one frame: the forest (an int32 per cell), two bits per cell in words
+// of 64 consecutive cells (hot; first of its row; zero words past the end, as
+// many as a read one row down needs), and the component slots, as many as are
+// left, at most kMaxSlots.
+constexpr int kMaxSlots = 2048, kMinSlots = 256;
+constexpr size_t kFrameStaticLds = 2560;  // at least the kernel's static shared variables
+struct FrameLds {
+    int words, padded;
+    size_t hot, row0, slot;  // byte offsets
+    __host__ __device__ size_t bytes(int slots) const { return slot + (size_t)slots * 16; }
+};
+
+__host__ __device__ inline FrameLds frame_lds(int gw, int gh) {
+    FrameLds l;
+    l.words = (gw * gh + 63) / 64;
+    l.padded = l.words + gw / 64 + 3;
+    l.hot = ((size_t)gw * gh * sizeof(int32_t) + 15) / 16 * 16;
+    l.row0 = l.hot + (size_t)l.padded * 8;
+    l.slot = (l.row0 + (size_t)l.padded * 8 + 15) / 16 * 16;
+    return l;
+}
+
+// One frame per workgroup, the cells in words of 64 whatever the
+// grid's width.  A wave takes every kFWaves-th word, kFlight of them at a time:
+//   A. the partial sums, and each word's hot bits by ballot: every hot cell
+//      points at the first cell of its horizontal run within the word (no
+//      atomics);
+//   B. joins, found from the bits by a thread per word: a run continued from
+//      the word before, a vertical pair only at the first of consecutive ones
+//      (the others join the same two runs), and for the 8-neighbourhood a
+//      diagonal pair only where neither of the cells between them is hot;
+//      queued and joined a thread each, while one thread turns the sums
+//      (added in a fixed order) into entropy, degree and the fixed-point
+//      scale;
+//   C. every run's first cell points at its root, and roots take component
+//      slots;
+//   D. labels, and the outputs' zeros; per word, the runs' cell counts and
+//      fixed-point masses by one prefix sum, each added to its component's
+//      slot;
+//   E. the slots' totals go to their label cells.
+// More components than slots repeat D's sums for the next slots.
+//
+// Bound by latency: the chain of phases on one compute unit per frame.
+// 64 frames of 128 x 72 cells 23.8 us, 256 of 256 x 144 64, 1800 of 128 x 72
+// 115 (33.2, 124 and 161 when the logarithm table was computed by every
+// workgroup, loads came one at a time, every cell tested its own joins, masses
+// were added by global atomics and a second kernel converted them).
+template <int kFThreads>
+__global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int slots) {
+    constexpr int kFWaves = kFThreads / 64;
+    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double s_red[3][kFWaves];
     __shared__ uint32_t s_max[kFWaves];
-    __shared__ int s_shift, s_ncomp;
+    __shared__ int s_shift, s_ncomp, s_nq;
     __shared__ LnTable lnt;
-    ln_table_init(lnt);
-    __syncthreads();
-    const int f = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int kFlight = 3;
+    const int f = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int gw = a.grid_w, gh = a.grid_h;
     const int cells = gw * gh;
+    const FrameLds l = frame_lds(gw, gh);
+    int32_t *P = reinterpret_cast<int32_t *>(smem);
+    uint64_t *hotw = reinterpret_cast<uint64_t *>(smem + l.hot), *row0w = reinterpret_cast<uint64_t *>(smem + l.row0);
+    unsigned long long *mass = reinterpret_cast<unsigned long long *>(smem + l.slot);
+    int32_t *count = reinterpret_cast<int32_t *>(mass + slots), *label = count + slots;
     const float *D = a.density + (size_t)f * cells;
     int32_t *L = a.labels + (size_t)f * cells;
     int32_t *CC = a.comp_cells + (size_t)f * cells;
     double *CM = a.comp_mass + (size_t)f * cells;
-    unsigned long long *CMu = reinterpret_cast<unsigned long long *>(CM);
+    auto load = [&](int word) { return D[min(64 * word + lane, cells - 1)]; };  // past the end: not used
 
     // A
+    ln_table_load(lnt);
+    float v[kFlight];
+#pragma unroll
+    for (int u = 0; u < kFlight; ++u) v[u] = load(min(wave + kFWaves * u, l.words));
+    if (tid == 0) s_ncomp = s_nq = 0;
+    for (int i = l.words + tid; i < l.padded; i += kFThreads) hotw[i] = row0w[i] = 0ull;
+    int x = (64 * wave + lane) % gw;              // column of this lane's cell
+    const int xstep = (64 * kFWaves) % gw;
+    __syncthreads();
     double s = 0.0, e = 0.0, hs = 0.0;
     uint32_t mb = 0;
-    for (int c = tid; c < cells; c += kFThreads) {
-        const float v = D[c];
-        const bool hot = v >= a.threshold;
-        P[c] = hot ? c : -1;
-        if (v > 0.0f) {
-            s += (double)v;
-            e += (double)v * ln_pos(v, lnt);
-            mb = max(mb, __float_as_uint(v));
+    for (int w0 = wave; w0 < l.words; w0 += kFWaves * kFlight) {
+        double ln[kFlight];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) ln[u] = ln_pos(v[u] > 0.0f ? v[u] : 1.0f, lnt);
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            const int w = w0 + kFWaves * u, c = 64 * w + lane;
+            const float d = v[u];
+            v[u] = load(min(w + kFWaves * kFlight, l.words));
+            const bool in = c < cells, hot = in & (d >= a.threshold), pos = in & (d > 0.0f);
+            s += pos ? (double)d : 0.0;
+            e += pos ? (double)d * ln[u] : 0.0;
+            mb = max(mb, pos ? __float_as_uint(d) : 0u);
+            hs += hot ? (double)d : 0.0;
+            const uint64_t hm = __ballot(hot), r0 = __ballot(in & (x == 0));
+            // first cells of the word's runs, and this lane's run's
+            const uint64_t first = hm & ~((hm << 1) & ~r0);
+            const uint64_t upto = first & (~0ull >> (63 - lane));
+            if (in) P[c] = hot ? 64 * w + 63 - __clzll(upto) : -1;
+            if (lane == 0 && w < l.words) {
+                hotw[w] = hm;
+                row0w[w] = r0;
+            }
+            x += xstep;
+            x -= x >= gw ? gw : 0;
         }
-        if (hot) hs += (double)v;
-        CC[c] = 0;
-        CM[c] = 0.0;
     }
-    s = wave_sum_d(s);
-    e = wave_sum_d(e);
-    hs = wave_sum_d(hs);
+    s = wave_sum_dpp(s);
+    e = wave_sum_dpp(e);
+    hs = wave_sum_dpp(hs);
     mb = wave_max_u(mb);
     if (lane == 0) {
         s_red[0][wave] = s;
@@ -453,7 +547,46 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int32
         s_max[wave] = mb;
     }
     __syncthreads();
-    if (tid == 0) {
+    // B (the queue is in the slots' space; pairs beyond it are joined in place)
+    int2 *queue = reinterpret_cast<int2 *>(smem + l.slot);
+    const int qcap = 2 * slots;
+    // the 64 bits from bit b on
+    auto bits = [&](int b) {
+        const int i = b >> 6, o = b & 63;
+        return (hotw[i] >> o) | (o ? hotw[i + 1] << (64 - o) : 0ull);
+    };
+    for (int i = tid; i < l.words; i += kFThreads) {
+        const uint64_t m = hotw[i];
+        if (m == 0ull) continue;
+        const uint64_t r0 = row0w[i], last = (r0 >> 1) | (row0w[i + 1] << 63);  // cells before the next row's first
+        const uint64_t before = i > 0 ? hotw[i - 1] >> 63 : 0ull;
+        const uint64_t lh = ((m << 1) | before) & ~r0, rh = ((m >> 1) | (hotw[i + 1] << 63)) & ~last;  // left, right hot
+        const uint64_t dn = bits(64 * i + gw), dl = bits(64 * i + gw - 1) & ~r0, dr = bits(64 * i + gw + 1) & ~last;
+        const uint64_t join = m & lh & 1ull;
+        const uint64_t down = m & dn & ~(lh & dl);
+        const uint64_t alone = a.connectivity == 8 ? m & ~dn : 0ull;  // cold below
+        const uint64_t right = alone & dr & ~rh, left = alone & dl & ~lh;
+        const int pairs = __popcll(join) + __popcll(down) + __popcll(right) + __popcll(left);
+        if (pairs == 0) continue;
+        int at = atomicAdd(&s_nq, pairs);
+        auto push = [&](uint64_t set, int d) {
+            for (; set; set &= set - 1) {
+                const int c = 64 * i + (int)__builtin_ctzll(set);
+                if (at < qcap) queue[at] = make_int2(c, c + d);
+                else uf_unite<kGroup>(P, c, c + d);
+                ++at;
+            }
+        };
+        push(join, -1);
+        push(down, gw);
+        push(right, gw + 1);
+        push(left, gw - 1);
+    }
+    __syncthreads();
+    const int nq = min(s_nq, qcap);
+    for (int q = tid; q < nq; q += kFThreads) uf_unite<kGroup>(P, queue[q].x, queue[q].y);
+    // the last thread, which seldom has a join, finishes the sums
+    if (tid == kFThreads - 1) {
         double S = 0.0, E = 0.0, HS = 0.0;
         uint32_t M = 0;
         for (int w = 0; w < kFWaves; ++w) {
@@ -468,69 +601,101 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int32
         int lg = 0;
         while ((1LL << lg) < (long long)cells) ++lg;
         s_shift = 62 - (max(Ex, -126) + 1) - lg;
-        shift[f] = s_shift;
-        s_ncomp = 0;
-    }
-    // B (reads and writes only this wave's rows)
-    for (int row = wave; row < gh; row += kFWaves) {
-        int carry = -1;  // first cell of the run still open at the end of the last chunk
-        for (int x0 = 0; x0 < gw; x0 += 64) {
-            const int x = x0 + lane, c = row * gw + x;
-            const bool hot = x < gw && P[c] >= 0;
-            const uint64_t hm = __ballot(hot);
-            const uint64_t cold_below = ~hm & ((1ull << lane) - 1ull);
-            const int start = cold_below ? row * gw + x0 + (63 - __clzll(cold_below)) + 1
-                                         : (carry >= 0 ? carry : row * gw + x0);
-            if (hot) P[c] = start;
-            const int s63 = __shfl(start, 63, 64);
-            carry = ((hm >> 63) & 1ull) ? s63 : -1;
-        }
     }
     __syncthreads();
-    // C
-    auto hotc = [&](int c) { return ld_rlx<kGroup>(P + c) >= 0; };
-    for (int c = tid; c < cells - gw; c += kFThreads) {
-        if (!hotc(c)) continue;
-        const int gx = c % gw, d = c + gw;
-        const bool dh = hotc(d);
-        const bool lh = gx > 0 && hotc(c - 1), rh = gx + 1 < gw && hotc(c + 1);
-        if (dh && !(lh && hotc(d - 1))) uf_unite<kGroup>(P, c, d);
-        if (a.connectivity == 8 && !dh) {
-            if (gx + 1 < gw && !rh && hotc(d + 1)) uf_unite<kGroup>(P, c, d + 1);
-            if (gx > 0 && !lh && hotc(d - 1)) uf_unite<kGroup>(P, c, d - 1);
+    // C (the walks only meet entries that move to roots); a root's entry then
+    // becomes -2 - its slot
+    auto run_firsts = [&](auto body) {
+        for (int i = tid; i < l.words; i += kFThreads) {
+            const uint64_t m = hotw[i];
+            for (uint64_t b = m & ~((m << 1) & ~row0w[i]); b; b &= b - 1) body(64 * i + (int)__builtin_ctzll(b));
         }
-    }
+    };
+    run_firsts([&](int c) { st_rlx<kGroup>(P + c, uf_root<kGroup>(P, c)); });
     __syncthreads();
-    // D (loop bound rounded up to whole waves: the shuffles need every lane)
-    const int sh = s_shift;
-    const int cells_up = (cells + 63) & ~63;
-    for (int c = tid; c < cells_up; c += kFThreads) {
-        const bool in = c < cells;
-        const int32_t p0 = in ? P[c] : -1;
-        const int32_t r = p0 >= 0 ? uf_root<kGroup>(P, c) : -1;
-        unsigned long long q = 0ull;
-        if (r >= 0) {
-            L[c] = r;
-            q = (unsigned long long)llrint(ldexp((double)D[c], sh));
-            if (r == c) roots[(size_t)f * cells + atomicAdd(&s_ncomp, 1)] = c;  // for heat_root_mass_kernel
-        } else if (in) {
-            L[c] = -1;
-        }
-        const int32_t prev = __shfl_up(r, 1, 64);
-        const bool head = lane == 0 || prev != r;
-        const uint64_t heads = __ballot(head);
-        const uint64_t after = lane == 63 ? 0ull : heads >> (lane + 1);
-        const int next = after ? lane + 1 + __ffsll((long long)after) - 1 : 64;  // next run's first lane
-        const unsigned long long incl = wave_incl_scan_u64(q);
-        const unsigned long long at_end = __shfl(incl, next - 1, 64);
-        const unsigned long long before = __shfl(incl, lane > 0 ? lane - 1 : 0, 64);
-        if (head && r >= 0) {
-            atomicAdd(CC + r, next - lane);
-            atomicAdd(CMu + r, at_end - (lane > 0 ? before : 0ull));
-        }
-    }
+    run_firsts([&](int c) {
+        if (P[c] == c) P[c] = -2 - atomicAdd(&s_ncomp, 1);
+    });
     __syncthreads();
-    if (tid == 0) a.n_components[f] = s_ncomp;
+    // D, E
+    const int sh = s_shift, ncomp = s_ncomp;
+    for (int base = 0; base == 0 || base < ncomp; base += slots) {
+        const int here = min(slots, ncomp - base);
+        for (int t = tid; t < here; t += kFThreads) {
+            mass[t] = 0ull;
+            count[t] = 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) v[u] = load(min(wave + kFWaves * u, l.words));
+        __syncthreads();
+        for (int w0 = wave; w0 < l.words; w0 += kFWaves * kFlight) {
+            int32_t root[kFlight], p[kFlight];
+            uint64_t m[kFlight], r0[kFlight];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {  // words past the end are not beyond the zero words when clamped
+                const int w = min(w0 + kFWaves * u, l.words);
+                m[u] = hotw[w];
+                r0[u] = row0w[w];
+            }
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {
+                m[u] = uniform(m[u]);
+                root[u] = __builtin_amdgcn_inverse_ballot_w64(m[u]) ? 64 * (w0 + kFWaves * u) + lane : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) p[u] = P[max(root[u], 0)];
+            // the words' walks in step (p < 0: at the root, or a cold cell);
+            // after C two steps reach every root
+            for (;;) {
+                bool any = false;
+#pragma unroll
+                for (int u = 0; u < kFlight; ++u) {
+                    const bool on = (root[u] >= 0) & (p[u] >= 0);
+                    root[u] = on ? p[u] : root[u];
+                    any |= on;
+                }
+                if (!__any(any)) break;
+#pragma unroll
+                for (int u = 0; u < kFlight; ++u) p[u] = P[max(root[u], 0)];
+            }
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {
+                const int w = w0 + kFWaves * u, c = 64 * w + lane;
+                if (c < cells && base == 0) {
+                    L[c] = root[u];
+                    if (root[u] != c) {  // a label cell's outputs come from its slot
+                        CC[c] = 0;
+                        CM[c] = 0.0;
+                    }
+                }
+                const float d = v[u];
+                v[u] = load(min(w + kFWaves * kFlight, l.words));
+                if (m[u] == 0ull) continue;  // wave-uniform
+                const int slot = root[u] >= 0 ? -2 - p[u] - base : -1;
+                const unsigned long long q = root[u] >= 0 ? (unsigned long long)llrint(ldexp((double)d, sh)) : 0ull;
+                const unsigned long long incl = wave_incl_scan_u64(q);
+                // a run's first lane takes its sum: up to its last lane, less what lies before it
+                const uint64_t firsts = m[u] & ~((m[u] << 1) & ~uniform(r0[u]));
+                const uint64_t lasts = m[u] & (~(m[u] >> 1) | (firsts >> 1) | (1ull << 63));
+                const uint64_t after = lasts >> lane;
+                const int end = after ? lane + __builtin_ctzll(after) : lane;
+                const unsigned long long at_end = __shfl(incl, end, 64);
+                if (__builtin_amdgcn_inverse_ballot_w64(firsts) && slot >= 0 && slot < here) {
+                    atomicAdd(count + slot, end - lane + 1);
+                    atomicAdd(mass + slot, at_end - (incl - q));
+                    if (root[u] == c) label[slot] = c;
+                }
+            }
+        }
+        __syncthreads();
+        for (int t = tid; t < here; t += kFThreads) {
+            const int32_t c = label[t];
+            CC[c] = count[t];
+            CM[c] = ldexp((double)mass[t], -sh) * a.cell_area;
+        }
+        __syncthreads();  // the next slots' zeros
+    }
+    if (tid == 0) a.n_components[f] = ncomp;
 }
 
 }  // namespace
@@ -542,23 +707,29 @@ size_t heatmap_workspace_bytes(int32_t n_frames, int32_t grid_w, int32_t grid_h)
     return parts + (((size_t)n_frames * sizeof(int32_t) + 255) & ~(size_t)255);
 }
 
-size_t heatmap_frame_lds_bytes(int32_t grid_w, int32_t grid_h) { return (size_t)grid_w * grid_h * sizeof(int32_t); }
-
-// A shift per frame, then each frame's label cells (at most one per cell).
-size_t heatmap_frame_workspace_bytes(int32_t n_frames, int32_t grid_w, int32_t grid_h) {
-    if (n_frames <= 0 || grid_w < 1 || grid_h < 1) return 0;
-    return (((size_t)n_frames * sizeof(int32_t) + 255) & ~(size_t)255) +
-           (size_t)n_frames * grid_w * grid_h * sizeof(int32_t);
+// Component slots of the frame-resident kernel in `lds_limit` bytes of LDS (0:
+// the grid does not fit).
+int heatmap_frame_slots(int32_t grid_w, int32_t grid_h, size_t lds_limit) {
+    const size_t used = frame_lds(grid_w, grid_h).bytes(0) + kFrameStaticLds;
+    if (used + kMinSlots * 16 > lds_limit) return 0;
+    const size_t slots = (lds_limit - used) / 16;
+    return (int)(slots < (size_t)kMaxSlots ? slots : (size_t)kMaxSlots);
 }
 
-hipError_t launch_heatmap(HeatArgs a, void *workspace, bool resident, hipStream_t stream) {
-    if (resident) {
-        int32_t *shift = static_cast<int32_t *>(workspace);
-        int32_t *roots = reinterpret_cast<int32_t *>(static_cast<unsigned char *>(workspace) +
-                                                     (((size_t)a.n_frames * sizeof(int32_t) + 255) & ~(size_t)255));
-        hipLaunchKernelGGL(heat_frame_kernel, dim3((unsigned)a.n_frames), dim3(kFThreads),
-                           heatmap_frame_lds_bytes(a.grid_w, a.grid_h), stream, a, shift, roots);
-        hipLaunchKernelGGL(heat_root_mass_kernel, dim3((unsigned)a.n_frames), dim3(256), 0, stream, a, shift, roots);
+hipError_t launch_heatmap(HeatArgs a, void *workspace, int frame_slots, int n_cus, hipStream_t stream) {
+    if (frame_slots > 0) {
+        const size_t lds = frame_lds(a.grid_w, a.grid_h).bytes(frame_slots);
+        // more frames than compute units: 512-thread workgroups, where several
+        // share a compute unit, wait less at each barrier and keep it busy
+        // (1800 x 128 x 72: 115 us against 159 with 1024 threads, 512 x 64 x
+        // 36: 18.5 against 27.7); with at most one frame per compute unit, or
+        // half its LDS per frame, a frame takes 1024 (64 x 128 x 72: 23.8
+        // against 26.3; 256 x 256 x 144: 64 against 71)
+        if (a.n_frames > n_cus && 2 * (lds + kFrameStaticLds) <= 160 * 1024)
+            hipLaunchKernelGGL(heat_frame_kernel<512>, dim3((unsigned)a.n_frames), dim3(512), lds, stream, a, frame_slots);
+        else
+            hipLaunchKernelGGL(heat_frame_kernel<1024>, dim3((unsigned)a.n_frames), dim3(1024), lds, stream, a,
+                               frame_slots);
         return hipGetLastError();
     }
     a.tiles_x = (a.grid_w + kHT - 1) / kHT;

@@ -112,14 +112,12 @@ struct HeatArgs {
 };
 
 size_t heatmap_workspace_bytes(int32_t n_frames, int32_t grid_w, int32_t grid_h);
-// Dynamic LDS of the frame-resident kernel (one workgroup per frame), and
-// its workspace (the per-frame fixed-point scales).
-size_t heatmap_frame_lds_bytes(int32_t grid_w, int32_t grid_h);
-size_t heatmap_frame_workspace_bytes(int32_t n_frames, int32_t grid_w, int32_t grid_h);
-// resident: one workgroup per frame with the grid in LDS (needs
-// heatmap_frame_lds_bytes within the device's limit); else the tiled kernels,
-// which use the workspace.
-hipError_t launch_heatmap(HeatArgs a, void *workspace, bool resident, hipStream_t stream);
+// Component slots the frame-resident kernel (one workgroup per frame) gets in
+// lds_limit bytes of LDS; 0 when the grid does not fit.
+int heatmap_frame_slots(int32_t grid_w, int32_t grid_h, size_t lds_limit);
+// frame_slots > 0: the frame-resident kernel, which needs no workspace; else
+// the tiled kernels, which use it.
+hipError_t launch_heatmap(HeatArgs a, void *workspace, int frame_slots, int n_cus, hipStream_t stream);
 
 // ----------------------------------------------------------------------------
 // Region of interest

@@ -95,6 +95,22 @@ def test_workload_grid_shapes_gpu(name):
     check(g, area, float(np.quantile(pos, 0.8)), 8, tag=name)
 
 
+@pytest.mark.parametrize("conn", [4, 8])
+@pytest.mark.parametrize("F,h,w", [(2, 300, 17), (2, 40, 63), (2, 23, 64), (2, 31, 65), (1, 65, 1), (1, 1, 200),
+                                   (300, 9, 13), (1, 140, 270), (1, 138, 276)])
+def test_word_edges_gpu(F, h, w, conn):
+    """Rows that end inside, at and just past the 64-cell words, grids at both
+    sides of the frame kernel's LDS limit, and more frames than compute units;
+    checkerboards for more components than the kernel has slots."""
+    rng = np.random.default_rng(h * 1000 + w)
+    g = (rng.random((F, h, w)) * 1e-3).astype(np.float32)
+    for q in (0.35, 0.8):
+        check(g, 2.0, float(np.quantile(g, q)), conn, tag=f"{F}x{h}x{w} q{q}")
+    yy, xx = np.meshgrid(np.arange(h), np.arange(w), indexing="ij")
+    dots = np.where((yy % 2 == 0) & (xx % 2 == 0), 1.0 + (yy * w + xx) / (h * w), 0.1).astype(np.float32)
+    check(np.broadcast_to(dots, (F, h, w)).copy(), 1.5, 0.5, conn, tag=f"{F}x{h}x{w} dots")
+
+
 def test_deterministic_gpu(path):
     g = wl.heat_grids(7, 6, 90, 140)
     thr = float(np.quantile(g[g > 0], 0.6))
