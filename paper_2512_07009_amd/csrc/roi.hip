@@ -7,20 +7,19 @@
 // edges and vertices included, under the even-odd rule; kept birds keep
 // their input order.  Integer coordinates in 1/16 px, exact 64-bit products.
 //
-// Four kernels over fixed blocks of 2048 birds, whatever the frames
+// Three kernels over fixed blocks of 2048 birds, whatever the frames
 // (HBM-bound: 8 bytes read per bird, 12 written per kept bird):
-//   1. roi_flag_kernel: the inside test per bird (polygon in LDS), a flag
-//      byte per bird and a count per block;
-//   2. roi_scan_kernel, one workgroup: each block's first output position;
-//   3. roi_write_kernel: each block's kept birds, which the flag kernel
-//      staged in input order (ballots and wave totals give each its rank in
-//      the block), are copied to the block's base + rank, so kept birds keep
-//      their input order;
-//   4. frame_counts_kernel, one wave per frame boundary: the output position
-//      of the boundary bird (its block's base plus the flags before it in the
+//   1. roi_flag_kernel: the inside test per bird, a flag bit per bird and a
+//      count per block; the kept birds staged in input order;
+//   2. roi_write_kernel: each block's kept birds copied to the block's base +
+//      rank, so kept birds keep their input order; the base is the sum of the
+//      counts before the block, by the block itself (beyond kRSelfScan blocks
+//      by roi_scan_kernel, one workgroup, first);
+//   3. roi_counts_kernel, one wave per frame boundary: the output position of
+//      the boundary bird (its block's base plus the flags before it in the
 //      block) gives out_offsets, and neighbouring boundaries give counts.
-// Drinker-line proximity reuses steps 2 and 4 on its own flags (see
-// drink_flag_kernel).
+// Drinker-line proximity: drink_flag_kernel, then drink_counts_kernel, which
+// adds each frame's blocks.
 
 #include <climits>
 
@@ -80,86 +79,122 @@ __device__ __forceinline__ void load_polygon(const RoiArgs &a, int2 *poly) {
 constexpr int kRBlock = kRoiBlock;             // birds per block
 constexpr int kRPer = kRBlock / kRThreadsR;    // birds per thread, consecutive chunks of 256
 
-// Flags of one block of birds.  The bounding-box test runs on every bird;
-// the birds inside the box (a small share for a region along a wall) are
-// queued in LDS and the edge tests run on the queue, so that whole waves
-// test in-box birds instead of every wave running the edge loop for the
-// few in-box lanes it holds.  The kept birds then go, in input order, to the
-// block's staging area (coordinates and input index), for the write kernel
-// to copy to their final places without reading every bird again.
-__global__ __launch_bounds__(kRThreadsR) void roi_flag_kernel(RoiArgs a, uint8_t *flag, int32_t *bcount,
+constexpr int kRWaveBirds = kRBlock / kRWaves;  // a wave's share of a block: kRPer chunks of 64
+constexpr int kRQueue = 128;                   // queued candidates per wave (part of a batch + one chunk)
+
+// A wave's queue of candidate birds: the cheap test runs on every bird, the
+// exact one on batches of 64 candidates, so that whole waves run it instead of
+// every wave running it for the few candidates it holds.  Private to the wave
+// (its LDS operations stay in order; the fences keep the compiler's too), so
+// no barrier is met between a block's loads and its results.
+struct WaveQueue {
+    int2 pt[kRQueue];
+    uint16_t at[kRQueue];  // the bird's index in the wave's share
+};
+
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Queue the lanes with `cand` set (chunk k of the share), and run `exact(pt,
+// at)` on 64 queued birds whenever that many wait; `flush` runs it on the rest.
+template <class Exact>
+struct QueuedTest {
+    WaveQueue &q;
+    int head, tail;  // positions, taken modulo kRQueue
+    Exact exact;
+    __device__ __forceinline__ void push(bool cand, int2 pt, int at, int lane) {
+        const uint64_t m = __ballot(cand);
+        if (m == 0ull) return;  // wave-uniform
+        if (cand) {
+            const int i = (tail + __popcll(m & ((1ull << lane) - 1ull))) & (kRQueue - 1);
+            q.pt[i] = pt;
+            q.at[i] = (uint16_t)at;
+        }
+        tail += __popcll(m);
+        if (tail - head >= 64) run(64, lane);
+    }
+    __device__ __forceinline__ void run(int n, int lane) {
+        wave_fence();
+        if (lane < n) {
+            const int i = (head + lane) & (kRQueue - 1);
+            exact(q.pt[i], (int)q.at[i]);
+        }
+        head += n;
+        wave_fence();
+    }
+    __device__ __forceinline__ void flush(int lane) {
+        if (tail > head) run(tail - head, lane);
+    }
+};
+template <class Exact>
+__device__ QueuedTest(WaveQueue &, int, int, Exact) -> QueuedTest<Exact>;
+
+// Flags of one block of birds, a bit per bird (64 birds per word), a wave per
+// kRWaveBirds of them.  Few birds lie inside the bounding box of a region along
+// a wall; those are queued and tested.  The kept birds then go, in input order,
+// to the block's staging area (coordinates and input index), for the write
+// kernel to copy to their final places without reading every bird again.
+// Bound by HBM: 1800 x 5000 birds, 14% kept, move 72 + 1 + 16 MB in 25.9
+// us; one queue per block between four barriers, with a byte per flag, took
+// 30.2.
+__global__ __launch_bounds__(kRThreadsR) void roi_flag_kernel(RoiArgs a, uint64_t *flag, int32_t *bcount,
                                                              int2 *stage_xy, int32_t *stage_idx) {
     __shared__ int2 poly[kRoiMaxVertices];
-    __shared__ int2 s_pt[kRBlock];        // in-box birds: coordinates
-    __shared__ uint16_t s_at[kRBlock];    // and their index in the block
-    __shared__ uint8_t s_f[kRBlock];      // every bird's flag
-    __shared__ int s_tot[kRPer][kRWaves];
-    __shared__ int s_nq;
-    if (threadIdx.x == 0) s_nq = 0;
-    load_polygon(a, poly);  // holds a barrier
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long i0 = (long long)blockIdx.x * kRBlock;
+    __shared__ WaveQueue s_q[kRWaves];
+    __shared__ uint64_t s_bits[kRWaves][kRPer];
+    __shared__ int s_tot[kRWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const long long i0 = (long long)blockIdx.x * kRBlock + wave * kRWaveBirds;  // the wave's first bird
     const int2 *P = reinterpret_cast<const int2 *>(a.xy);
     // all loads first, so that their latencies overlap
     int2 pts[kRPer];
 #pragma unroll
     for (int k = 0; k < kRPer; ++k) {
-        const long long i = i0 + k * kRThreadsR + tid;
-        pts[k] = i < a.total ? P[i] : make_int2(INT_MIN, INT_MIN);
+        const long long i = i0 + 64 * k + lane;
+        pts[k] = i < a.total ? P[i] : make_int2(INT_MIN, INT_MIN);  // a padding point is outside every box
     }
-    // box test; birds outside are out, the others queued
+    if (lane < kRPer) s_bits[wave][lane] = 0ull;
+    load_polygon(a, poly);  // holds a barrier
+    auto exact = [&](int2 pt, int at) {
+        if (in_polygon_boxed(a, poly, pt.x, pt.y))
+            atomicOr(reinterpret_cast<uint32_t *>(s_bits[wave]) + (at >> 5), 1u << (at & 31));
+    };
+    QueuedTest test{s_q[wave], 0, 0, exact};
 #pragma unroll
-    for (int k = 0; k < kRPer; ++k) {
-        const bool box = in_box(a, pts[k].x, pts[k].y);  // a padding lane's point is outside every box
-        const uint64_t m = __ballot(box);
-        int base = 0;
-        if (lane == 0 && m) base = atomicAdd(&s_nq, __popcll(m));
-        base = __shfl(base, 0, 64);
-        if (box) {
-            const int q = base + __popcll(m & ((1ull << lane) - 1));
-            s_pt[q] = pts[k];
-            s_at[q] = (uint16_t)(k * kRThreadsR + tid);
-        } else {
-            s_f[k * kRThreadsR + tid] = 0;
-        }
-    }
-    __syncthreads();
-    const int nq = s_nq;
-    for (int q = tid; q < nq; q += kRThreadsR) {
-        const int2 pt = s_pt[q];
-        s_f[s_at[q]] = in_polygon_boxed(a, poly, pt.x, pt.y);
-    }
-    __syncthreads();
+    for (int k = 0; k < kRPer; ++k) test.push(in_box(a, pts[k].x, pts[k].y), pts[k], 64 * k + lane, lane);
+    test.flush(lane);
+    wave_fence();
     // flags out, and the kept birds' ranks in the block (input order)
-    bool in[kRPer];
     uint64_t m[kRPer];
+    int n = 0;
 #pragma unroll
     for (int k = 0; k < kRPer; ++k) {
-        const long long i = i0 + k * kRThreadsR + tid;
-        in[k] = s_f[k * kRThreadsR + tid] != 0;
-        if (i < a.total) flag[i] = in[k];
-        m[k] = __ballot(in[k]);
-        if (lane == 0) s_tot[k][wave] = __popcll(m[k]);
+        m[k] = s_bits[wave][k];
+        n += __popcll(m[k]);
     }
+    if (lane < kRPer && i0 + 64 * lane < a.total) flag[i0 / 64 + lane] = s_bits[wave][lane];
+    if (lane == 0) s_tot[wave] = n;
     __syncthreads();
-    int at = 0;
-    const long long sbase = (long long)blockIdx.x * kRBlock;
+    long long r = (long long)blockIdx.x * kRBlock;
+    int all = 0;
+#pragma unroll
+    for (int w = 0; w < kRWaves; ++w) {
+        r += w < wave ? s_tot[w] : 0;
+        all += s_tot[w];
+    }
 #pragma unroll
     for (int k = 0; k < kRPer; ++k) {
-        int before = 0, chunk = 0;
-#pragma unroll
-        for (int w = 0; w < kRWaves; ++w) {
-            before += w < wave ? s_tot[k][w] : 0;
-            chunk += s_tot[k][w];
+        if ((m[k] >> lane) & 1ull) {
+            const long long at = r + __popcll(m[k] & ((1ull << lane) - 1ull));
+            stage_xy[at] = pts[k];
+            stage_idx[at] = (int32_t)(i0 + 64 * k + lane);
         }
-        if (in[k]) {
-            const long long r = sbase + at + before + __popcll(m[k] & ((1ull << lane) - 1ull));
-            stage_xy[r] = pts[k];
-            stage_idx[r] = (int32_t)(i0 + k * kRThreadsR + tid);
-        }
-        at += chunk;
+        r += __popcll(m[k]);
     }
-    if (tid == 0) bcount[blockIdx.x] = at;
+    if (tid == 0) bcount[blockIdx.x] = all;
 }
 
 // bbase[b] = bcount[0] + ... + bcount[b - 1]; bbase[nb] = all kept birds.
@@ -188,49 +223,79 @@ __global__ __launch_bounds__(1024) void roi_scan_kernel(const int32_t *bcount, i
 }
 
 // Each block's kept birds, staged in input order by the flag kernel, go to
-// base + rank.
-__global__ __launch_bounds__(kRThreadsR) void roi_write_kernel(RoiArgs a, const int32_t *bbase,
+// base + rank.  Up to kRSelfScan blocks a block adds up the counts before it
+// itself (at most 32 reads a thread, from L2) and leaves its base for the
+// counts kernel; beyond that the scan kernel has made the bases.
+constexpr int kRSelfScan = 8192;
+
+__global__ __launch_bounds__(kRThreadsR) void roi_write_kernel(RoiArgs a, const int32_t *bcount, int32_t *bbase, int nb,
                                                               const int2 *stage_xy, const int32_t *stage_idx) {
-    const int32_t base = bbase[blockIdx.x], n = bbase[blockIdx.x + 1] - base;
-    const long long sbase = (long long)blockIdx.x * kRBlock;
+    __shared__ int s_sum[kRWaves];
+    const int tid = threadIdx.x, b = blockIdx.x;
+    int32_t base;
+    if (nb <= kRSelfScan) {
+        int sum = 0;
+        for (int i0 = tid; i0 < b; i0 += kRThreadsR * 8) {
+            int c[8];  // in flight together
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c[u] = i0 + u * kRThreadsR < b ? bcount[i0 + u * kRThreadsR] : 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += c[u];
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if ((tid & 63) == 0) s_sum[tid >> 6] = sum;
+        __syncthreads();
+        base = 0;
+#pragma unroll
+        for (int w = 0; w < kRWaves; ++w) base += s_sum[w];
+        if (tid == 0) {
+            bbase[b] = base;
+            if (b == nb - 1) bbase[nb] = base + bcount[b];
+        }
+    } else {
+        base = bbase[b];
+    }
+    const int n = bcount[b];
+    const long long sbase = (long long)b * kRBlock;
     int2 *O = reinterpret_cast<int2 *>(a.out_xy);
-    for (int t = threadIdx.x; t < n; t += kRThreadsR) {
+    for (int t = tid; t < n; t += kRThreadsR) {
         O[base + t] = stage_xy[sbase + t];
         if (a.out_index) a.out_index[base + t] = stage_idx[sbase + t];
     }
 }
 
-// Per-frame counts of flagged birds, for the ROI filter (which also needs
-// the CSR offsets of its output) and the drinker flags.
-struct FrameCounts {
-    const uint8_t *flag;      // [total] 0 or 1, padded to 256 bytes
-    const int32_t *bbase;     // [nb + 1] flagged birds before each 2048-bird block
-    const int32_t *offsets;   // [n_frames + 1]
-    int32_t n_frames, total;
-    int32_t *counts;          // [n_frames]
-    int32_t *out_offsets;     // [n_frames + 1] or nullptr
-};
+// Flagged birds before input bird i (0 <= i <= total) in i's block, from the
+// ROI's bits or the drinkers' bytes (wave-uniform calls).
+__device__ __forceinline__ int32_t wave_total(int c) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+    return c;
+}
 
-// Flagged birds before input bird i0 (0 <= i0 <= total): its block's base
-// plus the flags before it in the block (wave-uniform call).
-__device__ __forceinline__ int32_t flagged_before(const FrameCounts &fc, int32_t i0) {
-    const int lane = threadIdx.x & 63;
-    const int32_t b = i0 / kRBlock;
-    const int32_t s0 = b * kRBlock;
+__device__ __forceinline__ int32_t bits_before(const uint64_t *flag, int32_t i) {
+    const int lane = threadIdx.x & 63, n = i % kRBlock - 64 * lane;  // bits of this lane's word
+    const uint64_t w = n > 0 ? flag[i / kRBlock * (kRBlock / 64) + lane] : 0ull;  // n > 0: lane < 32
+    return wave_total(__popcll(n >= 64 ? w : w & ((1ull << (n & 63)) - 1ull)));
+}
+
+__device__ __forceinline__ int32_t bytes_before(const uint8_t *flag, int32_t total, int32_t i) {
     // 16 flags per lane and load (a block is 2048 = 2 x 64 x 16 flags; the
-    // flag array is 16-byte aligned), bytes at or past i0 masked; the last
+    // flag array is 16-byte aligned), bytes at or past i masked; the last
     // partial word of the array is read byte by byte, never past total
+    const int lane = threadIdx.x & 63;
+    const int32_t s0 = i / kRBlock * kRBlock;
     int c = 0;
 #pragma unroll
     for (int j = 0; j < kRBlock / (64 * 16); ++j) {
         const int32_t base = s0 + 16 * (lane + 64 * j);
-        if (base >= i0) continue;
-        if (base + 16 > fc.total) {
-            for (int32_t i = base; i < i0; ++i) c += fc.flag[i];
+        if (base >= i) continue;
+        if (base + 16 > total) {
+            for (int32_t k = base; k < i; ++k) c += flag[k];
             continue;
         }
-        const uint4 w = *reinterpret_cast<const uint4 *>(fc.flag + base);
-        const int valid = min(16, i0 - base);
+        const uint4 w = *reinterpret_cast<const uint4 *>(flag + base);
+        const int valid = min(16, i - base);
         const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -239,24 +304,57 @@ __device__ __forceinline__ int32_t flagged_before(const FrameCounts &fc, int32_t
             c += (int)(((ws[q] & keep) * 0x01010101u) >> 24);  // bytes are 0 or 1
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-    return fc.bbase[b] + c;  // bbase has nb + 1 entries, and i0 = total gives b <= nb
+    return wave_total(c);
 }
 
-// One wave per frame boundary f = 0 .. n_frames.
-__global__ __launch_bounds__(256) void frame_counts_kernel(FrameCounts fc) {
+// Frame boundary g clamped into [0, total] (offsets are only validated with
+// FLOCK_VALIDATE; this keeps every read in bounds).
+__device__ __forceinline__ int32_t frame_bound(const int32_t *offsets, int32_t n_frames, int32_t total, int g) {
+    return g == n_frames ? total : min(max(offsets[g], 0), total);
+}
+
+// One wave per frame boundary f = 0 .. n_frames: the CSR offsets of the ROI's
+// output and its per-frame counts (bbase has nb + 1 entries, and i = total
+// gives block nb at most).
+__global__ __launch_bounds__(256) void roi_counts_kernel(RoiArgs a, const uint64_t *flag, const int32_t *bbase) {
     const int f = (int)(((long long)blockIdx.x * 256 + threadIdx.x) >> 6);
-    if (f > fc.n_frames) return;  // wave-uniform
-    // frame boundaries clamped into [0, total] (offsets are only validated
-    // with FLOCK_VALIDATE; this keeps every read in bounds)
-    auto bound = [&](int g) { return g == fc.n_frames ? fc.total : min(max(fc.offsets[g], 0), fc.total); };
-    const int32_t v = flagged_before(fc, bound(f));
-    if (fc.out_offsets && (threadIdx.x & 63) == 0) fc.out_offsets[f] = v;
-    if (f < fc.n_frames) {
-        const int32_t v1 = flagged_before(fc, bound(f + 1));
-        if ((threadIdx.x & 63) == 0) fc.counts[f] = max(v1 - v, 0);
+    if (f > a.n_frames) return;  // wave-uniform
+    auto before = [&](int g) {
+        const int32_t i = frame_bound(a.offsets, a.n_frames, a.total, g);
+        return bbase[i / kRBlock] + bits_before(flag, i);
+    };
+    const int32_t v = before(f);
+    if ((threadIdx.x & 63) == 0) a.out_offsets[f] = v;
+    if (f < a.n_frames) {
+        const int32_t v1 = before(f + 1);
+        if ((threadIdx.x & 63) == 0) a.counts[f] = max(v1 - v, 0);
     }
+}
+
+// One wave per frame: the drinkers' count from the blocks the frame covers
+// (whole blocks by their counts, the first and last by their flags), so that no
+// scan over all blocks is needed.
+__global__ __launch_bounds__(256) void drink_counts_kernel(DrinkArgs a, const int32_t *bcount) {
+    const int f = (int)(((long long)blockIdx.x * 256 + threadIdx.x) >> 6);
+    if (f >= a.n_frames) return;  // wave-uniform
+    const int lane = threadIdx.x & 63;
+    const int32_t i0 = frame_bound(a.offsets, a.n_frames, a.total, f);
+    const int32_t i1 = frame_bound(a.offsets, a.n_frames, a.total, f + 1);
+    if (i1 <= i0) {
+        if (lane == 0) a.counts[f] = 0;
+        return;
+    }
+    const int32_t b0 = i0 / kRBlock, b1 = i1 / kRBlock;  // blocks b0 .. b1 - 1 end inside the frame
+    int c = 0;
+    for (int32_t b = b0 + lane; b < b1; b += 64 * 4) {
+        int v[4];  // in flight together
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = b + 64 * u < b1 ? bcount[b + 64 * u] : 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c += v[u];
+    }
+    const int32_t n = wave_total(c) - bytes_before(a.drinking, a.total, i0) + bytes_before(a.drinking, a.total, i1);
+    if (lane == 0) a.counts[f] = n;
 }
 
 // ---------------------------------------------------------------------------
@@ -287,76 +385,78 @@ __device__ __forceinline__ bool near_segment(int4 s, int px, int py, long long t
     return ch < lh || (ch == lh && cl < ll);
 }
 
-// Flags of one block of birds.  A bird within T of a segment lies in the
-// segment's bounding box widened by T on every side, so birds outside all
-// widened boxes (most of them, for lines across the frame) are not drinking;
-// the others are queued in LDS and tested exactly on the queue, so that whole
-// waves run the exact tests.
+// Flags of one block of birds, a wave per kRWaveBirds of them.  A bird within T
+// of a segment lies in the segment's bounding box widened by T on every side,
+// so birds outside all widened boxes (most of them, for lines across the frame)
+// are not drinking; the others are queued and tested exactly.  The wave's
+// results wait in LDS as one byte per bird and leave in full lines.
+// Bound by HBM: 1800 x 5000 birds move 72 + 45 MB in 29.6 us (33.0 with
+// one queue per block and stores by the birds' own lanes).
 __global__ __launch_bounds__(kRThreadsR) void drink_flag_kernel(DrinkArgs a, int32_t *bcount) {
     __shared__ int4 seg[kDrinkMaxLines];
     __shared__ int4 box[kDrinkMaxLines];  // x0, y0, x1, y1 widened by T
-    __shared__ int2 s_pt[kRBlock];
-    __shared__ uint16_t s_at[kRBlock];
-    __shared__ int s_nq, s_in;
-    const int tid = threadIdx.x, lane = tid & 63;
-    if (tid == 0) s_nq = s_in = 0;
+    __shared__ WaveQueue s_q[kRWaves];
+    __shared__ uint64_t s_hit[kRWaves][kRWaveBirds / 8];  // a byte per bird: its segment, 0xff for none
+    __shared__ int s_in;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const long long i0 = (long long)blockIdx.x * kRBlock + wave * kRWaveBirds;  // the wave's first bird
+    const int2 *P = reinterpret_cast<const int2 *>(a.xy);
+    int2 pts[kRPer];
+#pragma unroll
+    for (int k = 0; k < kRPer; ++k) {
+        const long long i = i0 + 64 * k + lane;
+        pts[k] = i < a.total ? P[i] : make_int2(0, 0);
+    }
+    if (tid == 0) s_in = 0;
     if (tid < a.n_lines) {
         seg[tid] = make_int4(a.ax[tid], a.ay[tid], a.bx[tid], a.by[tid]);
         const int t = a.threshold;  // |coordinates|, T <= 2^24: no overflow
         box[tid] = make_int4(min(a.ax[tid], a.bx[tid]) - t, min(a.ay[tid], a.by[tid]) - t,
                              max(a.ax[tid], a.bx[tid]) + t, max(a.ay[tid], a.by[tid]) + t);
     }
+    static_assert(kRWaveBirds == 64 * 8, "eight result bytes per lane");
+    s_hit[wave][lane] = ~0ull;
     __syncthreads();
-    const long long i0 = (long long)blockIdx.x * kRBlock;
-    const int2 *P = reinterpret_cast<const int2 *>(a.xy);
     const long long t2 = (long long)a.threshold * a.threshold;
-    int2 pts[kRPer];
-#pragma unroll
-    for (int k = 0; k < kRPer; ++k) {
-        const long long i = i0 + k * kRThreadsR + tid;
-        pts[k] = i < a.total ? P[i] : make_int2(0, 0);
-    }
     bool cands[kRPer];
 #pragma unroll
     for (int k = 0; k < kRPer; ++k) cands[k] = false;
-    for (int l = 0; l < a.n_lines; ++l) {  // each box read once, for all of the thread's birds
+    for (int l = 0; l < a.n_lines; ++l) {  // each box read once, for all of the lane's birds
         const int4 b = box[l];
 #pragma unroll
         for (int k = 0; k < kRPer; ++k)
             cands[k] |= (pts[k].x > b.x) & (pts[k].x < b.z) & (pts[k].y > b.y) & (pts[k].y < b.w);
     }
+    uint8_t *hit = reinterpret_cast<uint8_t *>(s_hit[wave]);
+    auto exact = [&](int2 pt, int at) {
+        for (int l = 0; l < a.n_lines; ++l)
+            if (near_segment(seg[l], pt.x, pt.y, t2)) {
+                hit[at] = (uint8_t)l;
+                break;
+            }
+    };
+    QueuedTest test{s_q[wave], 0, 0, exact};
 #pragma unroll
-    for (int k = 0; k < kRPer; ++k) {
-        const long long i = i0 + k * kRThreadsR + tid;
-        const bool cand = cands[k] & (i < a.total);
-        const uint64_t m = __ballot(cand);
-        int base = 0;
-        if (lane == 0 && m) base = atomicAdd(&s_nq, __popcll(m));
-        base = __shfl(base, 0, 64);
-        if (cand) {
-            const int q = base + __popcll(m & ((1ull << lane) - 1));
-            s_pt[q] = pts[k];
-            s_at[q] = (uint16_t)(k * kRThreadsR + tid);
-        } else if (i < a.total) {
-            a.drinking[i] = 0;
-            if (a.line) a.line[i] = -1;
+    for (int k = 0; k < kRPer; ++k)
+        test.push(cands[k] & (i0 + 64 * k + lane < a.total), pts[k], 64 * k + lane, lane);
+    test.flush(lane);
+    wave_fence();
+    // eight birds' flags per lane: segments are below 64, so bit 7 tells none
+    const uint64_t flags = (~s_hit[wave][lane] >> 7) & 0x0101010101010101ull;
+    const long long at = i0 + 8 * lane;
+    if (at + 8 <= a.total) {
+        *reinterpret_cast<uint64_t *>(a.drinking + at) = flags;
+    } else {
+        for (int k = 0; k < 8 && at + k < a.total; ++k) a.drinking[at + k] = (uint8_t)(flags >> (8 * k));
+    }
+    if (a.line) {
+#pragma unroll
+        for (int k = 0; k < kRPer; ++k) {
+            const long long i = i0 + 64 * k + lane;
+            if (i < a.total) a.line[i] = (int32_t)(int8_t)hit[64 * k + lane];
         }
     }
-    __syncthreads();
-    const int nq = s_nq;
-    int cnt = 0;
-    for (int q = tid; q < nq; q += kRThreadsR) {
-        const int2 pt = s_pt[q];
-        int32_t hit = -1;
-        for (int l = 0; l < a.n_lines && hit < 0; ++l)
-            if (near_segment(seg[l], pt.x, pt.y, t2)) hit = l;
-        const long long i = i0 + s_at[q];
-        a.drinking[i] = hit >= 0;
-        if (a.line) a.line[i] = hit;
-        cnt += hit >= 0;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+    const int cnt = wave_total(__popcll(flags));
     if (lane == 0 && cnt) atomicAdd(&s_in, cnt);
     __syncthreads();
     if (tid == 0) bcount[blockIdx.x] = s_in;
@@ -364,50 +464,59 @@ __global__ __launch_bounds__(kRThreadsR) void drink_flag_kernel(DrinkArgs a, int
 
 }  // namespace
 
-// Workspace: a flag per bird; a count and a base per block; per block a
+// Workspace: a flag bit per bird; a count and a base per block; per block a
 // staging area of kRBlock coordinates and kRBlock input indices.
-size_t roi_workspace_bytes(int32_t total) {
-    if (total <= 0) return 256;
-    const size_t nb = ((size_t)total + kRBlock - 1) / kRBlock;
-    return (((size_t)total + 255) & ~(size_t)255) + (((2 * nb + 1) * sizeof(int32_t) + 255) & ~(size_t)255) +
-           nb * kRBlock * (sizeof(int2) + sizeof(int32_t));
+struct RoiLayout {
+    size_t flags, counts, xy, idx, bytes;  // offsets, and the size
+};
+
+RoiLayout roi_layout(int32_t total) {
+    auto up = [](size_t n) { return (n + 255) & ~(size_t)255; };
+    const size_t nb = total > 0 ? ((size_t)total + kRBlock - 1) / kRBlock : 0;
+    RoiLayout l;
+    l.flags = 0;
+    l.counts = up(nb * (kRBlock / 64) * sizeof(uint64_t));
+    l.xy = l.counts + up((2 * nb + 1) * sizeof(int32_t));
+    l.idx = l.xy + nb * kRBlock * sizeof(int2);
+    l.bytes = l.idx + nb * kRBlock * sizeof(int32_t);
+    return l;
 }
+
+size_t roi_workspace_bytes(int32_t total) { return roi_layout(total).bytes; }
 
 hipError_t launch_roi(const RoiArgs &a, void *workspace, hipStream_t stream) {
     const int nb = (int)(((long long)a.total + kRBlock - 1) / kRBlock);
-    uint8_t *flag = static_cast<uint8_t *>(workspace);
-    int32_t *bcount = reinterpret_cast<int32_t *>(flag + (a.total > 0 ? (((size_t)a.total + 255) & ~(size_t)255) : 0));
-    int32_t *bbase = bcount + nb;
-    char *stage = reinterpret_cast<char *>(bcount) + (((2 * (size_t)nb + 1) * sizeof(int32_t) + 255) & ~(size_t)255);
-    int2 *stage_xy = reinterpret_cast<int2 *>(stage);
-    int32_t *stage_idx = reinterpret_cast<int32_t *>(stage + (size_t)nb * kRBlock * sizeof(int2));
+    const RoiLayout l = roi_layout(a.total);
+    char *base = static_cast<char *>(workspace);
+    uint64_t *flag = reinterpret_cast<uint64_t *>(base + l.flags);
+    int32_t *bcount = reinterpret_cast<int32_t *>(base + l.counts), *bbase = bcount + nb;
+    int2 *stage_xy = reinterpret_cast<int2 *>(base + l.xy);
+    int32_t *stage_idx = reinterpret_cast<int32_t *>(base + l.idx);
     if (nb > 0)
         hipLaunchKernelGGL(roi_flag_kernel, dim3((unsigned)nb), dim3(kRThreadsR), 0, stream, a, flag, bcount, stage_xy,
                            stage_idx);
-    hipLaunchKernelGGL(roi_scan_kernel, dim3(1), dim3(1024), 0, stream, bcount, bbase, nb);
+    if (nb == 0 || nb > kRSelfScan)
+        hipLaunchKernelGGL(roi_scan_kernel, dim3(1), dim3(1024), 0, stream, bcount, bbase, nb);
     if (nb > 0)
-        hipLaunchKernelGGL(roi_write_kernel, dim3((unsigned)nb), dim3(kRThreadsR), 0, stream, a, bbase, stage_xy,
-                           stage_idx);
-    const FrameCounts fc{flag, bbase, a.offsets, a.n_frames, a.total, a.counts, a.out_offsets};
+        hipLaunchKernelGGL(roi_write_kernel, dim3((unsigned)nb), dim3(kRThreadsR), 0, stream, a, bcount, bbase, nb,
+                           stage_xy, stage_idx);
     const long long waves = (long long)a.n_frames + 1;
-    hipLaunchKernelGGL(frame_counts_kernel, dim3((unsigned)((waves * 64 + 255) / 256)), dim3(256), 0, stream, fc);
+    hipLaunchKernelGGL(roi_counts_kernel, dim3((unsigned)((waves * 64 + 255) / 256)), dim3(256), 0, stream, a, flag,
+                       bbase);
     return hipGetLastError();
 }
 
 size_t drink_workspace_bytes(int32_t total) {
-    const size_t nb = total > 0 ? ((size_t)total + kRBlock - 1) / kRBlock : 0;
-    return (((2 * nb + 1) * sizeof(int32_t) + 255) & ~(size_t)255);
+    const size_t nb = total > 0 ? ((size_t)total + kRBlock - 1) / kRBlock : 1;
+    return ((nb * sizeof(int32_t) + 255) & ~(size_t)255);
 }
 
 hipError_t launch_drinkers(const DrinkArgs &a, void *workspace, hipStream_t stream) {
     const int nb = (int)(((long long)a.total + kRBlock - 1) / kRBlock);
     int32_t *bcount = static_cast<int32_t *>(workspace);
-    int32_t *bbase = bcount + nb;
     if (nb > 0) hipLaunchKernelGGL(drink_flag_kernel, dim3((unsigned)nb), dim3(kRThreadsR), 0, stream, a, bcount);
-    hipLaunchKernelGGL(roi_scan_kernel, dim3(1), dim3(1024), 0, stream, bcount, bbase, nb);
-    const FrameCounts fc{a.drinking, bbase, a.offsets, a.n_frames, a.total, a.counts, nullptr};
-    const long long waves = (long long)a.n_frames + 1;
-    hipLaunchKernelGGL(frame_counts_kernel, dim3((unsigned)((waves * 64 + 255) / 256)), dim3(256), 0, stream, fc);
+    hipLaunchKernelGGL(drink_counts_kernel, dim3((unsigned)(((long long)a.n_frames * 64 + 255) / 256)), dim3(256), 0,
+                       stream, a, bcount);
     return hipGetLastError();
 }
 

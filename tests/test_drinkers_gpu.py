@@ -55,6 +55,18 @@ def test_random_batches_gpu(n_lines, t):
     check(xy, off, lines, t, tag="no line output", with_line=False)
 
 
+def test_block_edges_gpu():
+    """Frame boundaries on and beside the edges of wave shares and blocks, a
+    frame over many blocks, and batches that end there."""
+    rng = np.random.default_rng(21)
+    lines = drinker_lines(rng, 64)
+    counts = [64, 0, 448, 1, 511, 1024, 2048, 2047, 0, 4097, 63, 600000, 2048, 9]
+    for cut in range(1, len(counts) + 1):
+        xy, off = wl.pack([np.stack([rng.integers(0, W, n), rng.integers(0, H, n)], 1).astype(np.int32)
+                           for n in counts[:cut]])
+        check(xy, off, lines, 200, tag=f"first {cut} frames")
+
+
 def test_exact_boundaries_gpu():
     """Birds on a lattice around lattice-aligned and 3-4-5 segments: many at
     exactly the threshold distance, beyond the ends and on the segments."""

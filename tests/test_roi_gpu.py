@@ -87,6 +87,28 @@ def test_all_in_all_out_and_empty_gpu():
     check(e_xy, e_off, everything, tag="empty frames")
 
 
+EDGE_COUNTS = [64, 0, 448, 1, 511, 1024, 2048, 2047, 0, 4097, 63, 6000, 2048]
+
+
+def test_block_edges_gpu():
+    """Frame boundaries on and beside the edges of words, wave shares and
+    blocks, and batches that end there."""
+    rng = np.random.default_rng(12)
+    for cut in range(1, len(EDGE_COUNTS) + 1):
+        xy, off = wl.pack([np.stack([rng.integers(0, W, n), rng.integers(0, H, n)], 1).astype(np.int32)
+                           for n in EDGE_COUNTS[:cut]])
+        check(xy, off, polygons()["star"], tag=f"first {cut} frames")
+
+
+def test_many_blocks_gpu():
+    """More blocks than the write kernel adds up by itself (8192)."""
+    rng = np.random.default_rng(13)
+    n = 8192 * 2048 + 77
+    xy = rng.integers(0, H, (n, 2), dtype=np.int32)
+    off = np.array([0, 5, n // 3, n // 3, n], np.int32)
+    check(xy, off, polygons()["wall"], tag="8193 blocks")
+
+
 @pytest.mark.parametrize("name", ["batch64x2000_1080p", "batch256xpoisson8000_4k", "house30000_4k",
                                   "stream1800x5000_1080p"])
 def test_workloads_gpu(name):
