@@ -87,13 +87,15 @@ def _check(status: int):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr() if t is not None else None)
+    return t.data_ptr() if t is not None else None
 
 
-def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+# The current device and a device's current stream, without the objects that
+# torch.cuda.current_device() and current_stream() make (about 1 us each; a
+# call with one small kernel takes about 10 us in all).
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+    (lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 def _workspace(nbytes: int, dev, stream):
@@ -104,8 +106,20 @@ def _workspace(nbytes: int, dev, stream):
     capture, where the block comes from the graph's own pool)."""
     if not nbytes:
         return None
-    with torch.cuda.device(dev), torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(dev)):
+    if stream is None or stream.cuda_stream == _raw_stream(dev.index):
+        return torch.empty(nbytes, dtype=torch.uint8, device=dev)  # on dev's current stream
+    with torch.cuda.device(dev), torch.cuda.stream(stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=dev)
+
+
+def _call(fn, dev, stream, *args):
+    """fn(*args, stream) with dev as the current device."""
+    if _current_device() == dev.index:
+        st = fn(*args, _raw_stream(dev.index) if stream is None else stream.cuda_stream)
+    else:
+        with torch.cuda.device(dev):
+            st = fn(*args, _raw_stream(dev.index) if stream is None else stream.cuda_stream)
+    _check(st)
 
 
 def _batch(xy: torch.Tensor, offsets: torch.Tensor):
@@ -143,13 +157,11 @@ def cluster_frames(xy: torch.Tensor, offsets: torch.Tensor, eps_px: float, min_p
         ncl = torch.empty(max(F, 0), dtype=torch.int32, device=dev)
     else:
         labels, kind, ncl = out
-    ws_bytes = lib().cluster_frames_workspace(F, T, int(max_frame_points))
+    L = lib()
+    ws_bytes = L.cluster_frames_workspace(F, T, int(max_frame_points))
     ws = _workspace(ws_bytes, dev, stream)
-    with torch.cuda.device(dev):
-        st = lib().cluster_frames(_ptr(xy), _ptr(offsets), F, T, int(max_frame_points),
-                                  eps_to_quanta(eps_px), int(min_pts), _ptr(labels), _ptr(kind),
-                                  _ptr(ncl), _ptr(ws), ws_bytes, _stream(stream))
-    _check(st)
+    _call(L.cluster_frames, dev, stream, _ptr(xy), _ptr(offsets), F, T, int(max_frame_points),
+          eps_to_quanta(eps_px), int(min_pts), _ptr(labels), _ptr(kind), _ptr(ncl), _ptr(ws), ws_bytes)
     return labels, kind, ncl
 
 
@@ -164,14 +176,11 @@ def density_frames(xy: torch.Tensor, offsets: torch.Tensor, width_px: int, heigh
     dev = xy.device
     dens = out if out is not None else torch.empty((max(F, 0), grid_h, grid_w), dtype=torch.float32,
                                                   device=dev)
-    ws_bytes = lib().density_frames_workspace(F, T, int(grid_w), int(grid_h))
+    L = lib()
+    ws_bytes = L.density_frames_workspace(F, T, int(grid_w), int(grid_h))
     ws = _workspace(ws_bytes, dev, stream)
-    with torch.cuda.device(dev):
-        st = lib().density_frames(_ptr(xy), _ptr(offsets), F, T, int(max_frame_points),
-                                  int(width_px), int(height_px),
-                                  int(grid_w), int(grid_h), float(sigma_px), _ptr(dens), _ptr(ws),
-                                  ws_bytes, _stream(stream))
-    _check(st)
+    _call(L.density_frames, dev, stream, _ptr(xy), _ptr(offsets), F, T, int(max_frame_points), int(width_px),
+          int(height_px), int(grid_w), int(grid_h), float(sigma_px), _ptr(dens), _ptr(ws), ws_bytes)
     return dens
 
 
@@ -197,14 +206,12 @@ def heatmap_frames(density: torch.Tensor, cell_area_px2: float, threshold: float
                "degree": torch.empty(F, dtype=torch.float64, device=dev),
                "comp_cells": torch.empty((F, gh, gw), dtype=torch.int32, device=dev),
                "comp_mass": torch.empty((F, gh, gw), dtype=torch.float64, device=dev)}
-    ws_bytes = lib().heatmap_frames_workspace(F, gw, gh)
+    L = lib()
+    ws_bytes = L.heatmap_frames_workspace(F, gw, gh)
     ws = _workspace(ws_bytes, dev, stream)
-    with torch.cuda.device(dev):
-        st = lib().heatmap_frames(_ptr(density), F, gw, gh, float(cell_area_px2), float(threshold),
-                                  int(connectivity), _ptr(out["labels"]), _ptr(out["n_components"]),
-                                  _ptr(out["entropy"]), _ptr(out["degree"]), _ptr(out["comp_cells"]),
-                                  _ptr(out["comp_mass"]), _ptr(ws), ws_bytes, _stream(stream))
-    _check(st)
+    _call(L.heatmap_frames, dev, stream, _ptr(density), F, gw, gh, float(cell_area_px2), float(threshold),
+          int(connectivity), _ptr(out["labels"]), _ptr(out["n_components"]), _ptr(out["entropy"]),
+          _ptr(out["degree"]), _ptr(out["comp_cells"]), _ptr(out["comp_mass"]), _ptr(ws), ws_bytes)
     return out
 
 
@@ -226,13 +233,12 @@ def roi_filter_frames(xy: torch.Tensor, offsets: torch.Tensor, roi_xy, with_inde
                "xy": torch.empty((T, 2), dtype=torch.int32, device=dev),
                "offsets": torch.empty(F + 1, dtype=torch.int32, device=dev),
                "index": torch.empty(T, dtype=torch.int32, device=dev) if with_index else None}
-    ws_bytes = lib().roi_filter_frames_workspace(F, T)
+    L = lib()
+    ws_bytes = L.roi_filter_frames_workspace(F, T)
     ws = _workspace(ws_bytes, dev, stream)
-    with torch.cuda.device(dev):
-        st = lib().roi_filter_frames(_ptr(xy), _ptr(offsets), F, T, poly.ctypes.data_as(ctypes.c_void_p),
-                                     poly.shape[0], _ptr(out["counts"]), _ptr(out["xy"]), _ptr(out["offsets"]),
-                                     _ptr(out.get("index")), _ptr(ws), ws_bytes, _stream(stream))
-    _check(st)
+    _call(L.roi_filter_frames, dev, stream, _ptr(xy), _ptr(offsets), F, T, poly.ctypes.data, poly.shape[0],
+          _ptr(out["counts"]), _ptr(out["xy"]), _ptr(out["offsets"]), _ptr(out.get("index")), _ptr(ws),
+          ws_bytes)
     return out
 
 
@@ -252,14 +258,12 @@ def drinker_proximity_frames(xy: torch.Tensor, offsets: torch.Tensor, lines, thr
         out = {"drinking": torch.empty(T, dtype=torch.uint8, device=dev),
                "line": torch.empty(T, dtype=torch.int32, device=dev) if with_line else None,
                "counts": torch.empty(max(F, 0), dtype=torch.int32, device=dev)}
-    ws_bytes = lib().drinker_proximity_frames_workspace(F, T)
+    L = lib()
+    ws_bytes = L.drinker_proximity_frames_workspace(F, T)
     ws = _workspace(ws_bytes, dev, stream)
-    with torch.cuda.device(dev):
-        st = lib().drinker_proximity_frames(_ptr(xy), _ptr(offsets), F, T, ln.ctypes.data_as(ctypes.c_void_p),
-                                            ln.shape[0], int(threshold_q), _ptr(out["drinking"]),
-                                            _ptr(out.get("line")), _ptr(out["counts"]), _ptr(ws), ws_bytes,
-                                            _stream(stream))
-    _check(st)
+    _call(L.drinker_proximity_frames, dev, stream, _ptr(xy), _ptr(offsets), F, T, ln.ctypes.data, ln.shape[0],
+          int(threshold_q), _ptr(out["drinking"]), _ptr(out.get("line")), _ptr(out["counts"]), _ptr(ws),
+          ws_bytes)
     return out
 
 
@@ -301,15 +305,13 @@ def mask_components_frames(prob: torch.Tensor, threshold: float, connectivity: i
                "centroid": torch.empty((C, 2), dtype=torch.float64, device=dev),
                "xy": torch.empty((C, 2), dtype=torch.int32, device=dev),
                "score": torch.empty(C, dtype=torch.float32, device=dev)}
-    ws_bytes = lib().mask_components_frames_workspace(F, W, H, int(connectivity))
+    L = lib()
+    ws_bytes = L.mask_components_frames_workspace(F, W, H, int(connectivity))
     ws = _workspace(ws_bytes, dev, stream)
-    with torch.cuda.device(dev):
-        st = lib().mask_components_frames(_ptr(prob), F, W, H, float(threshold), int(connectivity),
-                                          _ptr(out.get("labels")), _ptr(out["n_components"]), _ptr(out["offsets"]),
-                                          C, _ptr(out.get("label")), _ptr(out.get("area")), _ptr(out.get("box")),
-                                          _ptr(out.get("centroid")), _ptr(out.get("xy")), _ptr(out.get("score")),
-                                          _ptr(ws), ws_bytes, _stream(stream))
-    _check(st)
+    _call(L.mask_components_frames, dev, stream, _ptr(prob), F, W, H, float(threshold), int(connectivity),
+          _ptr(out.get("labels")), _ptr(out["n_components"]), _ptr(out["offsets"]), C, _ptr(out.get("label")),
+          _ptr(out.get("area")), _ptr(out.get("box")), _ptr(out.get("centroid")), _ptr(out.get("xy")),
+          _ptr(out.get("score")), _ptr(ws), ws_bytes)
     return out
 
 
