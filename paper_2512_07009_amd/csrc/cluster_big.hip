@@ -95,33 +95,72 @@ __device__ __forceinline__ bool frame_ok(const ClusterArgs &a, int f, int32_t *b
     return !(*b < 0 || *e < *b || *e > a.total);
 }
 
-// Frame holding global point index i: the last f with offsets[f] <= i, or -1
-// when i lies past that frame's end (points beyond offsets[n_frames], or
-// under a frame whose offsets decrease): such points belong to no frame and
-// are never read.
-__device__ __forceinline__ int frame_of_point(const int32_t *offsets, int n_frames, int32_t i) {
-    int lo = 0, hi = n_frames - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (offsets[mid] <= i) lo = mid;
-        else hi = mid - 1;
-    }
-    return (i >= offsets[lo] && i < offsets[lo + 1]) ? lo : -1;
+__device__ __forceinline__ int64_t cell_base(const int32_t *offsets, int f) {
+    return 2 * (int64_t)offsets[f] + 2 * (int64_t)f;
 }
 
-// Frame owning cell-table entry c: the last f with 2 offsets[f] + 2 f <= c.
-__device__ __forceinline__ int frame_of_cell(const int32_t *offsets, int n_frames, int64_t c) {
-    int lo = 0, hi = n_frames - 1;
+// Last f with key(f) <= v for a value v equal in every lane (f = 0 when there
+// is none), the keys non-decreasing: 64 probes per round, one round for up to
+// 64 frames, two for 4096.  A search of its own in every thread costs a
+// dependent load per halving: on 96 frames the far unions' launch spent most of
+// its time there (37 us, now 23.5).
+template <class Key>
+__device__ __forceinline__ int wave_search(int n, int64_t v, Key key) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, len = n;
+    while (len > 1) {
+        const int step = (len + 63) / 64, at = lane * step;
+        const uint64_t m = __ballot(at < len && key(lo + at) <= v);
+        const int k = m ? 63 - __builtin_clzll(m) : 0;
+        lo += k * step;
+        len = min(step, len - k * step);
+    }
+    return lo;
+}
+
+// Last f with key(f) <= v, v non-decreasing over the wave's lanes (every lane
+// takes part): the first lane's by wave_search, and the others' among the next
+// 64 keys, or by halving where a wave spans more frames than that.
+template <class Key>
+__device__ __forceinline__ int lane_search(int n, int64_t v, Key key) {
+    const int lane = threadIdx.x & 63;
+    const int64_t v0 = __shfl(v, 0, 64), v1 = __shfl(v, 63, 64);
+    const int f0 = wave_search(n, v0, key);
+    const int64_t next = f0 + 1 + lane < n ? (int64_t)key(f0 + 1 + lane) : INT64_MAX;
+    const uint64_t m = __ballot(next <= v1);  // frames that begin inside the wave's range
+    if (m == 0) return f0;                    // wave-uniform: most waves lie in one frame
+    int lo = f0, hi = n - 1;
+    if (!(m >> 63)) {
+        // count the keys <= v among the window's popcount(m) first ones
+        const int c = __popcll(m);
+        int before = 0;
+        for (int k = 0; k < c; ++k) before += __shfl(next, k, 64) <= v ? 1 : 0;
+        return f0 + before;
+    }
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (2 * (int64_t)offsets[mid] + 2 * (int64_t)mid <= c) lo = mid;
+        if (key(mid) <= v) lo = mid;
         else hi = mid - 1;
     }
     return lo;
 }
 
-__device__ __forceinline__ int64_t cell_base(const int32_t *offsets, int f) {
-    return 2 * (int64_t)offsets[f] + 2 * (int64_t)f;
+// Frame holding point i, i the wave's consecutive points: the last f with
+// offsets[f] <= i, or -1 when i lies past that frame's end (points beyond
+// offsets[n_frames], or under a frame whose offsets decrease) or past the
+// batch: such points belong to no frame and are never read.  Every lane of the
+// wave takes part.
+__device__ __forceinline__ int frame_of_point(const ClusterArgs &a, int64_t i) {
+    const int32_t *offsets = a.offsets;
+    const int f = lane_search(a.n_frames, i, [offsets](int k) { return (int64_t)offsets[k]; });
+    return (i < a.total && i >= offsets[f] && i < offsets[f + 1]) ? f : -1;
+}
+
+// Frame owning cell-table entry c: the last f with 2 offsets[f] + 2 f <= c
+// (every lane takes part).
+__device__ __forceinline__ int frame_of_cell(const ClusterArgs &a, int64_t c) {
+    const int32_t *offsets = a.offsets;
+    return lane_search(a.n_frames, c, [offsets](int k) { return cell_base(offsets, k); });
 }
 
 struct BigGrid {
@@ -273,9 +312,8 @@ __global__ __launch_bounds__(kPrepThreads) void big_prep(ClusterArgs a, BigWs w)
 }
 
 __global__ __launch_bounds__(kBlock) void big_hist(ClusterArgs a, BigWs w) {
-    const int32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= a.total) return;
-    const int f = frame_of_point(a.offsets, a.n_frames, i);
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int f = frame_of_point(a, i);
     if (f < 0) return;
     const int32_t *rec = w.rec + (size_t)f * kRec;
     if (!rec[kBig]) return;
@@ -341,9 +379,8 @@ __global__ __launch_bounds__(kScanThreads) void big_scan(ClusterArgs a, BigWs w)
 }
 
 __global__ __launch_bounds__(kBlock) void big_scatter(ClusterArgs a, BigWs w) {
-    const int32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= a.total) return;
-    const int f = frame_of_point(a.offsets, a.n_frames, i);
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int f = frame_of_point(a, i);
     if (f < 0) return;
     const int32_t *rec = w.rec + (size_t)f * kRec;
     if (!rec[kBig]) return;
@@ -354,16 +391,16 @@ __global__ __launch_bounds__(kBlock) void big_scatter(ClusterArgs a, BigWs w) {
     const int32_t b = a.offsets[f];
     const int32_t pos = b + w.cstart[cell_base(a.offsets, f) + (int64_t)cy * g.ncx + cx] + w.rank[i];
     w.spos[pos] = p;
-    w.ssid[pos] = i - b;
+    w.ssid[pos] = (int32_t)i - b;
 }
 
 // Neighbour counts (dense cells are all core, the rest stop at min_pts), the
 // union-find parents and kinds, and each core cell's node.
 __global__ __launch_bounds__(kBlock) void big_core(ClusterArgs a, BigWs w) {
-    const int32_t p = blockIdx.x * kBlock + threadIdx.x;
-    if (p >= a.total) return;
-    const int f = frame_of_point(a.offsets, a.n_frames, p);
+    const int64_t at = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int f = frame_of_point(a, at);
     if (f < 0) return;
+    const int32_t p = (int32_t)at;
     const int32_t *rec = w.rec + (size_t)f * kRec;
     if (!rec[kBig]) return;
     const BigGrid g = load_grid(rec);
@@ -404,22 +441,18 @@ __global__ __launch_bounds__(kBlock) void big_core(ClusterArgs a, BigWs w) {
     if (core && g.dense) atomicMin(&w.cnode[cell_base(a.offsets, f) + own], o);
 }
 
-// k-th forward stencil offset (cells after this one in row-major order).
-__device__ __forceinline__ bool forward_offset(const BigGrid &g, int k, int *odx, int *ody) {
-    for (int dy = 0; dy <= g.reach; ++dy) {
-        const int lo = dy == 0 ? 1 : -dx_of(g, dy);
-        const int cnt = dx_of(g, dy) - lo + 1;
-        if (cnt > 0 && k < cnt) {
-            *odx = lo + k;
-            *ody = dy;
-            return true;
-        }
-        k -= max(cnt, 0);
-    }
-    return false;
+// The farther forward cells (those after this one in row-major order, beyond
+// the adjacent ones) lie at most two cells off: (2, 0), (-2, 1), (2, 1) and
+// (-2 .. 2, 2).  The k-th of them, if the stencil holds it.
+constexpr int kFar = 8;
+
+__device__ __forceinline__ bool far_offset(const BigGrid &g, int k, int *odx, int *ody) {
+    *odx = k == 0 ? 2 : k <= 2 ? 4 * k - 6 : k - 5;
+    *ody = k == 0 ? 0 : k <= 2 ? 1 : 2;
+    const int adx = *odx < 0 ? -*odx : *odx;
+    return *ody <= g.reach && adx <= dx_of(g, *ody);
 }
 
-constexpr int kMaxForward = 12;
 constexpr int kAdjacent = 4;  // forward adjacent cells
 
 // Walks a and b to their roots through cached parents, in step (one load
@@ -465,10 +498,10 @@ __device__ __forceinline__ void uf_unite_cached(int32_t *parent, int32_t a, int3
 }
 
 // Point-pair unions of point p when its frame's grid was coarsened.
-__device__ void union_points_one(const ClusterArgs &a, const BigWs &w, int32_t p) {
-    if (p >= a.total || !w.score[p]) return;
-    const int f = frame_of_point(a.offsets, a.n_frames, p);
-    if (f < 0) return;
+__device__ void union_points_one(const ClusterArgs &a, const BigWs &w, int64_t at) {
+    const int f = frame_of_point(a, at);
+    if (f < 0 || !w.score[at]) return;
+    const int32_t p = (int32_t)at;
     const int32_t *rec = w.rec + (size_t)f * kRec;
     if (!rec[kBig] || rec[kDense]) return;
     const BigGrid g = load_grid(rec);
@@ -547,16 +580,6 @@ __device__ __forceinline__ int64_t tile_slot(const int32_t *offsets, int f) {
     return cell_base(offsets, f) / kTileCells + f;
 }
 
-__device__ __forceinline__ int frame_of_slot(const int32_t *offsets, int n_frames, int64_t wg) {
-    int lo = 0, hi = n_frames - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tile_slot(offsets, mid) <= wg) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 __global__ __launch_bounds__(kTileThreads) void big_union_tiles(ClusterArgs a, BigWs w) {
     __shared__ int32_t s_node[kRegionCells];  // node of each region cell; INT_MAX: no core, or off the grid
     __shared__ int32_t s_par[kRegionCells];   // local forest over region cells
@@ -565,7 +588,8 @@ __global__ __launch_bounds__(kTileThreads) void big_union_tiles(ClusterArgs a, B
     __shared__ int s_hook[3];
     const int tid = threadIdx.x;
     const int64_t wg = blockIdx.x;
-    const int f = frame_of_slot(a.offsets, a.n_frames, wg);
+    const int32_t *off = a.offsets;
+    const int f = __builtin_amdgcn_readfirstlane(wave_search(a.n_frames, wg, [off](int k) { return tile_slot(off, k); }));
     const int32_t *rec = w.rec + (size_t)f * kRec;
     if (!rec[kBig]) return;
     const BigGrid g = load_grid(rec);
@@ -673,11 +697,11 @@ __global__ __launch_bounds__(kTileThreads) void big_union_tiles(ClusterArgs a, B
 // whose grid was coarsened.
 __global__ __launch_bounds__(kBlock) void big_union_far(ClusterArgs a, BigWs w, int64_t n_items) {
     const int64_t item = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (item < a.total) union_points_one(a, w, (int32_t)item);  // n_items >= total
+    if ((int64_t)blockIdx.x * kBlock < a.total) union_points_one(a, w, item);  // n_items >= total; the whole workgroup
+    const int64_t c = item / kFar;
+    const int k = (int)(item - c * kFar);
+    const int f = frame_of_cell(a, c);
     if (item >= n_items) return;
-    const int64_t c = item / kMaxForward;
-    const int k = (int)(item - c * kMaxForward);
-    const int f = frame_of_cell(a.offsets, a.n_frames, c);
     const int32_t *rec = w.rec + (size_t)f * kRec;
     if (!rec[kBig] || !rec[kDense]) return;
     const BigGrid g = load_grid(rec);
@@ -685,8 +709,7 @@ __global__ __launch_bounds__(kBlock) void big_union_far(ClusterArgs a, BigWs w, 
     const int32_t ca = (int32_t)(c - base);
     if (ca >= g.ncell) return;
     int odx, ody;
-    if (!forward_offset(g, k, &odx, &ody)) return;
-    if (odx >= -1 && odx <= 1 && ody <= 1) return;  // adjacent: the tiled launch's
+    if (!far_offset(g, k, &odx, &ody)) return;
     const int32_t ay = ca / g.ncx, ax = ca - ay * g.ncx;
     const int32_t bx = ax + odx, by = ay + ody;
     if (bx < 0 || bx >= g.ncx || by >= g.ncy) return;
@@ -721,10 +744,10 @@ __device__ __forceinline__ int32_t node_of(const BigWs &w, const ClusterArgs &a,
 }
 
 __global__ __launch_bounds__(kBlock) void big_label(ClusterArgs a, BigWs w) {
-    const int32_t p = blockIdx.x * kBlock + threadIdx.x;
-    if (p >= a.total) return;
-    const int f = frame_of_point(a.offsets, a.n_frames, p);
+    const int64_t at = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int f = frame_of_point(a, at);
     if (f < 0) return;
+    const int32_t p = (int32_t)at;
     const int32_t *rec = w.rec + (size_t)f * kRec;
     if (!rec[kBig]) return;
     const BigGrid g = load_grid(rec);
@@ -807,7 +830,7 @@ hipError_t launch_cluster_big(const ClusterArgs &a, void *workspace, hipStream_t
         hipLaunchKernelGGL(big_scatter, dim3(pts), dim3(kBlock), 0, stream, a, w);
         hipLaunchKernelGGL(big_core, dim3(pts), dim3(kBlock), 0, stream, a, w);
         // one more slot per frame than the cell table's blocks (tile_slot)
-        const int64_t slots = cells / kTileCells + a.n_frames, items = cells * kMaxForward;
+        const int64_t slots = cells / kTileCells + a.n_frames, items = cells * kFar;
         hipLaunchKernelGGL(big_union_tiles, dim3((unsigned)slots), dim3(kTileThreads), 0, stream, a, w);
         hipLaunchKernelGGL(big_union_far, dim3(blocks_for(items)), dim3(kBlock), 0, stream, a, w, items);
         hipLaunchKernelGGL(big_label, dim3(pts), dim3(kBlock), 0, stream, a, w);
