@@ -352,7 +352,7 @@ flock_status density_run(const int32_t *xy, const int32_t *offsets, int32_t n_fr
     a.grid_h = grid_h;
     a.sigma_px = sigma_px;
     a.density = density;
-    const flock::DensityPlan plan = flock::plan_density(a, dev->n_cus);
+    const flock::DensityPlan plan = flock::plan_density(a, dev->n_cus, workspace ? workspace_bytes : SIZE_MAX);
     if (plan.blocks > 0x7fffffffLL) return fail(FLOCK_EUNSUPPORTED, "batch too large for one launch");
     // a split launch keeps partial grids in the workspace
     const size_t need = plan.split > 1 ? (size_t)n_frames * plan.split * (size_t)grid_w * grid_h * sizeof(float) : 0;

@@ -748,8 +748,9 @@ size_t density_workspace_bytes(int32_t n_frames, int32_t total, int32_t grid_w, 
 
 // The launch plan of either path: region shape, waves per item and bird slices
 // of least modelled time.  FLOCK_DENSITY_SHAPE="rm,rn" forces the region shape
-// (for tuning).
-DensityPlan plan_density(const DensityArgs &a, int n_cus) {
+// (for tuning).  The direct path needs no workspace: it takes slices only where
+// their partial grids fit in `room` bytes.
+DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
     const char *force = std::getenv("FLOCK_DENSITY_SHAPE");
     GatherGeom gg;
     gather_geom(a, &gg);
@@ -768,8 +769,13 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus) {
                 forced = true;
             }
     const GatherForce over = gather_force();
+    auto fits = [&](int slices) {
+        return gg.ay.c || slices <= 1 ||
+               (size_t)a.n_frames * slices * (size_t)a.grid_w * a.grid_h * sizeof(float) <= room;
+    };
     if (forced) {
         gather_split(a.n_frames, g.kept, g.ry * g.rx, n_cus, over, &p.waves, &p.split);
+        if (!fits(p.split)) p.split = 1;
     } else {
         // bird slices where they pay for the second kernel: a launch that
         // would leave most of the chip idle is bound by each wave's own
@@ -780,9 +786,9 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus) {
         const GatherCost sg = gather_regions(ss, gg, a.grid_w, a.grid_h, birds);
         int sw = 1, sp = 1;
         gather_split(a.n_frames, sg.kept, sg.ry * sg.rx, n_cus, over, &sw, &sp);
-        if (over.split >= 1 || over.waves >= 1 ||
-            (sp > 1 && gather_us(ss, sw, sp, gg, sg, a.n_frames, birds, n_cus) <
-                           gather_us(sh, p.waves, 1, gg, g, a.n_frames, birds, n_cus))) {
+        if (fits(sp) && (over.split >= 1 || over.waves >= 1 ||
+                         (sp > 1 && gather_us(ss, sw, sp, gg, sg, a.n_frames, birds, n_cus) <
+                                        gather_us(sh, p.waves, 1, gg, g, a.n_frames, birds, n_cus)))) {
             sh = ss;
             g = sg;
             p.waves = sw;

@@ -81,7 +81,8 @@ struct DensityPlan {
     long long blocks;         // workgroups of the main kernel
 };
 
-DensityPlan plan_density(const DensityArgs &a, int n_cus);
+// `room`: bytes there are for partial grids (SIZE_MAX: as many as a plan takes).
+DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room);
 // Workspace for the partial grids of a split launch (0 if none); depends on the
 // batch shape and grid only, and bounds every plan for that shape.
 size_t density_workspace_bytes(int32_t n_frames, int32_t total, int32_t grid_w, int32_t grid_h, int n_cus);

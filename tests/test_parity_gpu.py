@@ -457,6 +457,27 @@ def test_density_workspace_gpu(monkeypatch):
         assert_density_close(out.cpu().numpy(), ref, np.diff(off), 30.0, tag="workspace")
 
 
+def test_density_direct_path_takes_short_workspace_gpu():
+    """A grid whose cells are no whole number of quanta needs no workspace: one
+    too short for bird slices is taken, and the grid computed without them."""
+    import ctypes
+    rng = np.random.default_rng(6)
+    xy, off = wl.pack([np.stack([rng.integers(0, 16 * 1920, 9000), rng.integers(0, 16 * 1080, 9000)],
+                                1).astype(np.int32)])
+    dxy, doff = dev_batch(xy, off)
+    lib = flock.lib()
+    assert lib.density_frames_workspace(1, xy.shape[0], 97, 61) > 256
+    ref = oracle.density_frames(xy, off, 1920, 1080, 97, 61, 30.0)
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda")
+    out = torch.full((1, 61, 97), -1.0, dtype=torch.float32, device="cuda")
+    st = lib.density_frames(ctypes.c_void_p(dxy.data_ptr()), ctypes.c_void_p(doff.data_ptr()), 1, xy.shape[0], 0, 1920,
+                            1080, 97, 61, ctypes.c_float(30.0), ctypes.c_void_p(out.data_ptr()),
+                            ctypes.c_void_p(ws.data_ptr()), 256, None)
+    assert st == 0, lib.flock_last_error().decode()
+    torch.cuda.synchronize()
+    assert_density_close(out.cpu().numpy(), ref, np.diff(off), 30.0, tag="short workspace")
+
+
 def test_density_single_bird_peak_gpu():
     sigma = 30.0
     # bird exactly at the centre of cell (40, 30) of a 128 x 72 grid on 1920 x 1080
