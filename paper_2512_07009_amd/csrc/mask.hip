@@ -57,7 +57,7 @@ constexpr int kRunsPerThread = kMaxRuns / kMThreads;
 constexpr int kBitBlock = 512;                  // bits per count block
 constexpr int kBitWords = kBitBlock / 32;
 constexpr int kSuper = 64;                      // blocks per superblock
-constexpr int kRelabel = 16;                    // relabelled pixels per lane per pass
+constexpr int kRelabel = 8;                     // relabelled pixels per lane per pass
 constexpr int kSuperBits = kBitBlock * kSuper;
 constexpr int kLocalSuper = 2048;               // superblocks the finish kernel scans itself (2^26 pixels)
 
@@ -107,6 +107,23 @@ __device__ __forceinline__ int run_last(uint64_t m, int x) {
     return x + __builtin_ctzll(en >> x);
 }
 
+// Is this lane's bit of a uniform mask set?
+__device__ __forceinline__ bool lane_of(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// A value equal in every lane, as a scalar.
+__device__ __forceinline__ uint64_t uniform64(uint64_t m) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)m) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(m >> 32)) << 32;
+}
+
+// Id of the run that holds this lane's pixel in a row of uniform mask m, its
+// first run numbered `first`: one more for every run that ended before the lane.
+__device__ __forceinline__ int run_id(uint64_t m, int first) {
+    const uint64_t en = m & ~(m >> 1);
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(en >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((uint32_t)en, (uint32_t)first));
+}
+
 struct TileLoc {
     int f, tx, ty, X0, Y0, tw, th;
     int64_t base;  // first slot of the tile
@@ -136,13 +153,17 @@ __device__ __forceinline__ int64_t tile_cap(const MaskArgs &a, const TileLoc &t)
     return a.connectivity == 8 ? (int64_t)((t.tw + 1) / 2) * ((t.th + 1) / 2) : ((int64_t)t.tw * t.th + 1) / 2;
 }
 
+// Bound by instruction issue and the chain of phases between a tile's loads
+// and stores.  8 frames of 1280 x 720: 35.5 us a launch, 41.1 with 64-bit
+// vector arithmetic on every row's bits (rows are scalar masks now, empty ones
+// skipped) and a label made per pixel instead of per run.
 __global__ __launch_bounds__(kMThreads) void mask_tile_kernel(MaskArgs a, MaskWs w) {
     __shared__ uint64_t s_mask[kT];
     __shared__ int32_t s_rowbase[kT + 1];    // first run id of each row; [kT] = number of runs
-    __shared__ int32_t s_side[2][kT];        // slots of the tile's left and right columns
     __shared__ uint16_t s_run[kMaxRuns];     // row | first pixel << 6
     __shared__ int32_t s_P[kMaxRuns];        // union-find over runs, then piece | first pixel << 11
-    __shared__ uint32_t s_rmax[kMaxRuns];    // largest probability of each run (bits; > 0, ordered as integers)
+    // largest probability of each run (bits; > 0, ordered as integers), then the run's label
+    __shared__ uint32_t s_rmax[kMaxRuns];
     __shared__ MaskAcc s_acc[kAccCap];
     __shared__ int32_t s_wtot[kMThreads / 64];
 
@@ -198,18 +219,17 @@ __global__ __launch_bounds__(kMThreads) void mask_tile_kernel(MaskArgs a, MaskWs
 #pragma unroll
         for (int i = 0; i < kRows; ++i) {
             const int r = wave * kRows + i;
-            const bool fg = col_ok && r < t.th && v[i] > a.threshold;
-            const uint64_t mr = __ballot(fg);
+            const uint64_t mr = __ballot(col_ok && r < t.th && v[i] > a.threshold);
+            if (mr == 0) continue;  // uniform
             const int rbr = __builtin_amdgcn_readlane(excl, r);  // first run id of row r
-            const uint64_t st = mr & ~(mr << 1);
-            const int id = rbr + __popcll(st & le) - 1;
-            if ((st >> lane) & 1) {
+            const int id = run_id(mr, rbr);
+            if (lane_of(mr & ~(mr << 1))) {
                 s_run[id] = (uint16_t)(r | lane << 6);
                 s_P[id] = id;
                 s_rmax[id] = 0u;
             }
             // after the run's first lane cleared it: one wave's LDS operations run in order
-            if (fg) atomicMax(&s_rmax[id], __float_as_uint(v[i]));
+            if (lane_of(mr)) atomicMax(&s_rmax[id], __float_as_uint(v[i]));
         }
     }
     __syncthreads();
@@ -246,7 +266,8 @@ __global__ __launch_bounds__(kMThreads) void mask_tile_kernel(MaskArgs a, MaskWs
 #pragma unroll
     for (int k = 0; k < kRunsPerThread; ++k) {
         const int j = tid + k * kMThreads;
-        rt[k] = j < nruns ? cl::uf_find<kGroup>(s_P, j) : -1;
+        rt[k] = -1;
+        if (k * kMThreads < nruns && j < nruns) rt[k] = cl::uf_find<kGroup>(s_P, j);
     }
     __syncthreads();
     int np = 0;
@@ -280,35 +301,8 @@ __global__ __launch_bounds__(kMThreads) void mask_tile_kernel(MaskArgs a, MaskWs
     }
     __syncthreads();
 
-    // 5. labels (the piece's first pixel for now) and the tile's outer slots
+    // 5. statistics per run, kAccCap pieces per pass
     const int64_t cap = tile_cap(a, t);
-    const int32_t lab0 = t.Y0 * a.width + t.X0;  // frame index of the tile's first pixel
-    int32_t *lrow0 = a.labels ? a.labels + fbase + lab0 : nullptr;
-#pragma unroll
-    for (int i = 0; i < kRows; ++i) {
-        const int r = wave * kRows + i;
-        if (r >= t.th) continue;
-        const uint64_t ml = s_mask[r];  // reloaded: the row masks do not stay in scalar registers
-        const uint64_t mr = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)ml) |
-                            (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ml >> 32)) << 32;
-        const uint64_t st = mr & ~(mr << 1);
-        const bool fg = (mr >> lane) & 1;
-        const int pk = fg ? s_P[s_rowbase[r] + __popcll(st & le) - 1] : -1;
-        const int pc = pk & 0x7ff, fp = pk >> 11;
-        const int32_t lab = fg ? lab0 + (int32_t)__umul24((uint32_t)(fp >> 6), (uint32_t)a.width) + (fp & 63) : -1;
-        const int32_t slot = fg && pc < cap ? (int32_t)t.base + pc : -1;
-        if (lrow0 && col_ok) lrow0[(int64_t)r * a.width + lane] = lab;
-        if (r == 0 && col_ok) w.hseam[((int64_t)(t.f * a.tiles_y + t.ty) * 2 + 0) * a.width + t.X0 + lane] = slot;
-        if (r == t.th - 1 && col_ok)
-            w.hseam[((int64_t)(t.f * a.tiles_y + t.ty) * 2 + 1) * a.width + t.X0 + lane] = slot;
-        if (lane == 0) s_side[0][r] = slot;
-        if (lane == t.tw - 1) s_side[1][r] = slot;
-    }
-    __syncthreads();
-    if (wave < 2 && lane < t.th)
-        w.vseam[((int64_t)(t.f * a.tiles_x + t.tx) * 2 + wave) * a.height + t.Y0 + lane] = s_side[wave][lane];
-
-    // 6. statistics per run, kAccCap pieces per pass
     for (int c0 = 0; c0 < np; c0 += kAccCap) {
         if (tid < kAccCap) s_acc[tid] = MaskAcc{0u, 0u, 0u, 63u, 0u, 0u, 0u, 0u};
         __syncthreads();
@@ -352,6 +346,41 @@ __global__ __launch_bounds__(kMThreads) void mask_tile_kernel(MaskArgs a, MaskWs
             w.gp[slot] = ((uint64_t)(fbase + fl) << 32) | (uint64_t)slot;
         }
         __syncthreads();
+    }
+    // 6. labels (the piece's first pixel for now), made once per run in the
+    //    place of the runs' probabilities, and the tile's outer slots
+    const int32_t lab0 = t.Y0 * a.width + t.X0;  // frame index of the tile's first pixel
+    if (a.labels) {
+        int32_t *s_lab = reinterpret_cast<int32_t *>(s_rmax);
+        for (int j = tid; j < nruns; j += kMThreads) {
+            const int fp = s_P[j] >> 11;
+            s_lab[j] = lab0 + (int32_t)__umul24((uint32_t)(fp >> 6), (uint32_t)a.width) + (fp & 63);
+        }
+        __syncthreads();
+        int32_t *lrow0 = a.labels + fbase + lab0;
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
+            const int r = wave * kRows + i;
+            if (r >= t.th) break;
+            const uint64_t mr = uniform64(s_mask[r]);
+            int32_t lab = -1;
+            if (lane_of(mr)) lab = s_lab[run_id(mr, s_rowbase[r])];
+            if (col_ok) lrow0[(int64_t)r * a.width + lane] = lab;
+        }
+    }
+    // a wave for each outer row and column
+    {
+        const int r = wave == 0 ? 0 : wave == 1 ? t.th - 1 : lane;
+        const int x = wave < 2 ? lane : wave == 2 ? 0 : t.tw - 1;
+        const bool in = wave < 2 ? col_ok : lane < t.th;
+        const uint64_t mr = s_mask[r];
+        int32_t slot = -1;
+        if ((mr >> x) & 1) {
+            const int pc = s_P[s_rowbase[r] + __popcll(mr & ~(mr << 1) & bits_upto(x)) - 1] & 0x7ff;
+            if (pc < cap) slot = (int32_t)t.base + pc;
+        }
+        if (in && wave < 2) w.hseam[((int64_t)(t.f * a.tiles_y + t.ty) * 2 + wave) * a.width + t.X0 + lane] = slot;
+        if (in && wave >= 2) w.vseam[((int64_t)(t.f * a.tiles_x + t.tx) * 2 + wave - 2) * a.height + t.Y0 + lane] = slot;
     }
     if (tid == 0) w.tile_np[blockIdx.x] = (int32_t)min((int64_t)np, cap);
 }
@@ -408,27 +437,32 @@ __device__ __forceinline__ void key_unite(uint64_t *gp, uint32_t a, uint32_t b) 
 
 // Slots P[i] and Q[i-1..i+1] (Q[i] only with 4 neighbours) face each other
 // across a seam; each touching pair is united at its first position along
-// the seam.
+// the seam.  All slots are loaded at once.
 __device__ __forceinline__ void join_seam(uint64_t *gp, const int32_t *P, const int32_t *Q, int i, int n,
                                           bool eight) {
     const int32_t p = P[i];
+    const int32_t pl = P[max(i - 1, 0)], pp = i > 0 ? pl : -1;
+    int32_t q[4];  // Q[i - 2 .. i + 1], -1 past the ends
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int j = i - 2 + k;
+        const int32_t v = Q[min(max(j, 0), n - 1)];
+        q[k] = j >= 0 && j < n ? v : -1;
+    }
     if (p < 0) return;
-    const int32_t pp = i > 0 ? P[i - 1] : -1;
-    int32_t prevq = -1;
-    for (int d = eight ? -1 : 0; d <= (eight ? 1 : 0); ++d) {
-        const int j = i + d;
-        if (j < 0 || j >= n) continue;
-        const int32_t q = Q[j];
-        if (q < 0 || q == prevq) {
-            prevq = q;
-            continue;
-        }
-        prevq = q;
-        if (pp == p && j > 0 && Q[j - 1] == q) continue;  // same pair one step back
-        key_unite(gp, (uint32_t)p, (uint32_t)q);
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+        if (k != 2 && !eight) continue;
+        if (q[k] < 0 || (eight && k > 1 && q[k] == q[k - 1])) continue;
+        if (pp == p && q[k - 1] == q[k]) continue;  // same pair one step back
+        key_unite(gp, (uint32_t)p, (uint32_t)q[k]);
     }
 }
 
+// Bound by latency (the walks in the global forest): 8 frames of 1280 x 720,
+// 13.0 us, 14.8 when a position's slots were loaded one after another.  Walks
+// through the XCD's cache without halving gave 15.0, and longer paths for
+// mask_resolve_kernel to walk (14.3 against 13.2).
 __global__ __launch_bounds__(256) void mask_seam_kernel(MaskArgs a, MaskWs w, int64_t nh, int64_t nv) {
     int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const bool eight = a.connectivity == 8;
@@ -568,18 +602,34 @@ __global__ __launch_bounds__(1024) void mask_scan_kernel(MaskArgs a, MaskWs w) {
     }
 }
 
+// floor(16 sum / area), from the fp64 quotient c = sum / area: its error is
+// far below one (a coordinate is below 2^31), so the floor is off by one at
+// most, which the remainder tells (two 64-bit divisions took longer than the
+// rest of a root's outputs).
+__device__ __forceinline__ int floor_sixteenths(double c, uint64_t sum, uint32_t area) {
+    const int64_t q = (int64_t)(16.0 * c);
+    const int64_t r = (int64_t)(16ull * sum) - q * (int64_t)area;
+    return (int)(r < 0 ? q - 1 : r >= (int64_t)area ? q + 1 : q);
+}
+
+// Bound by latency: a tile's records, ranks and boxes one after another.  8
+// frames of 1280 x 720: 20.3 us, 21.8 when a piece's record was loaded again
+// to relabel it, every pixel of a box took a division and the waves waited for
+// the roots' outputs.
 __global__ __launch_bounds__(kMThreads) void mask_finish_kernel(MaskArgs a, MaskWs w) {
-    __shared__ int32_t s_list[kT * kT / 2];
+    // pieces to relabel: box and first pixel's column in the tile (6 bits each:
+    // x0, y0, width - 1, height - 1, column), and the component's label
+    __shared__ uint32_t s_list[kT * kT / 2];
+    __shared__ int32_t s_lab[kT * kT / 2];
     __shared__ int32_t s_sbb[kLocalSuper + 1];
     __shared__ int s_wtot[kMThreads / 64];
-    __shared__ int32_t s_n;
+    __shared__ int32_t s_n, s_next;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const TileLoc t = tile_loc(a, blockIdx.x);
     const int np = w.tile_np[blockIdx.x];
     const int64_t WH = (int64_t)a.width * a.height;
     const int64_t fbase = (int64_t)t.f * WH;
-    if (tid == 0) s_n = 0;
+    if (tid == 0) s_n = s_next = 0;
     // the superblock bases: scanned here from the counts when they fit in
     // LDS (no separate scan launch), else read from the scan kernel
     const int32_t *sbbase = w.sbbase;
@@ -611,18 +661,38 @@ __global__ __launch_bounds__(kMThreads) void mask_finish_kernel(MaskArgs a, Mask
             if (f < a.n_frames) a.n_components[f] = rank_before(w, sbbase, (int64_t)(f + 1) * WH) - r0;
         }
     }
+    // a thread's first piece stays in registers; further ones (tiles of more
+    // than kMThreads pieces) are loaded again
+    uint64_t k = 0;
+    MaskRec R;
+    bool root = false;
     for (int p = tid; p < np; p += kMThreads) {
         const uint32_t s = (uint32_t)(t.base + p);
-        const uint64_t k = w.gp[s];
-        if ((uint32_t)k != s) {
-            if (a.labels) {
-                // a piece that is not its component's first: its pixels carry
-                // the piece's own first pixel, to be replaced by the root's
-                s_list[atomicAdd(&s_n, 1)] = p;
-            }
-            continue;
+        const uint64_t key = w.gp[s];
+        const MaskRec rec = w.rec[s];  // in flight together
+        if (p < kMThreads) {
+            k = key;
+            R = rec;
+            root = (uint32_t)key == s;
         }
-        const MaskRec R = w.rec[s];  // in flight with the rank's loads
+        if ((uint32_t)key != s && a.labels) {
+            // a piece that is not its component's first: its pixels carry
+            // the piece's own first pixel, to be replaced by the root's
+            const int i = atomicAdd(&s_n, 1);
+            const uint32_t fx = rec.root - rec.y0 * (uint32_t)a.width - (uint32_t)t.X0;
+            s_list[i] = (rec.x0 - t.X0) | (rec.y0 - t.Y0) << 6 | (rec.x1 - rec.x0) << 12 | (rec.y1 - rec.y0) << 18 | fx << 24;
+            s_lab[i] = (int32_t)((int64_t)(key >> 32) - fbase);
+        }
+    }
+    __syncthreads();
+    for (int p = tid; p < np; p += kMThreads) {
+        if (p >= kMThreads) {
+            const uint32_t s = (uint32_t)(t.base + p);
+            k = w.gp[s];
+            R = w.rec[s];
+            root = (uint32_t)k == s;
+        }
+        if (!root) continue;
         const int64_t rank = rank_before(w, sbbase, (int64_t)(k >> 32));
         if (rank >= a.capacity) continue;
         if (a.comp_label) a.comp_label[rank] = (int32_t)R.root;
@@ -630,39 +700,41 @@ __global__ __launch_bounds__(kMThreads) void mask_finish_kernel(MaskArgs a, Mask
         if (a.comp_box)
             reinterpret_cast<int4 *>(a.comp_box)[rank] =
                 make_int4((int)R.x0, (int)R.y0, (int)(R.x1 - R.x0 + 1), (int)(R.y1 - R.y0 + 1));
-        if (a.comp_centroid)
-            reinterpret_cast<double2 *>(a.comp_centroid)[rank] =
-                make_double2((double)R.sx / (double)R.area, (double)R.sy / (double)R.area);
+        const double cx = (double)R.sx / (double)R.area, cy = (double)R.sy / (double)R.area;
+        if (a.comp_centroid) reinterpret_cast<double2 *>(a.comp_centroid)[rank] = make_double2(cx, cy);
         if (a.comp_xy)
             reinterpret_cast<int2 *>(a.comp_xy)[rank] =
-                make_int2((int)((16ull * R.sx) / R.area), (int)((16ull * R.sy) / R.area));
+                make_int2(floor_sixteenths(cx, R.sx, R.area), floor_sixteenths(cy, R.sy, R.area));
         if (a.comp_score) a.comp_score[rank] = __uint_as_float(R.score);
     }
     if (!a.labels) return;
-    __syncthreads();
-    // each wave relabels one piece's box at a time, kRelabel pixels per lane
-    // in flight (loads first, then stores)
+    // each wave takes a piece from the list in turn (the waves without roots
+    // the most) and relabels its box, as many whole rows per step as it has
+    // lanes for, kRelabel steps in flight (loads first, then stores)
     const int n = s_n;
-    for (int q = wave; q < n; q += kMThreads / 64) {
-        const uint32_t s = (uint32_t)(t.base + s_list[q]);
-        const MaskRec R = w.rec[s];
-        const int32_t old = (int32_t)R.root;
-        const int32_t lab = (int32_t)((int64_t)(w.gp[s] >> 32) - fbase);
-        const int bw = (int)(R.x1 - R.x0 + 1), nb = bw * (int)(R.y1 - R.y0 + 1);
-        int32_t *row0 = a.labels + fbase + (int64_t)R.y0 * a.width + R.x0;
-        for (int e0 = 0; e0 < nb; e0 += 64 * kRelabel) {
+    for (;;) {
+        int q = 0;
+        if (lane == 0) q = atomicAdd(&s_next, 1);
+        q = __builtin_amdgcn_readfirstlane(q);
+        if (q >= n) break;
+        const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_list[q]);
+        const int32_t lab = s_lab[q];
+        const int bw = (int)(m >> 12 & 63) + 1, bh = (int)(m >> 18 & 63) + 1;
+        const int y0 = t.Y0 + (int)(m >> 6 & 63);
+        const int32_t old = y0 * a.width + t.X0 + (int)(m >> 24 & 63);
+        const int rows = 64 / bw, ey = lane / bw, ex = lane - ey * bw;
+        int32_t *row0 = a.labels + fbase + (int64_t)y0 * a.width + t.X0 + (m & 63);
+        const int end = ey < rows ? bh : 0;
+        for (int r0 = 0; r0 < bh; r0 += rows * kRelabel) {
             int32_t cur[kRelabel];
-            int64_t at[kRelabel];
 #pragma unroll
             for (int u = 0; u < kRelabel; ++u) {
-                const int e = e0 + u * 64 + lane;
-                const int ey = e / bw;
-                at[u] = (int64_t)ey * a.width + (e - ey * bw);
-                cur[u] = e < nb ? row0[at[u]] : -1;
+                const int r = r0 + u * rows + ey;
+                cur[u] = r < end ? row0[(int64_t)r * a.width + ex] : -1;
             }
 #pragma unroll
             for (int u = 0; u < kRelabel; ++u)
-                if (e0 + u * 64 + lane < nb && cur[u] == old) row0[at[u]] = lab;
+                if (cur[u] == old) row0[(int64_t)(r0 + u * rows + ey) * a.width + ex] = lab;
         }
     }
 }
