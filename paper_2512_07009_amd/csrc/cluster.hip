@@ -1022,13 +1022,15 @@ __device__ __forceinline__ void cluster_resident(const ClusterArgs &a) {
         else atomicMin(&cell[c], (uint32_t)c0 | ((uint32_t)i << 16));
     }
     __syncthreads();
+    // the list's length, read by every wave before the barrier after 4b: step
+    // 5 clears s_nlist for the border list without another one
+    const int32_t nwork = __builtin_amdgcn_readfirstlane(s_nlist);
     // 4b. count the listed points' neighbours, nearest rows first, stopping
     //     at min_pts; the bounds of all 2 reach + 1 <= 5 row spans are
     //     loaded before the first scan
     {
-        const int32_t nl = s_nlist;
         const int dxm0 = g.dxmax[0], dxm1 = g.reach >= 1 ? g.dxmax[1] : 0, dxm2 = g.reach >= 2 ? g.dxmax[2] : 0;
-        for (int32_t j = tid; j < nl; j += kThreads) {
+        for (int32_t j = tid; j < nwork; j += kThreads) {
             const int32_t p = list[j];
             const uint32_t v = pxy[p];
             int32_t cx, cy;
@@ -1059,7 +1061,7 @@ __device__ __forceinline__ void cluster_resident(const ClusterArgs &a) {
     // 5. forest roots, and the smallest core index of each cell whose cores
     //    came from the counts (dense cells had theirs set in the scatter)
     for (int32_t p = tid; p < n; p += kThreads) parent[p] = p;
-    for (int32_t j = tid; j < s_nlist; j += kThreads) {
+    for (int32_t j = tid; j < nwork; j += kThreads) {
         const int32_t p = list[j];
         if (score[p] == kCore) {
             int32_t cx, cy;

@@ -338,6 +338,24 @@ def test_determinism_and_batch_independence_gpu():
     assert np.array_equal(alone[1], a[1][off[3]:off[4]])
 
 
+@pytest.mark.parametrize("frames", [400, 200])
+def test_work_list_length_race_gpu(frames):
+    """Batches whose core cells mostly come from the work list (uniform birds,
+    few dense cells), on both on-chip kernels (two workgroups per compute unit
+    above 256 frames), clustered again and again: every pass gives the oracle's
+    labels.  (The list's counter was once cleared while slower waves still
+    read its length, so that a frame now and then lost cores.)"""
+    rng = np.random.default_rng(frames)
+    xy, off = wl.pack([np.stack([rng.integers(0, 16 * 1920, 1713), rng.integers(0, 16 * 1080, 1713)], 1).astype(np.int32)
+                       for _ in range(frames)])
+    rl, rk, rn = oracle.cluster_frames(xy, off, 728, 9)
+    dxy, doff = dev_batch(xy, off)
+    want = [torch.from_numpy(v).to("cuda") for v in (rl, rk, rn)]
+    for k in range(40):
+        got = flock.cluster_frames(dxy, doff, 728 / 16.0, 9, 1713)
+        assert all(torch.equal(g, w) for g, w in zip(got, want)), f"pass {k}"
+
+
 def test_permutation_invariance_gpu():
     xy, off, w = wl.generate("batch64x2000_1080p", n_frames=1)
     base_l, base_k, base_n = run_cluster(xy, off, w.eps_q, w.min_pts)
