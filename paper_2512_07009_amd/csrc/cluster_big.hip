@@ -95,15 +95,21 @@ __device__ __forceinline__ bool frame_ok(const ClusterArgs &a, int f, int32_t *b
     return !(*b < 0 || *e < *b || *e > a.total);
 }
 
+// (A negative offset, which no consistent frame has, counts as past the end.)
 __device__ __forceinline__ int64_t cell_base(const int32_t *offsets, int f) {
-    return 2 * (int64_t)offsets[f] + 2 * (int64_t)f;
+    return 2 * (int64_t)(uint32_t)offsets[f] + 2 * (int64_t)f;
 }
 
+// The searches below take the keys to be non-decreasing, as those of a valid
+// batch are.  A batch with inconsistent frames may have keys out of order,
+// and a search then may miss a consistent frame for some of its points only;
+// big_scan drops a frame that is not whole.
+
 // Last f with key(f) <= v for a value v equal in every lane (f = 0 when there
-// is none), the keys non-decreasing: 64 probes per round, one round for up to
-// 64 frames, two for 4096.  A search of its own in every thread costs a
-// dependent load per halving: on 96 frames the far unions' launch spent most of
-// its time there (37 us, now 23.5).
+// is none): 64 probes per round, one round for up to 64 frames, two for 4096.
+// A search of its own in every thread costs a dependent load per halving: on
+// 96 frames the far unions' launch spent most of its time there (37 us, now
+// 23.5).
 template <class Key>
 __device__ __forceinline__ int wave_search(int n, int64_t v, Key key) {
     const int lane = threadIdx.x & 63;
@@ -131,11 +137,13 @@ __device__ __forceinline__ int lane_search(int n, int64_t v, Key key) {
     if (m == 0) return f0;                    // wave-uniform: most waves lie in one frame
     int lo = f0, hi = n - 1;
     if (!(m >> 63)) {
-        // count the keys <= v among the window's popcount(m) first ones
-        const int c = __popcll(m);
-        int before = 0;
-        for (int k = 0; k < c; ++k) before += __shfl(next, k, 64) <= v ? 1 : 0;
-        return f0 + before;
+        // the last of them that begins at or before v
+        int f = f0;
+        for (uint64_t b = m; b; b &= b - 1) {  // wave-uniform
+            const int k = __builtin_ctzll(b);
+            f = __shfl(next, k, 64) <= v ? f0 + 1 + k : f;
+        }
+        return f;
     }
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -152,7 +160,7 @@ __device__ __forceinline__ int lane_search(int n, int64_t v, Key key) {
 // wave takes part.
 __device__ __forceinline__ int frame_of_point(const ClusterArgs &a, int64_t i) {
     const int32_t *offsets = a.offsets;
-    const int f = lane_search(a.n_frames, i, [offsets](int k) { return (int64_t)offsets[k]; });
+    const int f = lane_search(a.n_frames, i, [offsets](int k) { return (int64_t)(uint32_t)offsets[k]; });
     return (i < a.total && i >= offsets[f] && i < offsets[f + 1]) ? f : -1;
 }
 
@@ -327,7 +335,8 @@ __global__ __launch_bounds__(kBlock) void big_hist(ClusterArgs a, BigWs w) {
 // Exclusive scan of a frame's cell counts, in tiles of kScanThreads *
 // kScanUnroll cells: coalesced loads into LDS, kScanUnroll consecutive cells
 // per thread, a workgroup scan plus the carry of the earlier tiles, coalesced
-// stores.
+// stores.  A frame whose points were not all found (see the searches above:
+// its sorted positions would not all be filled) is inconsistent from here on.
 __global__ __launch_bounds__(kScanThreads) void big_scan(ClusterArgs a, BigWs w) {
     constexpr int kTileCells = kScanThreads * kScanUnroll;
     // cell c of a tile sits at (c / 32) * 33 + c % 32: both the coalesced
@@ -375,7 +384,13 @@ __global__ __launch_bounds__(kScanThreads) void big_scan(ClusterArgs a, BigWs w)
         carry = s_carry;
         __syncthreads();  // s_tile and s_carry are rewritten by the next tile
     }
-    if (tid == 0) cs[ncell] = carry;
+    if (tid == 0) {
+        cs[ncell] = carry;
+        if (carry != a.offsets[f + 1] - a.offsets[f]) {
+            w.rec[(size_t)f * kRec + kBig] = 0;
+            if (a.n_clusters) a.n_clusters[f] = -1;
+        }
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void big_scatter(ClusterArgs a, BigWs w) {
@@ -595,7 +610,8 @@ __global__ __launch_bounds__(kTileThreads) void big_union_tiles(ClusterArgs a, B
     const BigGrid g = load_grid(rec);
     const int32_t b = a.offsets[f];
     const int64_t s0 = tile_slot(a.offsets, f), nslots = tile_slot(a.offsets, f + 1) - s0;
-    if (wg >= s0 + nslots || !g.dense) return;  // past the last frame's slots; coarsened grids: far launch
+    // outside the frame's slots (past the last frame's); coarsened grids: far launch
+    if (wg < s0 || wg >= s0 + nslots || !g.dense) return;
     if (tid == 0) s_hook[0] = 0;
     const int64_t base = cell_base(a.offsets, f);
     const int32_t *cs = w.cstart + base;
@@ -706,8 +722,8 @@ __global__ __launch_bounds__(kBlock) void big_union_far(ClusterArgs a, BigWs w, 
     if (!rec[kBig] || !rec[kDense]) return;
     const BigGrid g = load_grid(rec);
     const int64_t base = cell_base(a.offsets, f);
+    if (c < base || c - base >= g.ncell) return;
     const int32_t ca = (int32_t)(c - base);
-    if (ca >= g.ncell) return;
     int odx, ody;
     if (!far_offset(g, k, &odx, &ody)) return;
     const int32_t ay = ca / g.ncx, ax = ca - ay * g.ncx;

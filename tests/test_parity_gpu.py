@@ -311,6 +311,25 @@ def test_bad_offsets_do_not_fault_gpu():
     assert ncl[0] == 1
 
 
+@pytest.mark.parametrize("bad", [10 ** 9, -7])
+def test_bad_offset_among_large_frames_gpu(bad):
+    """One corrupt offset in a batch of frames above the on-chip capacity: the
+    two frames it belongs to are left alone with n_clusters -1, the others
+    (whose starts fall inside waves of points) are clustered whole."""
+    rng = np.random.default_rng(8)
+    n = 10999
+    xy, off = wl.pack([np.stack([rng.integers(0, 16 * 3840, n), rng.integers(0, 16 * 2160, n)], 1).astype(np.int32)
+                       for _ in range(5)])
+    good = off.copy()
+    off[2] = bad
+    labels, kind, ncl = run_cluster(xy, off, 400, 6, max_fp=0)
+    rl, rk, rn = oracle.cluster_frames(xy, good, 400, 6)
+    assert ncl[1] == -1 and ncl[2] == -1
+    for f in (0, 3, 4):
+        b, e = good[f], good[f + 1]
+        assert np.array_equal(labels[b:e], rl[b:e]) and np.array_equal(kind[b:e], rk[b:e]) and ncl[f] == rn[f]
+
+
 def test_validate_mode_rejects_bad_offsets_gpu():
     xy = np.zeros((10, 2), np.int32)
     off = np.array([0, 5, 3, 10], np.int32)
