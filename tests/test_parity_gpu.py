@@ -330,6 +330,22 @@ def test_bad_offset_among_large_frames_gpu(bad):
         assert np.array_equal(labels[b:e], rl[b:e]) and np.array_equal(kind[b:e], rk[b:e]) and ncl[f] == rn[f]
 
 
+@pytest.mark.parametrize("where", ["first", "middle", "last"])
+@pytest.mark.parametrize("small", [300, 5000])
+def test_large_frames_among_many_small_gpu(small, where):
+    """Frames above the on-chip capacity between hundreds and thousands of
+    frames of 0 to 2 birds: searches over more than 64 and more than 4096
+    frames, and waves that span more than 64 frame starts."""
+    rng = np.random.default_rng(small)
+    one = lambda n: np.stack([rng.integers(0, 16 * 3840, n), rng.integers(0, 16 * 2160, n)], 1).astype(np.int32)  # noqa: E731
+    batch = [one(rng.integers(0, 3)) for _ in range(small)]
+    at = {"first": 0, "middle": small // 2, "last": small}[where]
+    batch[at:at] = [one(11003), one(2), one(10501)]
+    xy, off = wl.pack(batch)
+    got = run_cluster(xy, off, 400, 6, max_fp=0)
+    assert_cluster_equal(got, xy, off, 400, 6, tag=f"{small} {where}")
+
+
 def test_validate_mode_rejects_bad_offsets_gpu():
     xy = np.zeros((10, 2), np.int32)
     off = np.array([0, 5, 3, 10], np.int32)
