@@ -106,6 +106,7 @@ struct GatherAxis {
     int32_t nc;     // chunks of a window: 2 j4 + 1
     int32_t tab;    // byte offset of the table (its leading zero chunk) in LDS
     float h, inv_h; // cell size, px (direct path)
+    float reach;    // window half-width, quanta, whatever j's limit (direct path)
 };
 
 struct GatherGeom {
@@ -234,11 +235,11 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
     // are the same in px, a quantum wider for their rounding and clamped
     auto low = [](const GatherAxis &t, int first) {
         if (!DIRECT) return (first - t.j) * t.c;
-        return (int32_t)fminf(fmaxf((float)(first - t.j) * t.h * 16.0f - 1.0f, -33554432.0f), 33554432.0f);
+        return (int32_t)fminf(fmaxf((float)first * t.h * 16.0f - t.reach - 1.0f, -33554432.0f), 33554432.0f);
     };
     auto span = [](const GatherAxis &t, int rows, int first, int32_t lo) {
         if (!DIRECT) return (uint32_t)(rows + 2 * t.j) * (uint32_t)t.c;
-        const float end = (float)(first + rows + t.j) * t.h * 16.0f + 2.0f;
+        const float end = (float)(first + rows) * t.h * 16.0f + t.reach + 2.0f;
         return (uint32_t)((int32_t)fminf(fmaxf(end, -33554432.0f), 33554432.0f) - lo);
     };
 
@@ -518,12 +519,16 @@ void gather_lds(GatherGeom *gg) {
 }
 
 // Window of an axis of n cells over `extent` px: every cell centre within the
-// cut of a bird lies at most j cells from the bird's own.
+// cut of a bird lies at most j cells from the bird's own.  j is limited to
+// twice the widest grid: a window that wide holds any region whole, and only
+// `reach`, which has no limit, says how far off its birds may lie.
 void gather_window(GatherAxis *t, int extent, int n, double sigma) {
     const double h = (double)extent / n;
     t->h = (float)h;
     t->inv_h = (float)(1.0 / h);
-    t->j = (int32_t)std::min(std::ceil((double)kCutSigmas * sigma / h) + 1.0, 8192.0);
+    const double j = std::ceil((double)kCutSigmas * sigma / h) + 1.0;
+    t->j = (int32_t)std::min(j, 8192.0);
+    t->reach = (float)std::min(16.0 * j * h, 1.0e9);
     t->j4 = (t->j + 3) / 4;
     t->nc = 2 * t->j4 + 1;
 }

@@ -469,6 +469,23 @@ def test_density_window_edges_gpu(w, h, gx, gy, sigma, frames, n):
     assert_density_close(got, ref, np.diff(off), sigma, tag=f"{gx}x{gy} sigma {sigma}")
 
 
+@pytest.mark.parametrize("w,gx,sigma,x_px", [
+    (1920, 4096, 2000.0, 6000),    # 6 sigma is 25600 cells, the birds 8700 cells right of the frame
+    (100, 97, 1.0e5, 150000),      # 582000 cells
+    (1920, 4096, 1000.0, 5770),    # 12800 cells, the birds 8213 cells off
+])
+def test_density_far_outside_birds_gpu(w, gx, sigma, x_px):
+    """Birds outside the frame by more cells than any grid has, whose windows
+    still reach it."""
+    rng = np.random.default_rng(3)
+    n = 70
+    xy, off = wl.pack([np.stack([16 * x_px + rng.integers(0, 16, n), rng.integers(0, 16 * 64, n)], 1).astype(np.int32)])
+    got = run_density(xy, off, w, 64, gx, 7, sigma)
+    ref = oracle.density_frames(xy, off, w, 64, gx, 7, sigma)
+    assert ref.max() > 0
+    assert_density_close(got, ref, np.diff(off), sigma, tag=f"{gx} cells sigma {sigma}")
+
+
 @pytest.mark.parametrize("split", ["3", "16"])
 def test_density_bird_slices_gpu(split, monkeypatch):
     """Frames split into bird slices whose partial grids are added afterwards,
