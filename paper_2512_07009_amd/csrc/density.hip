@@ -357,7 +357,8 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
                 const GBird e = ring[(head + (lane & 31)) & (kGRing - 1)];
                 const int32_t q = isx ? e.rb_x : e.rb_y;
                 const float h = isx ? gg.ax.h : gg.ay.h;
-                const float pos = q == kGNone ? 1.0e15f : (float)q * 0.0625f;  // far off: every factor 0
+                // a padding bird's factors are 0 whatever sigma and the distance
+                const float pos = q == kGNone ? 0.0f : (float)q * 0.0625f, lift = q == kGNone ? -1.0e30f : 8.0f;
                 int first = isx ? col0 >> 2 : row0 >> 2;  // the row's first chunk, in chunks of the grid
                 if (!(isx ? whole_x : whole_y))
                     first = ((int)floorf(pos * (isx ? gg.ax.inv_h : gg.ay.inv_h)) >> 2) - (isx ? gg.ax.j4 : gg.ay.j4);
@@ -369,7 +370,7 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const float d = fmaf(cell + (float)i, h, -pos);
-                        f[i] = (_Float16)__builtin_amdgcn_exp2f(fmaf(d * d, gg.neg_k, 8.0f));  // 2^8 = kLift
+                        f[i] = (_Float16)__builtin_amdgcn_exp2f(fmaf(d * d, gg.neg_k, lift));  // 2^8 = kLift
                     }
                     *reinterpret_cast<half4 *>(row + 8 * k) = f;
                 }

@@ -486,6 +486,16 @@ def test_density_far_outside_birds_gpu(w, gx, sigma, x_px):
     assert_density_close(got, ref, np.diff(off), sigma, tag=f"{gx} cells sigma {sigma}")
 
 
+@pytest.mark.parametrize("sigma", [1.0e13, 3.0e14, 1.0e15, 1.0e18])
+def test_density_huge_sigma_gpu(sigma):
+    """Bandwidths beside which every distance vanishes: the grid is the number
+    of birds times 1 / (2 pi sigma^2), whatever fills the last step."""
+    xy, off = wl.pack([np.full((n, 2), 16 * 40, np.int32) for n in (1, 5, 33, 0, 64)])
+    got = run_density(xy, off, 1000, 700, 77, 53, sigma)
+    ref = oracle.density_frames(xy, off, 1000, 700, 77, 53, sigma)
+    assert_density_close(got, ref, tag=f"sigma {sigma}")
+
+
 @pytest.mark.parametrize("split", ["3", "16"])
 def test_density_bird_slices_gpu(split, monkeypatch):
     """Frames split into bird slices whose partial grids are added afterwards,
