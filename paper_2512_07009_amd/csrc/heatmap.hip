@@ -430,6 +430,11 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// Waits for this wave's memory operations: its stores and atomics have then
+// reached the L2, where the workgroup's later atomics and uncached loads meet
+// them.
+__device__ __forceinline__ void wait_memory() { __builtin_amdgcn_s_waitcnt(0); }
+
 // A value equal in every lane, as a scalar.
 __device__ __forceinline__ uint64_t uniform(uint64_t v) {
     return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
@@ -476,7 +481,11 @@ __host__ __device__ inline FrameLds frame_lds(int gw, int gh) {
 //      fixed-point masses by one prefix sum, each added to its component's
 //      slot;
 //   E. the slots' totals go to their label cells.
-// More components than slots repeat D's sums for the next slots.
+// Components beyond the slots add their runs to their label cells' outputs by
+// global atomics, on outputs zeroed beforehand, and E converts those masses:
+// 256 noisy frames of 256 x 144 cells with 2400 components each take 115 us,
+// 254 when D ran again for every further 281 components, 187 when D left only
+// the label cells out of its zeros.
 //
 // Bound by latency: the chain of phases on one compute unit per frame.
 // 64 frames of 128 x 72 cells 23.8 us, 256 of 256 x 144 64, 1800 of 128 x 72
@@ -623,88 +632,104 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int s
     };
     run_firsts([&](int c) { st_rlx<kGroup>(P + c, uf_root<kGroup>(P, c)); });
     __syncthreads();
+    unsigned long long *CMu = reinterpret_cast<unsigned long long *>(CM);
     run_firsts([&](int c) {
         if (P[c] == c) P[c] = -2 - atomicAdd(&s_ncomp, 1);
     });
     __syncthreads();
-    // D, E
-    const int sh = s_shift, ncomp = s_ncomp;
-    for (int base = 0; base == 0 || base < ncomp; base += slots) {
-        const int here = min(slots, ncomp - base);
-        for (int t = tid; t < here; t += kFThreads) {
-            mass[t] = 0ull;
-            count[t] = 0;
+    // D
+    const int sh = s_shift, ncomp = s_ncomp, here = min(slots, ncomp);
+    const bool over = ncomp > slots;
+    if (over) {  // the outputs' zeros first, in full lines: atomics follow
+        for (int c = tid; c < cells; c += kFThreads) {
+            CC[c] = 0;
+            CMu[c] = 0ull;
+        }
+        wait_memory();
+    }
+    for (int t = tid; t < here; t += kFThreads) {
+        mass[t] = 0ull;
+        count[t] = 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kFlight; ++u) v[u] = load(min(wave + kFWaves * u, l.words));
+    __syncthreads();
+    for (int w0 = wave; w0 < l.words; w0 += kFWaves * kFlight) {
+        int32_t root[kFlight], p[kFlight];
+        uint64_t m[kFlight], r0[kFlight];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {  // words past the end are not beyond the zero words when clamped
+            const int w = min(w0 + kFWaves * u, l.words);
+            m[u] = hotw[w];
+            r0[u] = row0w[w];
         }
 #pragma unroll
-        for (int u = 0; u < kFlight; ++u) v[u] = load(min(wave + kFWaves * u, l.words));
-        __syncthreads();
-        for (int w0 = wave; w0 < l.words; w0 += kFWaves * kFlight) {
-            int32_t root[kFlight], p[kFlight];
-            uint64_t m[kFlight], r0[kFlight];
+        for (int u = 0; u < kFlight; ++u) {
+            m[u] = uniform(m[u]);
+            root[u] = __builtin_amdgcn_inverse_ballot_w64(m[u]) ? 64 * (w0 + kFWaves * u) + lane : -1;
+        }
 #pragma unroll
-            for (int u = 0; u < kFlight; ++u) {  // words past the end are not beyond the zero words when clamped
-                const int w = min(w0 + kFWaves * u, l.words);
-                m[u] = hotw[w];
-                r0[u] = row0w[w];
-            }
+        for (int u = 0; u < kFlight; ++u) p[u] = P[max(root[u], 0)];
+        // the words' walks in step (p < 0: at the root, or a cold cell);
+        // after C two steps reach every root
+        for (;;) {
+            bool any = false;
 #pragma unroll
             for (int u = 0; u < kFlight; ++u) {
-                m[u] = uniform(m[u]);
-                root[u] = __builtin_amdgcn_inverse_ballot_w64(m[u]) ? 64 * (w0 + kFWaves * u) + lane : -1;
+                const bool on = (root[u] >= 0) & (p[u] >= 0);
+                root[u] = on ? p[u] : root[u];
+                any |= on;
             }
+            if (!__any(any)) break;
 #pragma unroll
             for (int u = 0; u < kFlight; ++u) p[u] = P[max(root[u], 0)];
-            // the words' walks in step (p < 0: at the root, or a cold cell);
-            // after C two steps reach every root
-            for (;;) {
-                bool any = false;
+        }
 #pragma unroll
-                for (int u = 0; u < kFlight; ++u) {
-                    const bool on = (root[u] >= 0) & (p[u] >= 0);
-                    root[u] = on ? p[u] : root[u];
-                    any |= on;
+        for (int u = 0; u < kFlight; ++u) {
+            const int w = w0 + kFWaves * u, c = 64 * w + lane;
+            if (c < cells) {
+                L[c] = root[u];
+                if (!over && root[u] != c) {  // a label cell's outputs come from its component's sums
+                    CC[c] = 0;
+                    CM[c] = 0.0;
                 }
-                if (!__any(any)) break;
-#pragma unroll
-                for (int u = 0; u < kFlight; ++u) p[u] = P[max(root[u], 0)];
             }
-#pragma unroll
-            for (int u = 0; u < kFlight; ++u) {
-                const int w = w0 + kFWaves * u, c = 64 * w + lane;
-                if (c < cells && base == 0) {
-                    L[c] = root[u];
-                    if (root[u] != c) {  // a label cell's outputs come from its slot
-                        CC[c] = 0;
-                        CM[c] = 0.0;
-                    }
-                }
-                const float d = v[u];
-                v[u] = load(min(w + kFWaves * kFlight, l.words));
-                if (m[u] == 0ull) continue;  // wave-uniform
-                const int slot = root[u] >= 0 ? -2 - p[u] - base : -1;
-                const unsigned long long q = root[u] >= 0 ? (unsigned long long)llrint(ldexp((double)d, sh)) : 0ull;
-                const unsigned long long incl = wave_incl_scan_u64(q);
-                // a run's first lane takes its sum: up to its last lane, less what lies before it
-                const uint64_t firsts = m[u] & ~((m[u] << 1) & ~uniform(r0[u]));
-                const uint64_t lasts = m[u] & (~(m[u] >> 1) | (firsts >> 1) | (1ull << 63));
-                const uint64_t after = lasts >> lane;
-                const int end = after ? lane + __builtin_ctzll(after) : lane;
-                const unsigned long long at_end = __shfl(incl, end, 64);
-                if (__builtin_amdgcn_inverse_ballot_w64(firsts) && slot >= 0 && slot < here) {
+            const float d = v[u];
+            v[u] = load(min(w + kFWaves * kFlight, l.words));
+            if (m[u] == 0ull) continue;  // wave-uniform
+            const unsigned long long q = root[u] >= 0 ? (unsigned long long)llrint(ldexp((double)d, sh)) : 0ull;
+            const unsigned long long incl = wave_incl_scan_u64(q);
+            // a run's first lane takes its sum: up to its last lane, less what lies before it
+            const uint64_t firsts = m[u] & ~((m[u] << 1) & ~uniform(r0[u]));
+            const uint64_t lasts = m[u] & (~(m[u] >> 1) | (firsts >> 1) | (1ull << 63));
+            const uint64_t after = lasts >> lane;
+            const int end = after ? lane + __builtin_ctzll(after) : lane;
+            const unsigned long long at_end = __shfl(incl, end, 64);
+            if (__builtin_amdgcn_inverse_ballot_w64(firsts)) {
+                const int slot = -2 - p[u];
+                if (slot < slots) {
                     atomicAdd(count + slot, end - lane + 1);
                     atomicAdd(mass + slot, at_end - (incl - q));
                     if (root[u] == c) label[slot] = c;
+                } else {
+                    atomicAdd(CC + root[u], end - lane + 1);
+                    atomicAdd(CMu + root[u], at_end - (incl - q));
                 }
             }
         }
-        __syncthreads();
-        for (int t = tid; t < here; t += kFThreads) {
-            const int32_t c = label[t];
-            CC[c] = count[t];
-            CM[c] = ldexp((double)mass[t], -sh) * a.cell_area;
-        }
-        __syncthreads();  // the next slots' zeros
     }
+    wait_memory();
+    __syncthreads();
+    // E
+    for (int t = tid; t < here; t += kFThreads) {
+        const int32_t c = label[t];
+        CC[c] = count[t];
+        CM[c] = ldexp((double)mass[t], -sh) * a.cell_area;
+    }
+    if (over)
+        for (int c = tid; c < cells; c += kFThreads)
+            if (P[c] <= -2 - slots)
+                CM[c] = ldexp((double)__hip_atomic_load(CMu + c, __ATOMIC_RELAXED, kAgent), -sh) * a.cell_area;
     if (tid == 0) a.n_components[f] = ncomp;
 }
 

@@ -111,6 +111,18 @@ def test_word_edges_gpu(F, h, w, conn):
     check(np.broadcast_to(dots, (F, h, w)).copy(), 1.5, 0.5, conn, tag=f"{F}x{h}x{w} dots")
 
 
+@pytest.mark.parametrize("conn", [4, 8])
+@pytest.mark.parametrize("F,h,w", [(3, 144, 256), (2, 128, 288)])
+def test_more_components_than_slots_gpu(F, h, w, conn):
+    """Grids whose LDS leaves few component slots (281 and 285): noisy maps of
+    hundreds to thousands of components, some of them large."""
+    rng = np.random.default_rng(h + conn)
+    g = (rng.random((F, h, w)) * 1e-3).astype(np.float32)
+    g[0] *= 0.2 + np.hypot(*np.meshgrid(np.linspace(-1, 1, w), np.linspace(-1, 1, h)))
+    for q in (0.45, 0.6, 0.9, 0.98):
+        check(g, 2.0, float(np.quantile(g, q)), conn, tag=f"{F}x{h}x{w} q{q}")
+
+
 def test_deterministic_gpu(path):
     g = wl.heat_grids(7, 6, 90, 140)
     thr = float(np.quantile(g[g > 0], 0.6))
