@@ -14,8 +14,8 @@
 //                of the positive cells (0 when S = 0);
 //   degree       (sum of density over hot cells) / S (0 when S = 0).
 //
-// Design.  Grids whose int32 forest fits in LDS with the kernel's bit words
-// and component slots (grid_w * grid_h <= about 38k cells) take
+// Design.  Grids whose int32 forest fits in LDS beside the component slots
+// (grid_w * grid_h <= 39,936 cells with 160 KiB; see plan_heatmap) take
 // heat_frame_kernel, one workgroup per frame (described there).  Larger grids
 // take four tiled kernels:
 //   1. heat_tile_kernel, one 256-thread workgroup per 32 x 32 tile: loads the
@@ -37,6 +37,7 @@
 //      cell_area * sum.
 // Every output is a deterministic function of the input.
 
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <type_traits>
@@ -444,8 +445,9 @@ __device__ __forceinline__ uint64_t uniform(uint64_t v) {
 // LDS of one frame: the forest (an int32 per cell), two bits per cell in words
 // of 64 consecutive cells (hot; first of its row; zero words past the end, as
 // many as a read one row down needs), and the component slots, as many as are
-// left, at most kMaxSlots.
-constexpr int kMaxSlots = 2048, kMinSlots = 256;
+// left, at most kMaxSlots.  Where fewer than kMinSlots would be (`spill`) the
+// words wait in the frame's part of comp_mass instead, up to phase D.
+constexpr int kMaxSlots = 2048, kMinSlots = 256, kMinSpillSlots = 96;
 constexpr size_t kFrameStaticLds = 2560;  // at least the kernel's static shared variables
 struct FrameLds {
     int words, padded;
@@ -453,13 +455,13 @@ struct FrameLds {
     __host__ __device__ size_t bytes(int slots) const { return slot + (size_t)slots * 16; }
 };
 
-__host__ __device__ inline FrameLds frame_lds(int gw, int gh) {
+__host__ __device__ inline FrameLds frame_lds(int gw, int gh, bool spill) {
     FrameLds l;
     l.words = (gw * gh + 63) / 64;
     l.padded = l.words + gw / 64 + 3;
     l.hot = ((size_t)gw * gh * sizeof(int32_t) + 15) / 16 * 16;
     l.row0 = l.hot + (size_t)l.padded * 8;
-    l.slot = (l.row0 + (size_t)l.padded * 8 + 15) / 16 * 16;
+    l.slot = spill ? l.hot : (l.row0 + (size_t)l.padded * 8 + 15) / 16 * 16;
     return l;
 }
 
@@ -492,7 +494,7 @@ __host__ __device__ inline FrameLds frame_lds(int gw, int gh) {
 // 115 (33.2, 124 and 161 when the logarithm table was computed by every
 // workgroup, loads came one at a time, every cell tested its own joins, masses
 // were added by global atomics and a second kernel converted them).
-template <int kFThreads>
+template <int kFThreads, bool SPILL>
 __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int slots) {
     constexpr int kFWaves = kFThreads / 64;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -505,15 +507,23 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int s
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int gw = a.grid_w, gh = a.grid_h;
     const int cells = gw * gh;
-    const FrameLds l = frame_lds(gw, gh);
+    const FrameLds l = frame_lds(gw, gh, SPILL);
     int32_t *P = reinterpret_cast<int32_t *>(smem);
-    uint64_t *hotw = reinterpret_cast<uint64_t *>(smem + l.hot), *row0w = reinterpret_cast<uint64_t *>(smem + l.row0);
     unsigned long long *mass = reinterpret_cast<unsigned long long *>(smem + l.slot);
     int32_t *count = reinterpret_cast<int32_t *>(mass + slots), *label = count + slots;
     const float *D = a.density + (size_t)f * cells;
     int32_t *L = a.labels + (size_t)f * cells;
     int32_t *CC = a.comp_cells + (size_t)f * cells;
     double *CM = a.comp_mass + (size_t)f * cells;
+    unsigned long long *CMu = reinterpret_cast<unsigned long long *>(CM);
+    uint64_t *hotw, *row0w;
+    if constexpr (SPILL) {
+        hotw = reinterpret_cast<uint64_t *>(CM);  // 2 padded words: at most cells / 16
+        row0w = hotw + l.padded;
+    } else {
+        hotw = reinterpret_cast<uint64_t *>(smem + l.hot);
+        row0w = reinterpret_cast<uint64_t *>(smem + l.row0);
+    }
     auto load = [&](int word) { return D[min(64 * word + lane, cells - 1)]; };  // past the end: not used
 
     // A
@@ -565,6 +575,7 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int s
         s_red[2][wave] = hs;
         s_max[wave] = mb;
     }
+    if constexpr (SPILL) wait_memory();
     __syncthreads();
     // B (the queue is in the slots' space; pairs beyond it are joined in place)
     int2 *queue = reinterpret_cast<int2 *>(smem + l.slot);
@@ -632,7 +643,6 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int s
     };
     run_firsts([&](int c) { st_rlx<kGroup>(P + c, uf_root<kGroup>(P, c)); });
     __syncthreads();
-    unsigned long long *CMu = reinterpret_cast<unsigned long long *>(CM);
     run_firsts([&](int c) {
         if (P[c] == c) P[c] = -2 - atomicAdd(&s_ncomp, 1);
     });
@@ -654,22 +664,36 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int s
 #pragma unroll
     for (int u = 0; u < kFlight; ++u) v[u] = load(min(wave + kFWaves * u, l.words));
     __syncthreads();
+    x = (64 * wave + lane) % gw;
     for (int w0 = wave; w0 < l.words; w0 += kFWaves * kFlight) {
         int32_t root[kFlight], p[kFlight];
         uint64_t m[kFlight], r0[kFlight];
+        if constexpr (SPILL) {  // the words' place may hold outputs by now: the bits again, from the forest
 #pragma unroll
-        for (int u = 0; u < kFlight; ++u) {  // words past the end are not beyond the zero words when clamped
-            const int w = min(w0 + kFWaves * u, l.words);
-            m[u] = hotw[w];
-            r0[u] = row0w[w];
+            for (int u = 0; u < kFlight; ++u) {
+                const int c = 64 * (w0 + kFWaves * u) + lane;
+                p[u] = P[min(c, cells - 1)];
+                root[u] = (c < cells) & (p[u] != -1) ? c : -1;
+                m[u] = __ballot(root[u] >= 0);
+                r0[u] = __ballot((c < cells) & (x == 0));
+                x += xstep;
+                x -= x >= gw ? gw : 0;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {  // words past the end are not beyond the zero words when clamped
+                const int w = min(w0 + kFWaves * u, l.words);
+                m[u] = hotw[w];
+                r0[u] = row0w[w];
+            }
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {
+                m[u] = uniform(m[u]);
+                root[u] = __builtin_amdgcn_inverse_ballot_w64(m[u]) ? 64 * (w0 + kFWaves * u) + lane : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) p[u] = P[max(root[u], 0)];
         }
-#pragma unroll
-        for (int u = 0; u < kFlight; ++u) {
-            m[u] = uniform(m[u]);
-            root[u] = __builtin_amdgcn_inverse_ballot_w64(m[u]) ? 64 * (w0 + kFWaves * u) + lane : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < kFlight; ++u) p[u] = P[max(root[u], 0)];
         // the words' walks in step (p < 0: at the root, or a cold cell);
         // after C two steps reach every root
         for (;;) {
@@ -742,29 +766,40 @@ size_t heatmap_workspace_bytes(int32_t n_frames, int32_t grid_w, int32_t grid_h)
     return parts + (((size_t)n_frames * sizeof(int32_t) + 255) & ~(size_t)255);
 }
 
-// Component slots of the frame-resident kernel in `lds_limit` bytes of LDS (0:
-// the grid does not fit).
-int heatmap_frame_slots(int32_t grid_w, int32_t grid_h, size_t lds_limit) {
-    const size_t used = frame_lds(grid_w, grid_h).bytes(0) + kFrameStaticLds;
-    if (used + kMinSlots * 16 > lds_limit) return 0;
-    const size_t slots = (lds_limit - used) / 16;
-    return (int)(slots < (size_t)kMaxSlots ? slots : (size_t)kMaxSlots);
+// The frame-resident kernel's plan in `lds_limit` bytes of LDS, or no slots:
+// the tiled kernels, for grids that do not fit, and for a few frames of those
+// whose bit words do not, where the chip is left to a few workgroups: 240 x 160
+// cells, 8 frames: 26 us tiled and 57 here on smooth maps, 66 .. 88 and 84 ..
+// 107 on noisy ones; 16 frames: 30 and 57, 89 .. 147 and 84 .. 108; 128: 75
+// and 60, 238 .. 405 and 88 .. 146.
+constexpr int kSpillTiledFrames = 8;
+
+HeatPlan plan_heatmap(int32_t n_frames, int32_t grid_w, int32_t grid_h, size_t lds_limit) {
+    for (const bool spill : {false, true}) {
+        if (spill && n_frames <= kSpillTiledFrames) break;
+        const size_t used = frame_lds(grid_w, grid_h, spill).bytes(0) + kFrameStaticLds;
+        if (used + (spill ? kMinSpillSlots : kMinSlots) * 16 > lds_limit) continue;
+        return {(int)std::min<size_t>((lds_limit - used) / 16, kMaxSlots), spill};
+    }
+    return {0, false};
 }
 
-hipError_t launch_heatmap(HeatArgs a, void *workspace, int frame_slots, int n_cus, hipStream_t stream) {
-    if (frame_slots > 0) {
-        const size_t lds = frame_lds(a.grid_w, a.grid_h).bytes(frame_slots);
+hipError_t launch_heatmap(HeatArgs a, void *workspace, const HeatPlan &plan, int n_cus, hipStream_t stream) {
+    if (plan.slots > 0) {
+        const size_t lds = frame_lds(a.grid_w, a.grid_h, plan.spill).bytes(plan.slots);
+        const dim3 grid((unsigned)a.n_frames);
         // more frames than compute units: 512-thread workgroups, where several
         // share a compute unit, wait less at each barrier and keep it busy
         // (1800 x 128 x 72: 115 us against 159 with 1024 threads, 512 x 64 x
         // 36: 18.5 against 27.7); with at most one frame per compute unit, or
         // half its LDS per frame, a frame takes 1024 (64 x 128 x 72: 23.8
         // against 26.3; 256 x 256 x 144: 64 against 71)
-        if (a.n_frames > n_cus && 2 * (lds + kFrameStaticLds) <= 160 * 1024)
-            hipLaunchKernelGGL(heat_frame_kernel<512>, dim3((unsigned)a.n_frames), dim3(512), lds, stream, a, frame_slots);
+        if (plan.spill)
+            hipLaunchKernelGGL((heat_frame_kernel<1024, true>), grid, dim3(1024), lds, stream, a, plan.slots);
+        else if (a.n_frames > n_cus && 2 * (lds + kFrameStaticLds) <= 160 * 1024)
+            hipLaunchKernelGGL((heat_frame_kernel<512, false>), grid, dim3(512), lds, stream, a, plan.slots);
         else
-            hipLaunchKernelGGL(heat_frame_kernel<1024>, dim3((unsigned)a.n_frames), dim3(1024), lds, stream, a,
-                               frame_slots);
+            hipLaunchKernelGGL((heat_frame_kernel<1024, false>), grid, dim3(1024), lds, stream, a, plan.slots);
         return hipGetLastError();
     }
     a.tiles_x = (a.grid_w + kHT - 1) / kHT;

@@ -113,12 +113,14 @@ struct HeatArgs {
 };
 
 size_t heatmap_workspace_bytes(int32_t n_frames, int32_t grid_w, int32_t grid_h);
-// Component slots the frame-resident kernel (one workgroup per frame) gets in
-// lds_limit bytes of LDS; 0 when the grid does not fit.
-int heatmap_frame_slots(int32_t grid_w, int32_t grid_h, size_t lds_limit);
-// frame_slots > 0: the frame-resident kernel, which needs no workspace; else
-// the tiled kernels, which use it.
-hipError_t launch_heatmap(HeatArgs a, void *workspace, int frame_slots, int n_cus, hipStream_t stream);
+// Launch plan: component slots of the frame-resident kernel (one workgroup per
+// frame, no workspace), 0 for the tiled kernels, which use the workspace.
+struct HeatPlan {
+    int slots;
+    bool spill;  // the frame's bit words wait in comp_mass
+};
+HeatPlan plan_heatmap(int32_t n_frames, int32_t grid_w, int32_t grid_h, size_t lds_limit);
+hipError_t launch_heatmap(HeatArgs a, void *workspace, const HeatPlan &plan, int n_cus, hipStream_t stream);
 
 // ----------------------------------------------------------------------------
 // Region of interest

@@ -99,8 +99,8 @@ def test_workload_grid_shapes_gpu(name):
 @pytest.mark.parametrize("F,h,w", [(2, 300, 17), (2, 40, 63), (2, 23, 64), (2, 31, 65), (1, 65, 1), (1, 1, 200),
                                    (300, 9, 13), (1, 140, 270), (1, 138, 276)])
 def test_word_edges_gpu(F, h, w, conn):
-    """Rows that end inside, at and just past the 64-cell words, grids at both
-    sides of the frame kernel's LDS limit, and more frames than compute units;
+    """Rows that end inside, at and just past the 64-cell words, grids whose
+    words of bits do not fit in LDS, and more frames than compute units;
     checkerboards for more components than the kernel has slots."""
     rng = np.random.default_rng(h * 1000 + w)
     g = (rng.random((F, h, w)) * 1e-3).astype(np.float32)
@@ -120,6 +120,20 @@ def test_more_components_than_slots_gpu(F, h, w, conn):
     g = (rng.random((F, h, w)) * 1e-3).astype(np.float32)
     g[0] *= 0.2 + np.hypot(*np.meshgrid(np.linspace(-1, 1, w), np.linspace(-1, 1, h)))
     for q in (0.45, 0.6, 0.9, 0.98):
+        check(g, 2.0, float(np.quantile(g, q)), conn, tag=f"{F}x{h}x{w} q{q}")
+
+
+@pytest.mark.parametrize("conn", [4, 8])
+@pytest.mark.parametrize("F,h,w", [(2, 366, 101), (9, 163, 227), (9, 303, 122), (300, 192, 208), (9, 9, 4096), (2, 9, 4096),
+                                   (9, 235, 170)])
+def test_frame_kernel_limits_gpu(F, h, w, conn):
+    """The largest grid whose bit words fit in LDS beside 256 slots (366 x
+    101), grids whose words do not (few frames of them take the tiled kernels),
+    the largest of the frame kernel (192 x 208, 96 slots) and one beyond it."""
+    rng = np.random.default_rng(h + w)
+    g = (rng.random((F, h, w)) * 1e-3).astype(np.float32)
+    g[0] *= 0.2 + np.hypot(*np.meshgrid(np.linspace(-1, 1, w), np.linspace(-1, 1, h)))
+    for q in (0.5, 0.9):
         check(g, 2.0, float(np.quantile(g, q)), conn, tag=f"{F}x{h}x{w} q{q}")
 
 
