@@ -566,10 +566,10 @@ namespace {
 
 // One workgroup per frame where the grid's forest fits in LDS, else the tiled
 // kernels (FLOCK_HEATMAP_PATH=tiled takes them for every grid).
-flock::HeatPlan heatmap_plan(int32_t n_frames, int32_t grid_w, int32_t grid_h, const DeviceInfo &dev) {
+flock::HeatPlan heatmap_plan(int32_t grid_w, int32_t grid_h, const DeviceInfo &dev) {
     const char *hp = std::getenv("FLOCK_HEATMAP_PATH");
     if (hp && std::strcmp(hp, "tiled") == 0) return {0, false};
-    return flock::plan_heatmap(n_frames, grid_w, grid_h, dev.lds_per_block);
+    return flock::plan_heatmap(grid_w, grid_h, dev.lds_per_block);
 }
 
 }  // namespace
@@ -580,7 +580,7 @@ size_t heatmap_frames_workspace(int32_t n_frames, int32_t grid_w, int32_t grid_h
     const DeviceInfo *dev = nullptr;
     const bool known = device_info(&dev) == FLOCK_OK;
     g_error[0] = '\0';
-    if (grid_w < 1 || grid_h < 1 || (known && heatmap_plan(n_frames, grid_w, grid_h, *dev).slots > 0)) return 0;
+    if (grid_w < 1 || grid_h < 1 || (known && heatmap_plan(grid_w, grid_h, *dev).slots > 0)) return 0;
     return flock::heatmap_workspace_bytes(n_frames, grid_w, grid_h);
 }
 
@@ -614,7 +614,7 @@ flock_status heatmap_frames(const float *density, int32_t n_frames, int32_t grid
     flock_status st = device_info(&dev);
     if (st != FLOCK_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const flock::HeatPlan plan = heatmap_plan(n_frames, grid_w, grid_h, *dev);
+    const flock::HeatPlan plan = heatmap_plan(grid_w, grid_h, *dev);
     const size_t need = plan.slots > 0 ? 0 : flock::heatmap_workspace_bytes(n_frames, grid_w, grid_h);
     if (workspace && workspace_bytes < need)
         return fail(FLOCK_ENOMEM, "workspace of %zu bytes < %zu needed", workspace_bytes, need);

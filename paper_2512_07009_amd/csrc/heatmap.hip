@@ -15,7 +15,7 @@
 //   degree       (sum of density over hot cells) / S (0 when S = 0).
 //
 // Design.  Grids whose int32 forest fits in LDS beside the component slots
-// (grid_w * grid_h <= 39,936 cells with 160 KiB; see plan_heatmap) take
+// (grid_w * grid_h <= 39,936 cells with 160 KiB) take
 // heat_frame_kernel, one workgroup per frame (described there).  Larger grids
 // take four tiled kernels:
 //   1. heat_tile_kernel, one 256-thread workgroup per 32 x 32 tile: loads the
@@ -115,9 +115,14 @@ __device__ __forceinline__ double ln_pos(float vf, const LnTable &t) {
     const int k = (int)((b >> 45) & (kLnBuckets - 1));
     const double m = __longlong_as_double((long long)((b & 0x000fffffffffffffull) | 0x3ff0000000000000ull));
     const double r = fma(m, t.inv_c[k], -1.0);
-    const double p =
-        r * (1.0 + r * (-0.5 + r * (1.0 / 3.0 + r * (-0.25 + r * (0.2 + r * (-1.0 / 6.0 + r * (1.0 / 7.0)))))));
-    return fma((double)e, 0.69314718055994530942, t.ln_c[k] + p);
+    // explicit fused steps: every kernel that sums logarithms gets the same bits
+    double p = fma(r, 1.0 / 7.0, -1.0 / 6.0);
+    p = fma(r, p, 0.2);
+    p = fma(r, p, -0.25);
+    p = fma(r, p, 1.0 / 3.0);
+    p = fma(r, p, -0.5);
+    p = fma(r, p, 1.0);
+    return fma((double)e, 0.69314718055994530942, fma(r, p, t.ln_c[k]));
 }
 
 struct TileGeom {
@@ -497,8 +502,12 @@ __host__ __device__ inline FrameLds frame_lds(int gw, int gh, bool spill) {
 template <int kFThreads, bool SPILL>
 __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int slots) {
     constexpr int kFWaves = kFThreads / 64;
+    // the sums' order is that of kSumWaves waves whatever the workgroup's size
+    // (a frame's bits do not depend on its batch): a wave of a smaller one adds
+    // the words of kShares such waves apart
+    constexpr int kSumWaves = 16, kShares = kSumWaves / kFWaves;
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double s_red[3][kFWaves];
+    __shared__ double s_red[3][kSumWaves];
     __shared__ uint32_t s_max[kFWaves];
     __shared__ int s_shift, s_ncomp, s_nq;
     __shared__ LnTable lnt;
@@ -536,7 +545,18 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int s
     int x = (64 * wave + lane) % gw;              // column of this lane's cell
     const int xstep = (64 * kFWaves) % gw;
     __syncthreads();
-    double s = 0.0, e = 0.0, hs = 0.0;
+    static_assert(kShares == 1 || (kShares == 2 && kFlight % 2 == 1), "the shares change places every kFlight words");
+    double s[kShares], e[kShares], hs[kShares];  // [k]: this wave's words of the next place k, k + kShares, ..
+#pragma unroll
+    for (int k = 0; k < kShares; ++k) s[k] = e[k] = hs[k] = 0.0;
+    auto change = [&] {
+        if constexpr (kShares == 2) {
+            const double t0 = s[0], t1 = e[0], t2 = hs[0];
+            s[0] = s[1], e[0] = e[1], hs[0] = hs[1];
+            s[1] = t0, e[1] = t1, hs[1] = t2;
+        }
+    };
+    bool changed = false;
     uint32_t mb = 0;
     for (int w0 = wave; w0 < l.words; w0 += kFWaves * kFlight) {
         double ln[kFlight];
@@ -548,10 +568,11 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int s
             const float d = v[u];
             v[u] = load(min(w + kFWaves * kFlight, l.words));
             const bool in = c < cells, hot = in & (d >= a.threshold), pos = in & (d > 0.0f);
-            s += pos ? (double)d : 0.0;
-            e += pos ? (double)d * ln[u] : 0.0;
+            constexpr int kLast = kShares - 1;
+            s[u & kLast] += pos ? (double)d : 0.0;
+            e[u & kLast] = fma(pos ? (double)d : 0.0, ln[u], e[u & kLast]);
             mb = max(mb, pos ? __float_as_uint(d) : 0u);
-            hs += hot ? (double)d : 0.0;
+            hs[u & kLast] += hot ? (double)d : 0.0;
             const uint64_t hm = __ballot(hot), r0 = __ballot(in & (x == 0));
             // first cells of the word's runs, and this lane's run's
             const uint64_t first = hm & ~((hm << 1) & ~r0);
@@ -564,17 +585,21 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int s
             x += xstep;
             x -= x >= gw ? gw : 0;
         }
+        change();
+        changed = !changed;
     }
-    s = wave_sum_dpp(s);
-    e = wave_sum_dpp(e);
-    hs = wave_sum_dpp(hs);
+    if (changed) change();
+#pragma unroll
+    for (int k = 0; k < kShares; ++k) {
+        const double ws = wave_sum_dpp(s[k]), we = wave_sum_dpp(e[k]), wh = wave_sum_dpp(hs[k]);
+        if (lane == 0) {
+            s_red[0][wave + kFWaves * k] = ws;
+            s_red[1][wave + kFWaves * k] = we;
+            s_red[2][wave + kFWaves * k] = wh;
+        }
+    }
     mb = wave_max_u(mb);
-    if (lane == 0) {
-        s_red[0][wave] = s;
-        s_red[1][wave] = e;
-        s_red[2][wave] = hs;
-        s_max[wave] = mb;
-    }
+    if (lane == 0) s_max[wave] = mb;
     if constexpr (SPILL) wait_memory();
     __syncthreads();
     // B (the queue is in the slots' space; pairs beyond it are joined in place)
@@ -619,12 +644,12 @@ __global__ __launch_bounds__(kFThreads) void heat_frame_kernel(HeatArgs a, int s
     if (tid == kFThreads - 1) {
         double S = 0.0, E = 0.0, HS = 0.0;
         uint32_t M = 0;
-        for (int w = 0; w < kFWaves; ++w) {
+        for (int w = 0; w < kSumWaves; ++w) {
             S += s_red[0][w];
             E += s_red[1][w];
             HS += s_red[2][w];
-            M = max(M, s_max[w]);
         }
+        for (int w = 0; w < kFWaves; ++w) M = max(M, s_max[w]);
         a.entropy[f] = S > 0.0 ? log(S) - E / S : 0.0;
         a.degree[f] = S > 0.0 ? HS / S : 0.0;
         const int Ex = M ? (int)((M >> 23) & 0xffu) - 127 : 0;
@@ -766,17 +791,14 @@ size_t heatmap_workspace_bytes(int32_t n_frames, int32_t grid_w, int32_t grid_h)
     return parts + (((size_t)n_frames * sizeof(int32_t) + 255) & ~(size_t)255);
 }
 
-// The frame-resident kernel's plan in `lds_limit` bytes of LDS, or no slots:
-// the tiled kernels, for grids that do not fit, and for a few frames of those
-// whose bit words do not, where the chip is left to a few workgroups: 240 x 160
-// cells, 8 frames: 26 us tiled and 57 here on smooth maps, 66 .. 88 and 84 ..
-// 107 on noisy ones; 16 frames: 30 and 57, 89 .. 147 and 84 .. 108; 128: 75
-// and 60, 238 .. 405 and 88 .. 146.
-constexpr int kSpillTiledFrames = 8;
-
-HeatPlan plan_heatmap(int32_t n_frames, int32_t grid_w, int32_t grid_h, size_t lds_limit) {
+// The frame-resident kernel's plan in `lds_limit` bytes of LDS, or no slots for
+// grids that do not fit (the tiled kernels).  The path depends on the grid
+// alone, since the two add a frame's sums in different orders: a few frames of
+// a grid near the limit would be faster tiled (240 x 160 cells, 8 frames: 26
+// against 57 us on smooth maps, 66 .. 88 against 84 .. 107 on noisy ones), many
+// are not (128: 75 against 60, 238 .. 405 against 88 .. 146).
+HeatPlan plan_heatmap(int32_t grid_w, int32_t grid_h, size_t lds_limit) {
     for (const bool spill : {false, true}) {
-        if (spill && n_frames <= kSpillTiledFrames) break;
         const size_t used = frame_lds(grid_w, grid_h, spill).bytes(0) + kFrameStaticLds;
         if (used + (spill ? kMinSpillSlots : kMinSlots) * 16 > lds_limit) continue;
         return {(int)std::min<size_t>((lds_limit - used) / 16, kMaxSlots), spill};

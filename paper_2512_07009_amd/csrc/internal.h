@@ -119,7 +119,7 @@ struct HeatPlan {
     int slots;
     bool spill;  // the frame's bit words wait in comp_mass
 };
-HeatPlan plan_heatmap(int32_t n_frames, int32_t grid_w, int32_t grid_h, size_t lds_limit);
+HeatPlan plan_heatmap(int32_t grid_w, int32_t grid_h, size_t lds_limit);
 hipError_t launch_heatmap(HeatArgs a, void *workspace, const HeatPlan &plan, int n_cus, hipStream_t stream);
 
 // ----------------------------------------------------------------------------

@@ -128,13 +128,25 @@ def test_more_components_than_slots_gpu(F, h, w, conn):
                                    (9, 235, 170)])
 def test_frame_kernel_limits_gpu(F, h, w, conn):
     """The largest grid whose bit words fit in LDS beside 256 slots (366 x
-    101), grids whose words do not (few frames of them take the tiled kernels),
-    the largest of the frame kernel (192 x 208, 96 slots) and one beyond it."""
+    101), grids whose words do not, the largest of the frame kernel (192 x 208,
+    96 slots) and one beyond it."""
     rng = np.random.default_rng(h + w)
     g = (rng.random((F, h, w)) * 1e-3).astype(np.float32)
     g[0] *= 0.2 + np.hypot(*np.meshgrid(np.linspace(-1, 1, w), np.linspace(-1, 1, h)))
     for q in (0.5, 0.9):
         check(g, 2.0, float(np.quantile(g, q)), conn, tag=f"{F}x{h}x{w} q{q}")
+
+
+@pytest.mark.parametrize("h,w", [(72, 128), (61, 97), (36, 64), (5, 7), (160, 240)])
+def test_frame_does_not_depend_on_its_batch_gpu(h, w):
+    """A frame alone, in a small batch and in one of more frames than compute
+    units (another workgroup size) gives the same bits."""
+    rng = np.random.default_rng(h)
+    g = (rng.random((300, h, w)) ** 4 * 1e-3).astype(np.float32)
+    thr = float(np.quantile(g, 0.8))
+    big, few, one = (run(g[:n], 2.0, thr, 8) for n in (300, 40, 1))
+    for k in big:
+        assert np.array_equal(big[k][:40], few[k]) and np.array_equal(big[k][:1], one[k]), k
 
 
 def test_deterministic_gpu(path):
