@@ -55,7 +55,8 @@ KERNEL_SOURCES = {
     "cluster": ["paper_2512_07009_amd/csrc/cluster.hip", "paper_2512_07009_amd/csrc/cluster_big.hip",
                 "paper_2512_07009_amd/csrc/cluster_common.h"],
     "density": ["paper_2512_07009_amd/csrc/density.hip"],
-    "heatmap": ["paper_2512_07009_amd/csrc/heatmap.hip", "paper_2512_07009_amd/csrc/cluster_common.h"],
+    "heatmap": ["paper_2512_07009_amd/csrc/heatmap.hip", "paper_2512_07009_amd/csrc/cluster_common.h",
+                "paper_2512_07009_amd/csrc/ln_table.h"],
     "roi": ["paper_2512_07009_amd/csrc/roi.hip"],
     "drinker": ["paper_2512_07009_amd/csrc/roi.hip"],
     "mask": ["paper_2512_07009_amd/csrc/mask.hip", "paper_2512_07009_amd/csrc/cluster_common.h"],

@@ -44,6 +44,7 @@
 
 #include "cluster_common.h"
 #include "internal.h"
+#include "ln_table.h"
 
 namespace flock {
 namespace {
@@ -73,6 +74,14 @@ __device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
     return v;
 }
 
+__device__ const LnTable kLnTable = make_ln_table();
+
+// Copied to LDS by the first 2 kLnBuckets threads; the caller syncs before use.
+__device__ __forceinline__ void ln_table_load(LnTable &t) {
+    const int k = threadIdx.x;
+    if (k < 2 * kLnBuckets) reinterpret_cast<double *>(&t)[k] = reinterpret_cast<const double *>(&kLnTable)[k];
+}
+
 // Natural log of a positive float in fp64, from a table of bucket centres:
 // v = m 2^e exactly (m in [1, 2)), c is the centre of m's bucket of width
 // 1/kLnBuckets, and ln v = e ln 2 + ln c + ln(1 + r) with r = m / c - 1,
@@ -80,35 +89,6 @@ __device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
 // through r^7 (truncation below 2^-67).  The absolute error is a few 1e-16
 // (ln 2 and the table entries are rounded to fp64; |e| <= 149), about the
 // library routine's, at a fraction of its instructions.
-constexpr int kLnBuckets = 128;
-struct LnTable {
-    double ln_c[kLnBuckets], inv_c[kLnBuckets];
-};
-
-// The table is a constant of the program: ln c = 2 atanh((c - 1) / (c + 1)) by
-// its series (z <= 1/3: the terms fall by 9 each, 20 of them pass below 2^-60).
-// Filling it with the library's log in every workgroup took about 1.5 us of
-// each.
-constexpr LnTable make_ln_table() {
-    LnTable t{};
-    for (int k = 0; k < kLnBuckets; ++k) {
-        const double c = 1.0 + ((double)k + 0.5) / kLnBuckets;
-        const double z = (c - 1.0) / (c + 1.0), z2 = z * z;
-        double sum = 0.0;
-        for (int i = 19; i >= 0; --i) sum = sum * z2 + 1.0 / (2 * i + 1);
-        t.ln_c[k] = 2.0 * z * sum;
-        t.inv_c[k] = 1.0 / c;
-    }
-    return t;
-}
-__device__ const LnTable kLnTable = make_ln_table();
-
-// Copied by the first 2 kLnBuckets threads; the caller syncs before use.
-__device__ __forceinline__ void ln_table_load(LnTable &t) {
-    const int k = threadIdx.x;
-    if (k < 2 * kLnBuckets) reinterpret_cast<double *>(&t)[k] = reinterpret_cast<const double *>(&kLnTable)[k];
-}
-
 __device__ __forceinline__ double ln_pos(float vf, const LnTable &t) {
     const uint64_t b = (uint64_t)__double_as_longlong((double)vf);
     const int e = (int)(b >> 52) - 1023;
