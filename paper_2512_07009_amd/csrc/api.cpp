@@ -354,6 +354,9 @@ flock_status density_run(const int32_t *xy, const int32_t *offsets, int32_t n_fr
     a.density = density;
     const flock::DensityPlan plan = flock::plan_density(a, dev->n_cus, workspace ? workspace_bytes : SIZE_MAX);
     if (plan.blocks > 0x7fffffffLL) return fail(FLOCK_EUNSUPPORTED, "batch too large for one launch");
+    if (plan.lds_bytes > dev->lds_per_block)
+        return fail(FLOCK_EUNSUPPORTED, "density kernel needs %zu bytes of LDS, the device has %zu", plan.lds_bytes,
+                    dev->lds_per_block);
     // a split launch keeps partial grids in the workspace
     const size_t need = plan.split > 1 ? (size_t)n_frames * plan.split * (size_t)grid_w * grid_h * sizeof(float) : 0;
     void *ws = workspace;
@@ -640,7 +643,7 @@ flock_status heatmap_frames(const float *density, int32_t n_frames, int32_t grid
     a.degree = degree;
     a.comp_cells = comp_cells;
     a.comp_mass = comp_mass;
-    err = flock::launch_heatmap(a, ws, plan, dev->n_cus, s);
+    err = flock::launch_heatmap(a, ws, plan, dev->n_cus, dev->lds_per_cu ? dev->lds_per_cu : dev->lds_per_block, s);
     if (!workspace && need > 0) {
         const hipError_t ferr = hipFreeAsync(ws, s);
         if (err == hipSuccess) err = ferr;

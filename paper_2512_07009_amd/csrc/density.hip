@@ -563,8 +563,8 @@ bool gather_geom(const DensityArgs &a, GatherGeom *gg) {
     return true;
 }
 
-// The direct path's scratch for regions of rm x rn tiles (at most 52 chunks
-// per bird for the instantiated shapes: 13 KiB per wave).
+// The direct path's scratch for regions of rm x rn tiles (at most 50 chunks
+// per bird for the shapes it takes: 12.5 KiB per wave).
 void direct_lds(GatherGeom *gg, int rm, int rn) {
     const int chunks = std::min(gg->ay.nc, 4 * rm) + std::min(gg->ax.nc, 4 * rn) + 2;
     gg->table_bytes = kGWaves * ((8 + 32 * 8 * chunks + 15) / 16 * 16);
@@ -805,6 +805,8 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
     p.rn = sh.rn;
     p.regions_y = (int)g.ry;
     p.regions_x = (int)g.rx;
+    if (!gg.ay.c) direct_lds(&gg, p.rm, p.rn);
+    p.lds_bytes = (size_t)gg.lds_bytes;
     const long long items = (long long)a.n_frames * g.ry * g.rx * p.split;
     const int per_wg = kGWaves / p.waves;
     if (items > 0xffffffffLL) {  // item numbers are 32 bits wide: refused by the caller's check of `blocks`
@@ -827,7 +829,7 @@ hipError_t launch_density(const DensityArgs &a, const DensityPlan &p, float *par
     hipError_t err = hipErrorInvalidValue;
 #define FLOCK_LAUNCH(TM, TN, DIRECT)                                                                              \
     hipLaunchKernelGGL((density_gather_kernel<TM, TN, DIRECT>), dim3((unsigned)p.blocks), dim3(kGThreads),        \
-                       (size_t)gg.lds_bytes, stream, a, gg, p.regions_y, p.regions_x, p.split, p.waves, items, partial)
+                       p.lds_bytes, stream, a, gg, p.regions_y, p.regions_x, p.split, p.waves, items, partial)
 #define FLOCK_GSHAPE(TM, TN)                                                                                      \
     if (p.rm == TM && p.rn == TN) {                                                                               \
         if (tables) FLOCK_LAUNCH(TM, TN, false);                                                                  \

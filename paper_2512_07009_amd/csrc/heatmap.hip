@@ -786,7 +786,7 @@ HeatPlan plan_heatmap(int32_t grid_w, int32_t grid_h, size_t lds_limit) {
     return {0, false};
 }
 
-hipError_t launch_heatmap(HeatArgs a, void *workspace, const HeatPlan &plan, int n_cus, hipStream_t stream) {
+hipError_t launch_heatmap(HeatArgs a, void *workspace, const HeatPlan &plan, int n_cus, size_t lds_per_cu, hipStream_t stream) {
     if (plan.slots > 0) {
         const size_t lds = frame_lds(a.grid_w, a.grid_h, plan.spill).bytes(plan.slots);
         const dim3 grid((unsigned)a.n_frames);
@@ -798,7 +798,7 @@ hipError_t launch_heatmap(HeatArgs a, void *workspace, const HeatPlan &plan, int
         // against 26.3; 256 x 256 x 144: 64 against 71)
         if (plan.spill)
             hipLaunchKernelGGL((heat_frame_kernel<1024, true>), grid, dim3(1024), lds, stream, a, plan.slots);
-        else if (a.n_frames > n_cus && 2 * (lds + kFrameStaticLds) <= 160 * 1024)
+        else if (a.n_frames > n_cus && 2 * (lds + kFrameStaticLds) <= lds_per_cu)
             hipLaunchKernelGGL((heat_frame_kernel<512, false>), grid, dim3(512), lds, stream, a, plan.slots);
         else
             hipLaunchKernelGGL((heat_frame_kernel<1024, false>), grid, dim3(1024), lds, stream, a, plan.slots);

@@ -79,6 +79,7 @@ struct DensityPlan {
     int split;                // bird slices per (frame, region); > 1 adds partial grids afterwards
     int waves;                // waves sharing one (frame, region, slice)
     long long blocks;         // workgroups of the main kernel
+    size_t lds_bytes;         // of each
 };
 
 // `room`: bytes there are for partial grids (SIZE_MAX: as many as a plan takes).
@@ -120,7 +121,7 @@ struct HeatPlan {
     bool spill;  // the frame's bit words wait in comp_mass
 };
 HeatPlan plan_heatmap(int32_t grid_w, int32_t grid_h, size_t lds_limit);
-hipError_t launch_heatmap(HeatArgs a, void *workspace, const HeatPlan &plan, int n_cus, hipStream_t stream);
+hipError_t launch_heatmap(HeatArgs a, void *workspace, const HeatPlan &plan, int n_cus, size_t lds_per_cu, hipStream_t stream);
 
 // ----------------------------------------------------------------------------
 // Region of interest
