@@ -754,8 +754,12 @@ size_t density_workspace_bytes(int32_t n_frames, int32_t total, int32_t grid_w, 
 
 // The launch plan of either path: region shape, waves per item and bird slices
 // of least modelled time.  FLOCK_DENSITY_SHAPE="rm,rn" forces the region shape
-// (for tuning).  The direct path needs no workspace: it takes slices only where
-// their partial grids fit in `room` bytes.
+// (for tuning).  Where `room` holds fewer partial grids than the slices want
+// there are fewer slices.  Room for less than two means none at all on grids
+// that never needed a workspace (cells of no whole number of quanta, windows of
+// more than kNeverSplit cells); on the others the caller refuses the plan.
+constexpr int kNeverSplit = 30;
+
 DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
     const char *force = std::getenv("FLOCK_DENSITY_SHAPE");
     GatherGeom gg;
@@ -775,13 +779,16 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
                 forced = true;
             }
     const GatherForce over = gather_force();
-    auto fits = [&](int slices) {
-        return gg.ay.c || slices <= 1 ||
-               (size_t)a.n_frames * slices * (size_t)a.grid_w * a.grid_h * sizeof(float) <= room;
+    auto limit = [&](int slices) {
+        const size_t most = room / ((size_t)a.n_frames * a.grid_w * a.grid_h * sizeof(float));
+        if (slices <= 1 || (size_t)slices <= most) return slices;
+        const bool optional = !gg.ay.c || std::max(gg.ay.j, gg.ax.j) > kNeverSplit;
+        if (over.split >= 1) return optional ? 1 : slices;
+        return most >= 2 ? (int)most : optional ? 1 : slices;
     };
     if (forced) {
         gather_split(a.n_frames, g.kept, g.ry * g.rx, n_cus, over, &p.waves, &p.split);
-        if (!fits(p.split)) p.split = 1;
+        p.split = limit(p.split);
     } else {
         // bird slices where they pay for the second kernel: a launch that
         // would leave most of the chip idle is bound by each wave's own
@@ -792,9 +799,11 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
         const GatherCost sg = gather_regions(ss, gg, a.grid_w, a.grid_h, birds);
         int sw = 1, sp = 1;
         gather_split(a.n_frames, sg.kept, sg.ry * sg.rx, n_cus, over, &sw, &sp);
-        if (fits(sp) && (over.split >= 1 || over.waves >= 1 ||
-                         (sp > 1 && gather_us(ss, sw, sp, gg, sg, a.n_frames, birds, n_cus) <
-                                        gather_us(sh, p.waves, 1, gg, g, a.n_frames, birds, n_cus)))) {
+        const int asked = sp;
+        sp = limit(sp);
+        if ((sp > 1 || asked == 1) && (over.split >= 1 || over.waves >= 1 ||
+                                       (sp > 1 && gather_us(ss, sw, sp, gg, sg, a.n_frames, birds, n_cus) <
+                                                      gather_us(sh, p.waves, 1, gg, g, a.n_frames, birds, n_cus)))) {
             sh = ss;
             g = sg;
             p.waves = sw;

@@ -558,6 +558,30 @@ def test_density_direct_path_takes_short_workspace_gpu():
     assert_density_close(out.cpu().numpy(), ref, np.diff(off), 30.0, tag="short workspace")
 
 
+def test_density_short_workspace_gpu():
+    """A workspace with room for fewer bird slices than a launch wants is used
+    for as many as it holds; with room for less than two, grids that were never
+    split (windows of more than 30 cells here) run without, others are refused."""
+    rng = np.random.default_rng(6)
+    n = 30000
+    xy, off = wl.pack([np.stack([rng.integers(0, 16 * 1920, n), rng.integers(0, 16 * 1080, n)], 1).astype(np.int32)])
+    dxy, doff = dev_batch(xy, off)
+    lib = flock.lib()
+    for gx, gy, sigma, grids, want in ((192, 108, 60.0, 0.5, 0), (192, 108, 60.0, 2.5, 0), (128, 72, 30.0, 2.5, 0),
+                                       (128, 72, 30.0, 1.5, flock.binding.FLOCK_ENOMEM)):
+        size = int(grids * gx * gy * 4) // 256 * 256
+        assert lib.density_frames_workspace(1, n, gx, gy) > size
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        out = torch.full((1, gy, gx), -1.0, dtype=torch.float32, device="cuda")
+        st = lib.density_frames(dxy.data_ptr(), doff.data_ptr(), 1, n, 0, 1920, 1080, gx, gy, sigma, out.data_ptr(),
+                                ws.data_ptr(), size, None)
+        assert st == want, (gx, grids, lib.flock_last_error().decode())
+        torch.cuda.synchronize()
+        if want == 0:
+            ref = oracle.density_frames(xy, off, 1920, 1080, gx, gy, sigma)
+            assert_density_close(out.cpu().numpy(), ref, np.diff(off), sigma, tag=f"{gx} x {gy}, {grids} grids")
+
+
 def test_density_single_bird_peak_gpu():
     sigma = 30.0
     # bird exactly at the centre of cell (40, 30) of a 128 x 72 grid on 1920 x 1080
