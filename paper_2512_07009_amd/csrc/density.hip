@@ -83,7 +83,7 @@ constexpr int kGStep = 32;                 // birds per MFMA k-step (16 x 16 x 3
 constexpr int kGRedTiles = 8;              // 16 x 16 tiles per round of the cross-wave sum
 constexpr int kGPair = 2;                  // blocks of 64 birds a wave tests at a time
 constexpr int kGAhead = 2;                 // pairs of blocks loaded ahead
-constexpr int kGRing = 256;                // staged birds per wave (one k-step left over + one pair of blocks)
+constexpr int kGRing = 160;                // staged birds per wave (under one k-step left over + one pair of blocks)
 constexpr int kGMaxLds = 159 * 1024;        // of a compute unit's 160 KiB
 constexpr int kGMaxTableBytes = kGMaxLds - kGWaves * kGRing * 16;  // both factor tables
 constexpr int kGMinWaveBirds = 32;         // kept birds per wave, at least, when a launch splits frames
@@ -344,7 +344,9 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
         const int32_t yoff = (row0 >> 2) + (lane & 3), xoff = (col0 >> 2) + (lane & 3);
         const int32_t y_lo = low(gg.ay, row0), x_lo = low(gg.ax, col0);
         const uint32_t y_n = span(gg.ay, 16 * TM, row0, y_lo), x_n = span(gg.ax, 16 * TN, col0, x_lo);
-        int32_t head = 0, tail = 0;  // ring positions, taken modulo kGRing
+        int32_t head = 0, staged = 0;  // the staged birds: ring positions from head on, modulo kGRing
+        static_assert(kGRing >= kGStep - 1 + 64 * kGPair && kGRing % kGStep == 0, "a step's birds are contiguous");
+        auto place = [&](int32_t p) { return p >= kGRing ? p - kGRing : p; };
         auto step = [&] {
             wave_sync();
             // every operand's reads are issued before the first MFMA (left to
@@ -354,7 +356,7 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
             if constexpr (DIRECT) {
                 // lane l: bird l % 32, axis y for l < 32, else x
                 const bool isx = lane >= 32;
-                const GBird e = ring[(head + (lane & 31)) & (kGRing - 1)];
+                const GBird e = ring[head + (lane & 31)];
                 const int32_t q = isx ? e.rb_x : e.rb_y;
                 const float h = isx ? gg.ax.h : gg.ay.h;
                 // a padding bird's factors are 0 whatever sigma and the distance
@@ -381,7 +383,7 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
                 operands<TN>(bx, LaneBirds{rx, xoff - fx0, rx + 4 * rowx, xoff - fx1}, ncx, lds);
                 operands<TM>(ay, LaneBirds{ry, yoff - fy0, ry + 4 * rowy, yoff - fy1}, ncy, lds);
             } else {
-                const GBird *sb = ring + (head & (kGRing - 1)) + bird;
+                const GBird *sb = ring + head + bird;
                 const int4 q0 = *reinterpret_cast<const int4 *>(sb), q1 = *reinterpret_cast<const int4 *>(sb + 4);
                 operands<TN>(bx, LaneBirds{q0.z, q0.w + xoff, q1.z, q1.w + xoff}, ncx, lds);
                 operands<TM>(ay, LaneBirds{q0.x, q0.y + yoff, q1.x, q1.y + yoff}, ncy, lds);
@@ -392,7 +394,8 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
                 for (int t = 0; t < TN; ++t)
                     acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ay[m], bx[t], acc[m][t], 0, 0, 0);
-            head += kGStep;
+            head = place(head + kGStep);
+            staged -= kGStep;
             wave_sync();  // the step's reads are done before the ring is written again
         };
         while (left > 0) {  // wave-uniform
@@ -419,16 +422,16 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
                             stage_axis(q[h].y, gg.ay, inv_cy, &gb.rb_y, &gb.g_y);
                             stage_axis(q[h].x, gg.ax, inv_cx, &gb.rb_x, &gb.g_x);
                         }
-                        ring[(tail + __popcll(m[h] & below)) & (kGRing - 1)] = gb;
+                        ring[place(head + staged + __popcll(m[h] & below))] = gb;
                     }
-                    tail += __popcll(m[h]);
+                    staged += __popcll(m[h]);
                 }
-                while (tail - head >= kGStep) step();
+                while (staged >= kGStep) step();
             }
         }
         // the last, partial step is filled with birds whose factors are all zero
-        if (tail > head) {
-            if (lane < kGStep && head + lane >= tail) ring[(head + lane) & (kGRing - 1)] = none;
+        if (staged > 0) {
+            if (lane < kGStep && lane >= staged) ring[head + lane] = none;
             step();
         }
 

@@ -496,6 +496,21 @@ def test_density_huge_sigma_gpu(sigma):
     assert_density_close(got, ref, tag=f"sigma {sigma}")
 
 
+@pytest.mark.parametrize("w,h,gx,gy,sigma,frames,n", [
+    (1920, 1080, 128, 72, 68.2, 3, 900),     # the widest windows whose tables fit (138 KiB)
+    (1920, 1080, 128, 72, 76.0, 2, 700),     # past them
+    (320, 176, 20, 11, 9.0, 3, 3000),        # every bird kept: the ring of staged birds wraps
+])
+def test_density_large_tables_gpu(w, h, gx, gy, sigma, frames, n):
+    """Tables that leave little LDS beside them, and the ring's wrap."""
+    rng = np.random.default_rng(gx + n)
+    xy, off = wl.pack([np.stack([rng.integers(0, 16 * w, k), rng.integers(0, 16 * h, k)], 1).astype(np.int32)
+                       for k in rng.integers(n // 2, n + 1, frames)])
+    got = run_density(xy, off, w, h, gx, gy, sigma)
+    ref = oracle.density_frames(xy, off, w, h, gx, gy, sigma)
+    assert_density_close(got, ref, np.diff(off), sigma, tag=f"{gx}x{gy} sigma {sigma}")
+
+
 @pytest.mark.parametrize("split", ["3", "16"])
 def test_density_bird_slices_gpu(split, monkeypatch):
     """Frames split into bird slices whose partial grids are added afterwards,
