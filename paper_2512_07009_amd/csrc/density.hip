@@ -107,6 +107,9 @@ struct GatherAxis {
     int32_t tab;    // byte offset of the table (its leading zero chunk) in LDS
     float h, inv_h; // cell size, px (direct path)
     float reach;    // window half-width, quanta, whatever j's limit (direct path)
+    // with k = -log2(e) / (2 s^2): 2 k h, k h^2 and exp2(2 k h^2), for steps of
+    // one cell where h <= 2 s (else step_q is 0)
+    float step_d, step_h, step_q;
 };
 
 struct GatherGeom {
@@ -354,31 +357,53 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
             half8 bx[TN], ay[TM];
             const int bird = 8 * grp + (r16 >> 2);  // this lane's two birds of the step: i / 4 and i / 4 + 4 of its group's eight
             if constexpr (DIRECT) {
-                // lane l: bird l % 32, axis y for l < 32, else x
-                const bool isx = lane >= 32;
+                // lanes l and l + 32 make bird l's factors, every other chunk of
+                // both axes each (an axis each leaves the lanes of the narrower
+                // window waiting: 460 frames of 4340 birds on 46 x 123 cells,
+                // windows of 8 and 19 cells either side, 152 us, now 96)
                 const GBird e = ring[head + (lane & 31)];
-                const int32_t q = isx ? e.rb_x : e.rb_y;
-                const float h = isx ? gg.ax.h : gg.ay.h;
                 // a padding bird's factors are 0 whatever sigma and the distance
-                const float pos = q == kGNone ? 0.0f : (float)q * 0.0625f, lift = q == kGNone ? -1.0e30f : 8.0f;
-                int first = isx ? col0 >> 2 : row0 >> 2;  // the row's first chunk, in chunks of the grid
-                if (!(isx ? whole_x : whole_y))
-                    first = ((int)floorf(pos * (isx ? gg.ax.inv_h : gg.ay.inv_h)) >> 2) - (isx ? gg.ax.j4 : gg.ay.j4);
-                unsigned char *row = lds + (isx ? scratch_x + (lane - 32) * rowx : scratch_y + lane * rowy);
-                const int nc = isx ? ncx : ncy;
-                float cell = (float)(4 * first) + 0.5f;
-                for (int k = 0; k < nc; ++k, cell += 4.0f) {
-                    half4 f;
+                const bool none = e.rb_y == kGNone;
+                const float lift = none ? -1.0e30f : 8.0f;  // 2^8 = kLift
+                const int half = lane >> 5;
+                auto make = [&](int32_t q, const GatherAxis &t, int first, bool whole, unsigned char *row, int nc, int k0) {
+                    const float pos = none ? 0.0f : (float)q * 0.0625f;
+                    if (!whole) first = ((int)floorf(pos * t.inv_h) >> 2) - t.j4;  // the row's first chunk, in chunks of the grid
+                    float cell = (float)(4 * (first + k0)) + 0.5f;
+                    if (t.step_q > 0.0f) {  // uniform
+                        // the factor and its ratio to the next cell's as exact
+                        // exponentials per chunk, the other three cells by
+                        // F(d + h) = F(d) R(d), R(d + h) = R(d) step_q.  (Far
+                        // off F is 0 and R is held finite; three cells further,
+                        // at most 6 s, F is still below fp16's range.)
+                        for (int k = k0; k < nc; k += 2, cell += 8.0f) {
+                            const float d = fmaf(cell, t.h, -pos);
+                            const float f0 = __builtin_amdgcn_exp2f(fmaf(d * d, gg.neg_k, lift));
+                            const float r0 = __builtin_amdgcn_exp2f(fminf(fmaf(d, t.step_d, t.step_h), 100.0f));
+                            const float r1 = r0 * t.step_q, r2 = r1 * t.step_q;
+                            const float f1 = f0 * r0, f2 = f1 * r1, f3 = f2 * r2;
+                            *reinterpret_cast<half4 *>(row + 8 * k) =
+                                half4{(_Float16)f0, (_Float16)f1, (_Float16)f2, (_Float16)f3};
+                        }
+                    } else {
+                        for (int k = k0; k < nc; k += 2, cell += 8.0f) {
+                            half4 f;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float d = fmaf(cell + (float)i, h, -pos);
-                        f[i] = (_Float16)__builtin_amdgcn_exp2f(fmaf(d * d, gg.neg_k, lift));  // 2^8 = kLift
+                            for (int i = 0; i < 4; ++i) {
+                                const float d = fmaf(cell + (float)i, t.h, -pos);
+                                f[i] = (_Float16)__builtin_amdgcn_exp2f(fmaf(d * d, gg.neg_k, lift));
+                            }
+                            *reinterpret_cast<half4 *>(row + 8 * k) = f;
+                        }
                     }
-                    *reinterpret_cast<half4 *>(row + 8 * k) = f;
-                }
+                    return first;
+                };
+                const int fy = make(e.rb_y, gg.ay, row0 >> 2, whole_y, lds + scratch_y + (lane & 31) * rowy, ncy, half);
+                const int fx = make(e.rb_x, gg.ax, col0 >> 2, whole_x, lds + scratch_x + (lane & 31) * rowx, ncx,
+                                    half ^ (ncy & 1));
                 wave_sync();
-                const int fy0 = __shfl(first, bird, 64), fy1 = __shfl(first, bird + 4, 64);
-                const int fx0 = __shfl(first, bird + 32, 64), fx1 = __shfl(first, bird + 36, 64);
+                const int fy0 = __shfl(fy, bird, 64), fy1 = __shfl(fy, bird + 4, 64);
+                const int fx0 = __shfl(fx, bird, 64), fx1 = __shfl(fx, bird + 4, 64);
                 const int ry = scratch_y + bird * rowy, rx = scratch_x + bird * rowx;
                 operands<TN>(bx, LaneBirds{rx, xoff - fx0, rx + 4 * rowx, xoff - fx1}, ncx, lds);
                 operands<TM>(ay, LaneBirds{ry, yoff - fy0, ry + 4 * rowy, yoff - fy1}, ncy, lds);
@@ -511,14 +536,16 @@ struct Shape {
 // tiles per region, so that the accumulators and operands fit the registers
 // of two waves per SIMD without spilling)
 constexpr int kDirectTiles = 32;  // the direct path's registers hold this many
+constexpr int kPairTiles = 8;     // and those of two workgroups per compute unit this many
 constexpr Shape kGShapes[] = {{1, 1}, {2, 2}, {1, 4}, {4, 1}, {2, 4}, {4, 2}, {3, 4},
                               {4, 4}, {5, 4}, {9, 2}, {9, 4}, {3, 8}, {4, 8}};
 
 // LDS beside the tables or scratch: the rings, whose space also holds the
-// cross-wave sum's tiles.
-void gather_lds(GatherGeom *gg) {
+// cross-wave sum's tiles (within `limit` bytes in all; two tiles of every wave
+// take no more than the rings).
+void gather_lds(GatherGeom *gg, int limit = kGMaxLds) {
     const int ring = kGWaves * kGRing * (int)sizeof(GBird), red = kGWaves * kGRedTiles * 1024;
-    gg->red_tiles = gg->table_bytes + red <= kGMaxLds ? kGRedTiles : 2;  // two tiles of every wave take the rings' space
+    gg->red_tiles = gg->table_bytes + red <= limit ? kGRedTiles : 2;
     gg->lds_bytes = gg->table_bytes + std::max(ring, gg->red_tiles == kGRedTiles ? red : 0);
 }
 
@@ -535,6 +562,10 @@ void gather_window(GatherAxis *t, int extent, int n, double sigma) {
     t->reach = (float)std::min(16.0 * j * h, 1.0e9);
     t->j4 = (t->j + 3) / 4;
     t->nc = 2 * t->j4 + 1;
+    const double k = -1.4426950408889634 / (2.0 * sigma * sigma);
+    t->step_d = (float)(2.0 * k * h);
+    t->step_h = (float)(k * h * h);
+    t->step_q = h <= 2.0 * sigma ? (float)std::exp2(2.0 * k * h * h) : 0.0f;
 }
 
 // Geometry of a launch.  Tables where a cell is a whole number of quanta on
@@ -568,10 +599,18 @@ bool gather_geom(const DensityArgs &a, GatherGeom *gg) {
 
 // The direct path's scratch for regions of rm x rn tiles (at most 50 chunks
 // per bird for the shapes it takes: 12.5 KiB per wave).
-void direct_lds(GatherGeom *gg, int rm, int rn) {
+void direct_lds(GatherGeom *gg, int rm, int rn, int resident) {
     const int chunks = std::min(gg->ay.nc, 4 * rm) + std::min(gg->ax.nc, 4 * rn) + 2;
     gg->table_bytes = kGWaves * ((8 + 32 * 8 * chunks + 15) / 16 * 16);
-    gather_lds(gg);
+    gather_lds(gg, kGMaxLds / resident);
+}
+
+// Workgroups that share a compute unit on the direct path: two where there are
+// that many and the registers (at most 128 up to kPairTiles tiles) and half the
+// LDS suffice, so that one's work fills the other's waits (585 frames of 3413
+// birds on 35 x 87 cells, regions of 2 x 4 tiles: 76 us against 96).
+int direct_resident(int rm, int rn, long long groups, int n_cus) {
+    return rm * rn <= kPairTiles && groups > n_cus ? 2 : 1;
 }
 
 // Share of a frame's birds whose window of 2 j + 1 cells meets one region
@@ -596,11 +635,11 @@ constexpr double kGroupUs = 1.0;    // a workgroup's start on an item group
 constexpr double kLaunchUs = 5.0;   // launch and table build
 constexpr double kSliceSumUs = 4.0; // the second kernel of a launch split into bird slices
 
-// A step of the direct path also makes its factors, by the longer of a lane's
-// two axes.
+// A step of the direct path also makes its factors, half of a bird's chunks per
+// lane.
 double step_us(const Shape &sh, const GatherGeom &gg) {
     const double us = 0.0135 * (sh.rm + sh.rn) + 0.0159 * sh.rm * sh.rn;
-    return gg.ay.c ? us : us + kChunkUs * std::max(std::min(gg.ay.nc, 4 * sh.rm), std::min(gg.ax.nc, 4 * sh.rn));
+    return gg.ay.c ? us : us + kChunkUs * 0.5 * (std::min(gg.ay.nc, 4 * sh.rm) + std::min(gg.ax.nc, 4 * sh.rn));
 }
 struct GatherCost {
     long long ry, rx;
@@ -817,10 +856,12 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
     p.rn = sh.rn;
     p.regions_y = (int)g.ry;
     p.regions_x = (int)g.rx;
-    if (!gg.ay.c) direct_lds(&gg, p.rm, p.rn);
-    p.lds_bytes = (size_t)gg.lds_bytes;
     const long long items = (long long)a.n_frames * g.ry * g.rx * p.split;
     const int per_wg = kGWaves / p.waves;
+    n_cus = std::max(n_cus, 1);
+    p.resident = gg.ay.c ? 1 : direct_resident(p.rm, p.rn, (items + per_wg - 1) / per_wg, n_cus);
+    if (!gg.ay.c) direct_lds(&gg, p.rm, p.rn, p.resident);
+    p.lds_bytes = (size_t)gg.lds_bytes;
     if (items > 0xffffffffLL) {  // item numbers are 32 bits wide: refused by the caller's check of `blocks`
         p.blocks = items;
         return p;
@@ -828,14 +869,14 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
     // a workgroup takes its share of the item groups one after another, with
     // one table build: 256 x 8000 with eight waves per item took 91 against
     // 103 us with a workgroup per group
-    p.blocks = std::min<long long>((items + per_wg - 1) / per_wg, std::max(n_cus, 1));
+    p.blocks = std::min<long long>((items + per_wg - 1) / per_wg, (long long)n_cus * p.resident);
     return p;
 }
 
 hipError_t launch_density(const DensityArgs &a, const DensityPlan &p, float *partial, hipStream_t stream) {
     GatherGeom gg;
     const bool tables = gather_geom(a, &gg);
-    if (!tables) direct_lds(&gg, p.rm, p.rn);
+    if (!tables) direct_lds(&gg, p.rm, p.rn, p.resident);
     if (p.split > 1 && !partial) return hipErrorInvalidValue;
     const uint32_t items = (uint32_t)((long long)a.n_frames * p.regions_y * p.regions_x * p.split);
     hipError_t err = hipErrorInvalidValue;

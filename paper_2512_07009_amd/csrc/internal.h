@@ -79,6 +79,7 @@ struct DensityPlan {
     int split;                // bird slices per (frame, region); > 1 adds partial grids afterwards
     int waves;                // waves sharing one (frame, region, slice)
     long long blocks;         // workgroups of the main kernel
+    int resident;             // of them per compute unit
     size_t lds_bytes;         // of each
 };
 

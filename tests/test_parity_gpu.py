@@ -511,6 +511,25 @@ def test_density_large_tables_gpu(w, h, gx, gy, sigma, frames, n):
     assert_density_close(got, ref, np.diff(off), sigma, tag=f"{gx}x{gy} sigma {sigma}")
 
 
+@pytest.mark.parametrize("w,h,gx,gy,sigma,frames,n", [
+    (1920, 1080, 35, 87, 35.4, 4, 900),      # 5 chunks of one axis, 11 of the other
+    (3840, 2160, 25, 182, 1208.0, 2, 500),   # whole regions far beyond the window
+    (1280, 720, 42, 24, 5.8, 300, 90),       # cells wider than 2 sigma: exponentials only
+    (1000, 700, 77, 53, 1000.0 / 77 / 2, 3, 900),  # 2 sigma is a cell of x, more than one of y
+    (1000, 700, 77, 53, 6.7, 3, 900),        # 2 sigma between the two
+    (1280, 720, 19, 12, 400.0, 600, 40),     # two workgroups per compute unit, in turns
+])
+def test_density_direct_factors_gpu(w, h, gx, gy, sigma, frames, n):
+    """The direct path's factors: windows of different widths on the two axes,
+    stepped from exact exponentials and not, birds outside the frame."""
+    rng = np.random.default_rng(gx * 100 + gy)
+    xy, off = wl.pack([np.stack([rng.integers(0, 16 * w + 999, k), rng.integers(0, 16 * h + 999, k)], 1).astype(np.int32)
+                       for k in rng.integers(n // 2, n + 1, frames)])
+    got = run_density(xy, off, w, h, gx, gy, sigma)
+    ref = oracle.density_frames(xy, off, w, h, gx, gy, sigma)
+    assert_density_close(got, ref, np.diff(off), sigma, tag=f"{gx}x{gy} sigma {sigma}")
+
+
 @pytest.mark.parametrize("split", ["3", "16"])
 def test_density_bird_slices_gpu(split, monkeypatch):
     """Frames split into bird slices whose partial grids are added afterwards,
