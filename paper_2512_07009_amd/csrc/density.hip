@@ -530,7 +530,7 @@ __global__ __launch_bounds__(256) void density_reduce_kernel(float *density, con
 }
 
 struct Shape {
-    int rm, rn;
+    int rm, rn;  // tiles of 16 x 16 cells
 };
 // instantiated region shapes (tiles of 16 x 16; at most 36
 // tiles per region, so that the accumulators and operands fit the registers
@@ -568,11 +568,8 @@ void gather_window(GatherAxis *t, int extent, int n, double sigma) {
     t->step_q = h <= 2.0 * sigma ? (float)std::exp2(2.0 * k * h * h) : 0.0f;
 }
 
-// Geometry of a launch.  Tables where a cell is a whole number of quanta on
-// both axes and they fit beside the rings; else the direct path, whose scratch
-// depends on the region shape (direct_lds).  FLOCK_DENSITY_PATH=recur takes
-// the direct path for every grid (for tests).
-bool gather_geom(const DensityArgs &a, GatherGeom *gg) {
+// Geometry of a launch on the direct path, but for its scratch (direct_lds).
+void base_geom(const DensityArgs &a, GatherGeom *gg) {
     const double s = (double)a.sigma_px;
     gather_window(&gg->ay, a.height_px, a.grid_h, s);
     gather_window(&gg->ax, a.width_px, a.grid_w, s);
@@ -580,8 +577,11 @@ bool gather_geom(const DensityArgs &a, GatherGeom *gg) {
     gg->scale = (float)(1.0 / (2.0 * 3.14159265358979323846 * s * s) / ((double)kLift * kLift));
     gg->ay.c = gg->ax.c = 0;
     gg->ay.tab = gg->ax.tab = 0;
-    const char *path = std::getenv("FLOCK_DENSITY_PATH");
-    if (path && std::strcmp(path, "recur") == 0) return false;
+}
+
+// Makes it the geometry of the table path where a cell is a whole number of
+// quanta on both axes and the tables fit beside the rings.
+bool table_geom(const DensityArgs &a, GatherGeom *gg) {
     if ((16LL * a.height_px) % a.grid_h != 0 || (16LL * a.width_px) % a.grid_w != 0) return false;
     const int64_t cy = 16LL * a.height_px / a.grid_h, cx = 16LL * a.width_px / a.grid_w;
     auto bytes = [](int64_t c, const GatherAxis &t) { return (8 + 4 * c * table_row_bytes(t) + 15) / 16 * 16; };
@@ -616,94 +616,113 @@ int direct_resident(int rm, int rn, long long groups, int n_cus) {
 // Share of a frame's birds whose window of 2 j + 1 cells meets one region
 // of `rows` grid rows, `nreg` regions along the axis: about 1 + 2 j / rows
 // regions per bird, at most all of them.
-double meet_share(int j, int rows, long long nreg) {
+double meet_share(int j, int rows, int nreg) {
     return std::min((double)nreg, 1.0 + 2.0 * j / rows) / (double)nreg;
 }
 
 long long axis_regions(int grid_n, int rows) { return (grid_n + rows - 1) / rows; }
 
-// The gather kernel's cost model, in microseconds of one wave beside the
-// other of its SIMD (least squares over 40 measured plans of 64 x 2000 and
-// 1800 x 5000 birds on 128 x 72 grids and 256 x 8000 on 256 x 144: 4% mean
-// error, 9% at most).  A 32-bird k-step costs its tile reads and its MFMAs,
-// which did not overlap; every block of 64 birds costs its test on each
-// region.
-constexpr double kChunkUs = 0.113;  // four factors per lane on the direct path
-constexpr double kBlockUs = 0.335;  // a 64-bird block's test and staging
-constexpr double kTileUs = 0.11;    // a tile's sum over an item's waves
-constexpr double kGroupUs = 1.0;    // a workgroup's start on an item group
+// The kernel's cost model, in microseconds of one wave beside the other of its
+// SIMD.  A 32-bird k-step costs its tile reads and its MFMAs, which did not
+// overlap, and on the direct path its factors, half of a bird's chunks per lane;
+// every block of 64 birds costs its test and staging on each region.  Table path:
+// least squares over 52 plans each of 244 batches (1 .. 1800 frames of 20 ..
+// 30000 birds, even and in groups; the plan it picks takes 2% more than the
+// fastest of the 52 on average); direct path: over 40 plans of three batches.
+struct PathCost {
+    double group;        // a workgroup's start on an item group
+    double edge, tile;   // a step's reads per row or column of tiles, its MFMAs per tile
+    double chunk;        // its factors, per chunk of four
+    double block, sum;   // a 64-bird block; a tile's sum over an item's waves
+    double uneven;       // the fullest region of a single round against the average
+};
+constexpr PathCost kTableCost = {0.66, 0.0261, 0.014, 0.0, 0.258, 0.116, 1.035};
+constexpr PathCost kDirectCost = {1.0, 0.0135, 0.0159, 0.113, 0.335, 0.11, 1.25};
 constexpr double kLaunchUs = 5.0;   // launch and table build
 constexpr double kSliceSumUs = 4.0; // the second kernel of a launch split into bird slices
 
-// A step of the direct path also makes its factors, half of a bird's chunks per
-// lane.
-double step_us(const Shape &sh, const GatherGeom &gg) {
-    const double us = 0.0135 * (sh.rm + sh.rn) + 0.0159 * sh.rm * sh.rn;
-    return gg.ay.c ? us : us + kChunkUs * 0.5 * (std::min(gg.ay.nc, 4 * sh.rm) + std::min(gg.ax.nc, 4 * sh.rn));
-}
+// A shape on a grid: its regions, the birds an item keeps on average, and what
+// a step costs it.
 struct GatherCost {
     long long ry, rx;
-    double kept;  // birds an item keeps, on average
+    double kept, step;
+    const PathCost *path;
 };
 
 GatherCost gather_regions(const Shape &sh, const GatherGeom &gg, int grid_w, int grid_h, double birds) {
     GatherCost g;
     g.ry = axis_regions(grid_h, 16 * sh.rm);
     g.rx = axis_regions(grid_w, 16 * sh.rn);
-    g.kept = birds * meet_share(gg.ay.j, 16 * sh.rm, g.ry) * meet_share(gg.ax.j, 16 * sh.rn, g.rx);
+    g.kept = birds * meet_share(gg.ay.j, 16 * sh.rm, (int)g.ry) * meet_share(gg.ax.j, 16 * sh.rn, (int)g.rx);
+    const PathCost &c = *(g.path = gg.ay.c ? &kTableCost : &kDirectCost);
+    g.step = c.edge * (sh.rm + sh.rn) + c.tile * sh.rm * sh.rn +
+             c.chunk * 0.5 * (std::min(gg.ay.nc, 4 * sh.rm) + std::min(gg.ax.nc, 4 * sh.rn));
     return g;
+}
+
+long long item_groups(const GatherCost &g, int waves, int split, long long n_frames) {
+    return (n_frames * g.ry * g.rx * split * waves + kGWaves - 1) / kGWaves;
 }
 
 // Modelled time of a launch with `waves` waves per item and `split` bird
 // slices.  A compute unit runs one workgroup at a time and takes its share of
 // the item groups in turn; one round of workgroups ends with its fullest
-// region (about 1.25 times the average unless all eight waves share each
-// region).
-double gather_us(const Shape &sh, int waves, int split, const GatherGeom &gg, const GatherCost &g,
-                 long long n_frames, double birds, int n_cus) {
-    const long long items = n_frames * g.ry * g.rx * split, groups = (items * waves + kGWaves - 1) / kGWaves;
-    const long long cus = std::max(n_cus, 1);
-    const double rounds = groups <= 4 * cus ? (double)((groups + cus - 1) / cus) : (double)groups / cus;
-    const double uneven = rounds == 1.0 && waves < kGWaves ? 1.25 : 1.0;
-    const double units = (double)waves * split, steps = g.kept * uneven / (kGStep * units) + 0.5;
+// region (unless all eight waves share each region).
+double gather_us(const Shape &sh, int waves, int split, const GatherCost &g, long long n_frames, double birds, int n_cus) {
+    const PathCost &c = *g.path;
+    const long long groups = item_groups(g, waves, split, n_frames);
+    const double share = (double)groups / n_cus;
+    const double rounds = groups <= 4LL * n_cus ? (double)((groups + n_cus - 1) / n_cus) : share;
+    const double per = 1.0 / (double)(waves * split);
+    const double steps = g.kept * (rounds == 1.0 && waves < kGWaves ? c.uneven : 1.0) * (1.0 / kGStep) * per + 0.5;
     return kLaunchUs + (split > 1 ? kSliceSumUs : 0.0) +
-           rounds * (kGroupUs + steps * step_us(sh, gg) + std::max(birds / (64.0 * units), 1.0) * kBlockUs +
-                     (waves > 1 ? kTileUs * sh.rm * sh.rn : 0.0));
+           rounds * (c.group + steps * g.step + std::max(birds * (1.0 / 64.0) * per, 1.0) * c.block +
+                     (waves > 1 ? c.sum * sh.rm * sh.rn : 0.0));
 }
 
-// Region shape and waves per item of least modelled time.
-Shape gather_shape(const GatherGeom &gg, int grid_w, int grid_h, long long n_frames, double birds, int n_cus,
-                   int *waves) {
-    Shape best = kGShapes[0];
-    double best_us = 1e300;
+// Region shape and waves per item of least modelled time.  For a batch whose
+// clustering (a compute unit per frame of about a thousand birds and more) takes
+// an eighth to half of the chip, a plan of one round that leaves it room is
+// preferred where it is within kNearly of the best: a program that runs both at
+// once otherwise waits for whichever finds the chip full (64 x 2000 birds on 128 x
+// 72 cells, the whole step on two streams: 1.524M frames/s with 192 workgroups,
+// 1.493M with 256, joined after every step 1.370M and 1.305M; this call alone
+// 10.2 and 9.9 us).
+constexpr double kNearly = 1.1;
+
+struct Choice {
+    Shape shape;
+    GatherCost cost;
+    int waves;
+    double us;
+};
+
+Choice gather_shape(const GatherGeom &gg, int grid_w, int grid_h, long long n_frames, double birds, int n_cus) {
+    Choice best{}, beside{};
+    best.us = beside.us = 1e300;
+    const bool room = gg.ay.c && birds >= 1000.0 && 8 * n_frames >= n_cus && 2 * n_frames <= n_cus;
     for (const Shape &sh : kGShapes) {
         if (!gg.ay.c && sh.rm * sh.rn > kDirectTiles) continue;
         const GatherCost g = gather_regions(sh, gg, grid_w, grid_h, birds);
         for (int w = 1; w <= kGWaves; w *= 2) {
-            const double us = gather_us(sh, w, 1, gg, g, n_frames, birds, n_cus);
-            if (us < best_us * 0.999) {
-                best = sh;
-                *waves = w;
-                best_us = us;
-            }
+            const double us = gather_us(sh, w, 1, g, n_frames, birds, n_cus);
+            if (us < best.us * 0.999) best = {sh, g, w, us};
+            if (room && us < beside.us * 0.999 && item_groups(g, w, 1, n_frames) + n_frames <= n_cus) beside = {sh, g, w, us};
         }
     }
-    return best;
+    return beside.us <= kNearly * best.us ? beside : best;
 }
 
 // Region shape of a launch split into bird slices (at most 16 tiles, see
-// plan_density): least modelled work per frame, whatever its spread.
-Shape gather_split_shape(const GatherGeom &gg, int grid_w, int grid_h, double birds) {
-    Shape best = kGShapes[0];
-    double best_us = 1e300;
+// plan_path): least modelled work per frame, whatever its spread.
+Choice gather_split_shape(const GatherGeom &gg, int grid_w, int grid_h, double birds) {
+    Choice best{};
+    best.us = 1e300;
     for (const Shape &sh : kGShapes) {
         if (sh.rm * sh.rn > 16) continue;
         const GatherCost g = gather_regions(sh, gg, grid_w, grid_h, birds);
-        const double us = (g.kept / kGStep * step_us(sh, gg) + birds / 64.0 * kBlockUs + kGroupUs) * (double)(g.ry * g.rx);
-        if (us < best_us * 0.999) {
-            best = sh;
-            best_us = us;
-        }
+        const double us = (g.kept / kGStep * g.step + birds / 64.0 * g.path->block + g.path->group) * (double)(g.ry * g.rx);
+        if (us < best.us * 0.999) best = {sh, g, 1, us};
     }
     return best;
 }
@@ -794,74 +813,100 @@ size_t density_workspace_bytes(int32_t n_frames, int32_t total, int32_t grid_w, 
     return (size_t)n_frames * most * (size_t)grid_w * grid_h * sizeof(float);
 }
 
-// The launch plan of either path: region shape, waves per item and bird slices
-// of least modelled time.  FLOCK_DENSITY_SHAPE="rm,rn" forces the region shape
-// (for tuning).  Where `room` holds fewer partial grids than the slices want
-// there are fewer slices.  Room for less than two means none at all on grids
-// that never needed a workspace (cells of no whole number of quanta, windows of
-// more than kNeverSplit cells); on the others the caller refuses the plan.
+namespace {
+
+// Where `room` holds fewer partial grids than the slices want there are fewer
+// slices.  Room for less than two means none at all on grids that never needed
+// a workspace (cells of no whole number of quanta, windows of more than
+// kNeverSplit cells); on the others the caller refuses the plan.
 constexpr int kNeverSplit = 30;
 
-DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
-    const char *force = std::getenv("FLOCK_DENSITY_SHAPE");
-    GatherGeom gg;
-    gather_geom(a, &gg);
-    const double birds = a.n_frames > 0 ? (double)a.total / a.n_frames : 0.0;
-    DensityPlan p{};
-    p.split = 1;
-    Shape sh = gather_shape(gg, a.grid_w, a.grid_h, a.n_frames, birds, n_cus, &p.waves);
-    GatherCost g = gather_regions(sh, gg, a.grid_w, a.grid_h, birds);
-    int grm = 0, grn = 0;
-    bool forced = false;
-    if (force && std::sscanf(force, "%d,%d", &grm, &grn) == 2)
-        for (const Shape &k : kGShapes)
-            if (k.rm == grm && k.rn == grn && (gg.ay.c || grm * grn <= kDirectTiles)) {
-                sh = k;
-                g = gather_regions(sh, gg, a.grid_w, a.grid_h, birds);
-                forced = true;
-            }
-    const GatherForce over = gather_force();
+// The plan of one path: region shape, waves per item and bird slices of least
+// modelled time.
+struct PathPlan {
+    Choice c;
+    int split;
+};
+
+PathPlan plan_path(const DensityArgs &a, const GatherGeom &gg, bool whole, double birds, int n_cus, size_t room,
+                   const Shape *forced, const GatherForce &over) {
     auto limit = [&](int slices) {
         const size_t most = room / ((size_t)a.n_frames * a.grid_w * a.grid_h * sizeof(float));
         if (slices <= 1 || (size_t)slices <= most) return slices;
-        const bool optional = !gg.ay.c || std::max(gg.ay.j, gg.ax.j) > kNeverSplit;
+        const bool optional = !whole || std::max(gg.ay.j, gg.ax.j) > kNeverSplit;
         if (over.split >= 1) return optional ? 1 : slices;
         return most >= 2 ? (int)most : optional ? 1 : slices;
     };
-    if (forced) {
-        gather_split(a.n_frames, g.kept, g.ry * g.rx, n_cus, over, &p.waves, &p.split);
+    if (forced && (gg.ay.c || forced->rm * forced->rn <= kDirectTiles)) {
+        PathPlan p{{*forced, gather_regions(*forced, gg, a.grid_w, a.grid_h, birds), 1, 0.0}, 1};
+        gather_split(a.n_frames, p.c.cost.kept, p.c.cost.ry * p.c.cost.rx, n_cus, over, &p.c.waves, &p.split);
         p.split = limit(p.split);
-    } else {
-        // bird slices where they pay for the second kernel: a launch that
-        // would leave most of the chip idle is bound by each wave's own
-        // path, whose fixed part grows with the tiles an item's waves add
-        // up at the end (kGRedTiles per round); shapes of at most 16
-        // tiles keep that to two rounds
-        const Shape ss = gather_split_shape(gg, a.grid_w, a.grid_h, birds);
-        const GatherCost sg = gather_regions(ss, gg, a.grid_w, a.grid_h, birds);
-        int sw = 1, sp = 1;
-        gather_split(a.n_frames, sg.kept, sg.ry * sg.rx, n_cus, over, &sw, &sp);
-        const int asked = sp;
-        sp = limit(sp);
-        if ((sp > 1 || asked == 1) && (over.split >= 1 || over.waves >= 1 ||
-                                       (sp > 1 && gather_us(ss, sw, sp, gg, sg, a.n_frames, birds, n_cus) <
-                                                      gather_us(sh, p.waves, 1, gg, g, a.n_frames, birds, n_cus)))) {
-            sh = ss;
-            g = sg;
-            p.waves = sw;
-            p.split = sp;
-        }
+        return p;
     }
-    p.rm = sh.rm;
-    p.rn = sh.rn;
-    p.regions_y = (int)g.ry;
-    p.regions_x = (int)g.rx;
-    const long long items = (long long)a.n_frames * g.ry * g.rx * p.split;
-    const int per_wg = kGWaves / p.waves;
+    PathPlan p{gather_shape(gg, a.grid_w, a.grid_h, a.n_frames, birds, n_cus), 1};
+    // bird slices where they pay for the second kernel: a launch that would
+    // leave most of the chip idle is bound by each wave's own path, whose
+    // fixed part grows with the tiles an item's waves add up at the end
+    // (kGRedTiles per round); shapes of at most 16 tiles keep that to two
+    // rounds
+    PathPlan s{gather_split_shape(gg, a.grid_w, a.grid_h, birds), 1};
+    gather_split(a.n_frames, s.c.cost.kept, s.c.cost.ry * s.c.cost.rx, n_cus, over, &s.c.waves, &s.split);
+    const int asked = s.split;
+    s.split = limit(s.split);
+    s.c.us = gather_us(s.c.shape, s.c.waves, s.split, s.c.cost, a.n_frames, birds, n_cus);
+    if ((s.split > 1 || asked == 1) && (over.split >= 1 || over.waves >= 1 || (s.split > 1 && s.c.us < p.c.us))) return s;
+    return p;
+}
+
+}  // namespace
+
+// The launch plan.  The table path where its tables fit, but for launches of so
+// few steps (two per compute unit) that their exponentials cost less than a
+// table build of several passes: 127 birds in one frame of 96 x 54 cells, sigma
+// 45 px, 4.5 against 6.6 us, 2000 birds 6.6 and 7.6, 16 frames of 2000 (2500
+// steps) 9.3 and 9.0.
+// FLOCK_DENSITY_PATH=direct (or recur) and =table force the path where both
+// apply, FLOCK_DENSITY_SHAPE="rm,rn" the region shape (for tests and tuning).
+DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
     n_cus = std::max(n_cus, 1);
-    p.resident = gg.ay.c ? 1 : direct_resident(p.rm, p.rn, (items + per_wg - 1) / per_wg, n_cus);
-    if (!gg.ay.c) direct_lds(&gg, p.rm, p.rn, p.resident);
-    p.lds_bytes = (size_t)gg.lds_bytes;
+    const char *path = std::getenv("FLOCK_DENSITY_PATH"), *force = std::getenv("FLOCK_DENSITY_SHAPE");
+    const bool direct = path && (std::strcmp(path, "direct") == 0 || std::strcmp(path, "recur") == 0);
+    const GatherForce over = gather_force();
+    Shape given{};
+    bool forced = false;
+    if (force && std::sscanf(force, "%d,%d", &given.rm, &given.rn) == 2)
+        for (const Shape &k : kGShapes) forced |= k.rm == given.rm && k.rn == given.rn;
+    const double birds = a.n_frames > 0 ? (double)a.total / a.n_frames : 0.0;
+    GatherGeom gg;
+    base_geom(a, &gg);
+    GatherGeom tg = gg;
+    const bool whole = table_geom(a, &tg);
+    DensityPlan p{};
+    PathPlan pp{};
+    p.tables = whole && !direct;
+    if (p.tables) {
+        pp = plan_path(a, tg, whole, birds, n_cus, room, forced ? &given : nullptr, over);
+        // every thread makes two chunks of four rows per pass of a table build
+        const int passes = (tg.ay.c * ((tg.ay.nc + 2) / 2) + kGThreads - 1) / kGThreads;
+        const double steps = (double)a.n_frames * pp.c.cost.ry * pp.c.cost.rx * pp.c.cost.kept / kGStep;
+        if (!path && !forced && over.split < 1 && over.waves < 1 && passes > 1 && steps <= 2.0 * n_cus) {
+            pp = plan_path(a, gg, whole, birds, n_cus, room, nullptr, over);
+            p.tables = false;
+        }
+    } else {
+        pp = plan_path(a, gg, whole, birds, n_cus, room, forced ? &given : nullptr, over);
+    }
+    p.rm = pp.c.shape.rm;
+    p.rn = pp.c.shape.rn;
+    p.regions_y = (int)pp.c.cost.ry;
+    p.regions_x = (int)pp.c.cost.rx;
+    p.waves = pp.c.waves;
+    p.split = pp.split;
+    const long long items = (long long)a.n_frames * p.regions_y * p.regions_x * p.split;
+    const int per_wg = kGWaves / p.waves;
+    p.resident = p.tables ? 1 : direct_resident(p.rm, p.rn, (items + per_wg - 1) / per_wg, n_cus);
+    if (!p.tables) direct_lds(&gg, p.rm, p.rn, p.resident);
+    p.lds_bytes = (size_t)(p.tables ? tg : gg).lds_bytes;
     if (items > 0xffffffffLL) {  // item numbers are 32 bits wide: refused by the caller's check of `blocks`
         p.blocks = items;
         return p;
@@ -875,8 +920,9 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
 
 hipError_t launch_density(const DensityArgs &a, const DensityPlan &p, float *partial, hipStream_t stream) {
     GatherGeom gg;
-    const bool tables = gather_geom(a, &gg);
-    if (!tables) direct_lds(&gg, p.rm, p.rn, p.resident);
+    base_geom(a, &gg);
+    if (!p.tables) direct_lds(&gg, p.rm, p.rn, p.resident);
+    else if (!table_geom(a, &gg)) return hipErrorInvalidValue;
     if (p.split > 1 && !partial) return hipErrorInvalidValue;
     const uint32_t items = (uint32_t)((long long)a.n_frames * p.regions_y * p.regions_x * p.split);
     hipError_t err = hipErrorInvalidValue;
@@ -885,7 +931,7 @@ hipError_t launch_density(const DensityArgs &a, const DensityPlan &p, float *par
                        p.lds_bytes, stream, a, gg, p.regions_y, p.regions_x, p.split, p.waves, items, partial)
 #define FLOCK_GSHAPE(TM, TN)                                                                                      \
     if (p.rm == TM && p.rn == TN) {                                                                               \
-        if (tables) FLOCK_LAUNCH(TM, TN, false);                                                                  \
+        if (p.tables) FLOCK_LAUNCH(TM, TN, false);                                                                  \
         else if (TM * TN <= kDirectTiles) FLOCK_LAUNCH(TM, TN, (TM * TN <= kDirectTiles));                         \
         else return hipErrorInvalidValue;                                                                         \
         err = hipGetLastError();                                                                                  \

@@ -74,6 +74,7 @@ struct DensityArgs {
 };
 
 struct DensityPlan {
+    bool tables;              // factors from tables, else evaluated (density.hip)
     int rm, rn;               // region height and width in tiles of 16 x 16 cells
     int regions_y, regions_x; // regions per frame
     int split;                // bird slices per (frame, region); > 1 adds partial grids afterwards

@@ -530,6 +530,22 @@ def test_density_direct_factors_gpu(w, h, gx, gy, sigma, frames, n):
     assert_density_close(got, ref, np.diff(off), sigma, tag=f"{gx}x{gy} sigma {sigma}")
 
 
+@pytest.mark.parametrize("path", [None, "direct", "table"])
+@pytest.mark.parametrize("frames,n", [(1, 1), (1, 127), (4, 238), (1, 2000), (16, 2000), (64, 200), (64, 2000)])
+def test_density_path_choice_gpu(frames, n, path, monkeypatch):
+    """Launches at both sides of the choice between building tables and
+    evaluating the factors, and of the plan that leaves compute units for the
+    batch's clustering, by either path and by the plan's own choice."""
+    if path:
+        monkeypatch.setenv("FLOCK_DENSITY_PATH", path)
+    rng = np.random.default_rng(frames + n)
+    xy, off = wl.pack([np.stack([rng.integers(0, 16 * 1920, n), rng.integers(0, 16 * 1080, n)], 1).astype(np.int32)
+                       for _ in range(frames)])
+    got = run_density(xy, off, 1920, 1080, 96, 54, 44.7)
+    ref = oracle.density_frames(xy, off, 1920, 1080, 96, 54, 44.7)
+    assert_density_close(got, ref, np.diff(off), 44.7, tag=f"{frames} x {n} {path}")
+
+
 @pytest.mark.parametrize("split", ["3", "16"])
 def test_density_bird_slices_gpu(split, monkeypatch):
     """Frames split into bird slices whose partial grids are added afterwards,
