@@ -27,7 +27,9 @@
  *  Errors: a negative status; flock_last_error() then describes it.  On
  *  FLOCK_EINVAL nothing is enqueued and the outputs are untouched.  A frame
  *  whose offsets are inconsistent (negative count, past total) is never read;
- *  its outputs are left untouched and its n_clusters entry is set to -1.
+ *  its outputs are left untouched and its n_clusters entry is set to -1 (so is
+ *  that of a frame above the on-chip capacity whose birds cannot all be told
+ *  from another, inconsistent frame's).
  *  Thread safety: calls on different streams may run concurrently; the only
  *  global state is a per-thread error string and a once-initialised cache of
  *  device properties.
@@ -132,8 +134,16 @@ size_t cluster_frames_workspace(int32_t n_frames, int32_t total, int32_t max_fra
  *   workspace             as for cluster_frames, sized by
  *                         density_frames_workspace(...).  Batches with few
  *                         frames are split into bird slices whose partial
- *                         grids are kept there and added in slice order.
- * The result is deterministic (fixed summation order).  Frames whose offsets
+ *                         grids are kept there and added in slice order.  A
+ *                         shorter workspace holds fewer slices; one that holds
+ *                         less than two is taken, without slices, on grids
+ *                         whose cells are no whole number of 1/16 px or whose
+ *                         6-sigma windows reach more than 29 cells, and
+ *                         refused (FLOCK_ENOMEM) where another grid's launch
+ *                         wants slices.
+ * The result is deterministic (fixed summation order; the order, and with it
+ * the last bits, depends on the slices, so on a workspace shorter than the
+ * query's).  Frames whose offsets
  * are invalid (checked only with FLOCK_VALIDATE) leave their grid unspecified.
  */
 flock_status density_frames(const int32_t *xy, const int32_t *offsets, int32_t n_frames,
@@ -152,7 +162,8 @@ size_t density_frames_workspace(int32_t n_frames, int32_t total, int32_t grid_w,
  * harnesses that forbid allocation.
  *
  * Arguments, result and accuracy are those of density_frames (the same plan
- * and kernels, so the same bits), without the workspace: a launch split into
+ * and kernels, so the same bits as with a NULL workspace or one of the queried
+ * size), without the workspace: a launch split into
  * bird slices keeps its partial grids in a static scratch array of the
  * library, 16 MiB per device (n_frames * slices * grid_w * grid_h * 4 bytes;
  * density_frames_workspace() gives that size for a batch shape).  The call

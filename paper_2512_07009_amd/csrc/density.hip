@@ -30,27 +30,29 @@
 // with no packing, no tile writes and no barriers.  (Reading a 32-bit factor
 // pair per lane and bird instead, as before, took eight clamped reads and
 // eight byte permutes for every two tiles: 256 x 8000 birds on 256 x 144
-// cells 143 us, now 79; 64 x 2000 on 128 x 72 17.2, now 11.1.)  What bounds
-// it now: a 32-bird step's reads and MFMAs do not overlap (28 and 21 of the
-// 79 us), the per-block bird test and staging (17 us), and launch, table
-// build and final sum (13 us).
+// cells 143 us, now 78; 64 x 2000 on 128 x 72 17.0, now 10.2.)  What bounds
+// it now: the matrix cores are busy 26% of the launch on the former (55 GFLOP
+// issued) and 2.4% on the latter; the rest is what a 32-bird step's reads, which
+// do not overlap its MFMAs, the per-block bird test and staging, and launch,
+// table build and final sum take.
 // Waves sharing a frame region add their tiles in a fixed order at the end;
 // batches with few (frame, region) pairs also split frames into bird slices
 // whose partial grids a second kernel adds in slice order.
 //
 // Direct path (any other grid, and windows too wide for the tables).  The same
-// kernel, with the 32 birds of a k-step evaluated instead of looked up: each
-// lane takes one bird and axis, writes the factors of its window (or of the
-// whole region, where that is smaller) as exact exponentials into a row of its
-// wave's own LDS scratch, and the operands are read from there as above.
-// (Before, 128 birds at a time were written as columns of cleared LDS tiles by
-// a recurrence between barriers: 48 ragged frames of up to 3000 birds on a
-// 97 x 61 grid took 38 us, now 23.6.)  Bound by the exponentials, about 36
-// per lane and step at a window of 27 cells.
+// kernel, with the 32 birds of a k-step evaluated instead of looked up: two
+// lanes take a bird, write the factors of its windows (or of the whole region,
+// where that is smaller) into rows of their wave's own LDS scratch, and the
+// operands are read from there as above.  Each chunk of four cells starts from
+// exact exponentials.  (Before, 128 birds at a time were written as columns of
+// cleared LDS tiles by a recurrence between barriers: 48 ragged frames of up to
+// 3000 birds on a 97 x 61 grid took 38 us, now 15.5.)  Bound by the factors:
+// about 18 exponentials per lane and step at windows of 27 cells.
 //
 // Accuracy: a normal fp16 factor (f >= 2^-22) carries a relative rounding
 // error <= 2^-11 (plus a few fp32 ulps before the conversion); a subnormal
-// one an absolute error <= 2^-25 of 2^8 f, i.e. 2^-33 of f.  A term is a
+// one an absolute error <= 2^-25 of 2^8 f, i.e. 2^-33 of f.  (Stepping three
+// cells on adds at most 2^-17 of f.)  A term is a
 // product of two factors <= 1, so its error is <= about 2^-10 of the term plus
 // 2^-32 absolute; all terms are positive, so an output's error is <= 2^-10 of
 // the output plus N 2^-32 c for N birds (c = 1 / (2 pi s^2)), against an

@@ -475,8 +475,8 @@ __host__ __device__ inline FrameLds frame_lds(int gw, int gh, bool spill) {
 // the label cells out of its zeros.
 //
 // Bound by latency: the chain of phases on one compute unit per frame.
-// 64 frames of 128 x 72 cells 23.8 us, 256 of 256 x 144 64, 1800 of 128 x 72
-// 115 (33.2, 124 and 161 when the logarithm table was computed by every
+// 64 frames of 128 x 72 cells 23.1 us, 256 of 256 x 144 61, 600 of 128 x 72
+// 55 (31.5, 102 and 69 when the logarithm table was computed by every
 // workgroup, loads came one at a time, every cell tested its own joins, masses
 // were added by global atomics and a second kernel converted them).
 template <int kFThreads, bool SPILL>

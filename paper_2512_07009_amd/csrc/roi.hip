@@ -137,9 +137,9 @@ __device__ QueuedTest(WaveQueue &, int, int, Exact) -> QueuedTest<Exact>;
 // a wall; those are queued and tested.  The kept birds then go, in input order,
 // to the block's staging area (coordinates and input index), for the write
 // kernel to copy to their final places without reading every bird again.
-// Bound by HBM: 1800 x 5000 birds, 14% kept, move 72 + 1 + 16 MB in 25.9
-// us; one queue per block between four barriers, with a byte per flag, took
-// 30.2.
+// Bound by HBM: 1800 x 5000 birds, 14% kept, move 72 + 1 + 16 MB in 28.8 us
+// (27.8 at best); one queue per block between four barriers, with a byte per
+// flag, took some 4 us more.
 __global__ __launch_bounds__(kRThreadsR) void roi_flag_kernel(RoiArgs a, uint64_t *flag, int32_t *bcount,
                                                              int2 *stage_xy, int32_t *stage_idx) {
     __shared__ int2 poly[kRoiMaxVertices];
@@ -225,7 +225,10 @@ __global__ __launch_bounds__(1024) void roi_scan_kernel(const int32_t *bcount, i
 // Each block's kept birds, staged in input order by the flag kernel, go to
 // base + rank.  Up to kRSelfScan blocks a block adds up the counts before it
 // itself (at most 32 reads a thread, from L2) and leaves its base for the
-// counts kernel; beyond that the scan kernel has made the bases.
+// counts kernel; beyond that the scan kernel has made the bases.  The whole call
+// with own sums and with the scan kernel: 64 blocks 12.3 and 14.3 us, 4096 38.2
+// and 41.0, 8192 65.5 and 72.2, 16384 135.6 and 141.0, 24576 226.6 and 212.4 (the
+// own sums' work grows with the square of the blocks).
 constexpr int kRSelfScan = 8192;
 
 __global__ __launch_bounds__(kRThreadsR) void roi_write_kernel(RoiArgs a, const int32_t *bcount, int32_t *bbase, int nb,
@@ -390,8 +393,8 @@ __device__ __forceinline__ bool near_segment(int4 s, int px, int py, long long t
 // so birds outside all widened boxes (most of them, for lines across the frame)
 // are not drinking; the others are queued and tested exactly.  The wave's
 // results wait in LDS as one byte per bird and leave in full lines.
-// Bound by HBM: 1800 x 5000 birds move 72 + 45 MB in 29.6 us (33.0 with
-// one queue per block and stores by the birds' own lanes).
+// Bound by HBM: 1800 x 5000 birds move 72 + 45 MB in 27.9 us (some 3 us more
+// with one queue per block and stores by the birds' own lanes).
 __global__ __launch_bounds__(kRThreadsR) void drink_flag_kernel(DrinkArgs a, int32_t *bcount) {
     __shared__ int4 seg[kDrinkMaxLines];
     __shared__ int4 box[kDrinkMaxLines];  // x0, y0, x1, y1 widened by T

@@ -437,7 +437,7 @@ def test_density_input_order_path_gpu(max_fp):
     (1920, 1080, 128, 72, 30.0, 20), (3840, 2160, 512, 288, 20.0, 3), (3840, 2160, 256, 144, 45.0, 6),
 ])
 def test_density_paths_gpu(path, w, h, gx, gy, sigma, frames, monkeypatch):
-    """Both ways of making the factor tiles (exact tables / recurrence) agree with the oracle."""
+    """Both ways of making the factor tiles (exact tables / evaluated per step) agree with the oracle."""
     monkeypatch.setenv("FLOCK_DENSITY_PATH", path)
     xy, off = wl.random_batch(gx + frames, frames, 1500, width_px=w, height_px=h)
     got = run_density(xy, off, w, h, gx, gy, sigma)
