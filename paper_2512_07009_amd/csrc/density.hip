@@ -627,10 +627,10 @@ long long axis_regions(int grid_n, int rows) { return (grid_n + rows - 1) / rows
 // The kernel's cost model, in microseconds of one wave beside the other of its
 // SIMD.  A 32-bird k-step costs its tile reads and its MFMAs, which did not
 // overlap, and on the direct path its factors, half of a bird's chunks per lane;
-// every block of 64 birds costs its test and staging on each region.  Table path:
-// least squares over 52 plans each of 244 batches (1 .. 1800 frames of 20 ..
-// 30000 birds, even and in groups; the plan it picks takes 2% more than the
-// fastest of the 52 on average); direct path: over 40 plans of three batches.
+// every block of 64 birds costs its test and staging on each region.  Least
+// squares over 40 plans of three batches; on 244 others (1 .. 1800 frames of 20
+// .. 30000 birds, even and in groups, 52 plans each) the plan it picks on the
+// table path takes 2% more than the fastest on average.
 struct PathCost {
     double group;        // a workgroup's start on an item group
     double edge, tile;   // a step's reads per row or column of tiles, its MFMAs per tile
@@ -638,7 +638,7 @@ struct PathCost {
     double block, sum;   // a 64-bird block; a tile's sum over an item's waves
     double uneven;       // the fullest region of a single round against the average
 };
-constexpr PathCost kTableCost = {0.66, 0.0261, 0.014, 0.0, 0.258, 0.116, 1.035};
+constexpr PathCost kTableCost = {1.0, 0.0135, 0.0159, 0.0, 0.335, 0.11, 1.25};
 constexpr PathCost kDirectCost = {1.0, 0.0135, 0.0159, 0.113, 0.335, 0.11, 1.25};
 constexpr double kLaunchUs = 5.0;   // launch and table build
 constexpr double kSliceSumUs = 4.0; // the second kernel of a launch split into bird slices
@@ -690,7 +690,7 @@ double gather_us(const Shape &sh, int waves, int split, const GatherCost &g, lon
 // 72 cells, the whole step on two streams: 1.524M frames/s with 192 workgroups,
 // 1.493M with 256, joined after every step 1.370M and 1.305M; this call alone
 // 10.2 and 9.9 us).
-constexpr double kNearly = 1.1;
+constexpr double kNearly = 1.14;  // the model holds such plans' regions for less even than most are
 
 struct Choice {
     Shape shape;
@@ -863,10 +863,10 @@ PathPlan plan_path(const DensityArgs &a, const GatherGeom &gg, bool whole, doubl
 }  // namespace
 
 // The launch plan.  The table path where its tables fit, but for launches of so
-// few steps (two per compute unit) that their exponentials cost less than a
-// table build of several passes: 127 birds in one frame of 96 x 54 cells, sigma
-// 45 px, 4.5 against 6.6 us, 2000 birds 6.6 and 7.6, 16 frames of 2000 (2500
-// steps) 9.3 and 9.0.
+// few steps (two per compute unit, no slices) that their exponentials cost less
+// than a table build of several passes: on 96 x 54 cells, sigma 45 px, 127 birds
+// in one frame 4.5 against 6.6 us, 16 frames of 200 (300 steps) 5.1 and 6.9, 16 of
+// 2000 (2500 steps) 9.3 and 9.0; 8000 birds in one frame, split, 11.4 and 9.7.
 // FLOCK_DENSITY_PATH=direct (or recur) and =table force the path where both
 // apply, FLOCK_DENSITY_SHAPE="rm,rn" the region shape (for tests and tuning).
 DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
@@ -891,7 +891,7 @@ DensityPlan plan_density(const DensityArgs &a, int n_cus, size_t room) {
         // every thread makes two chunks of four rows per pass of a table build
         const int passes = (tg.ay.c * ((tg.ay.nc + 2) / 2) + kGThreads - 1) / kGThreads;
         const double steps = (double)a.n_frames * pp.c.cost.ry * pp.c.cost.rx * pp.c.cost.kept / kGStep;
-        if (!path && !forced && over.split < 1 && over.waves < 1 && passes > 1 && steps <= 2.0 * n_cus) {
+        if (!path && !forced && over.split < 1 && over.waves < 1 && passes > 1 && pp.split == 1 && steps <= 2.0 * n_cus) {
             pp = plan_path(a, gg, whole, birds, n_cus, room, nullptr, over);
             p.tables = false;
         }
