@@ -631,15 +631,13 @@ long long axis_regions(int grid_n, int rows) { return (grid_n + rows - 1) / rows
 // squares over 40 plans of three batches; on 244 others (1 .. 1800 frames of 20
 // .. 30000 birds, even and in groups, 52 plans each) the plan it picks on the
 // table path takes 2% more than the fastest on average.
-struct PathCost {
-    double group;        // a workgroup's start on an item group
-    double edge, tile;   // a step's reads per row or column of tiles, its MFMAs per tile
-    double chunk;        // its factors, per chunk of four
-    double block, sum;   // a 64-bird block; a tile's sum over an item's waves
-    double uneven;       // the fullest region of a single round against the average
-};
-constexpr PathCost kTableCost = {1.0, 0.0135, 0.0159, 0.0, 0.335, 0.11, 1.25};
-constexpr PathCost kDirectCost = {1.0, 0.0135, 0.0159, 0.113, 0.335, 0.11, 1.25};
+constexpr double kGroupUs = 1.0;    // a workgroup's start on an item group
+constexpr double kEdgeUs = 0.0135;  // a step's reads per row or column of tiles
+constexpr double kMfmaUs = 0.0159;  // its MFMAs per tile
+constexpr double kChunkUs = 0.113;  // its factors on the direct path, per chunk of four
+constexpr double kBlockUs = 0.335;  // a 64-bird block
+constexpr double kTileUs = 0.11;    // a tile's sum over an item's waves
+constexpr double kUneven = 1.25;    // the fullest region of a single round against the average
 constexpr double kLaunchUs = 5.0;   // launch and table build
 constexpr double kSliceSumUs = 4.0; // the second kernel of a launch split into bird slices
 
@@ -648,7 +646,6 @@ constexpr double kSliceSumUs = 4.0; // the second kernel of a launch split into 
 struct GatherCost {
     long long ry, rx;
     double kept, step;
-    const PathCost *path;
 };
 
 GatherCost gather_regions(const Shape &sh, const GatherGeom &gg, int grid_w, int grid_h, double birds) {
@@ -656,9 +653,8 @@ GatherCost gather_regions(const Shape &sh, const GatherGeom &gg, int grid_w, int
     g.ry = axis_regions(grid_h, 16 * sh.rm);
     g.rx = axis_regions(grid_w, 16 * sh.rn);
     g.kept = birds * meet_share(gg.ay.j, 16 * sh.rm, (int)g.ry) * meet_share(gg.ax.j, 16 * sh.rn, (int)g.rx);
-    const PathCost &c = *(g.path = gg.ay.c ? &kTableCost : &kDirectCost);
-    g.step = c.edge * (sh.rm + sh.rn) + c.tile * sh.rm * sh.rn +
-             c.chunk * 0.5 * (std::min(gg.ay.nc, 4 * sh.rm) + std::min(gg.ax.nc, 4 * sh.rn));
+    g.step = kEdgeUs * (sh.rm + sh.rn) + kMfmaUs * sh.rm * sh.rn;
+    if (!gg.ay.c) g.step += kChunkUs * 0.5 * (std::min(gg.ay.nc, 4 * sh.rm) + std::min(gg.ax.nc, 4 * sh.rn));
     return g;
 }
 
@@ -671,15 +667,14 @@ long long item_groups(const GatherCost &g, int waves, int split, long long n_fra
 // the item groups in turn; one round of workgroups ends with its fullest
 // region (unless all eight waves share each region).
 double gather_us(const Shape &sh, int waves, int split, const GatherCost &g, long long n_frames, double birds, int n_cus) {
-    const PathCost &c = *g.path;
     const long long groups = item_groups(g, waves, split, n_frames);
     const double share = (double)groups / n_cus;
     const double rounds = groups <= 4LL * n_cus ? (double)((groups + n_cus - 1) / n_cus) : share;
     const double per = 1.0 / (double)(waves * split);
-    const double steps = g.kept * (rounds == 1.0 && waves < kGWaves ? c.uneven : 1.0) * (1.0 / kGStep) * per + 0.5;
+    const double steps = g.kept * (rounds == 1.0 && waves < kGWaves ? kUneven : 1.0) * (1.0 / kGStep) * per + 0.5;
     return kLaunchUs + (split > 1 ? kSliceSumUs : 0.0) +
-           rounds * (c.group + steps * g.step + std::max(birds * (1.0 / 64.0) * per, 1.0) * c.block +
-                     (waves > 1 ? c.sum * sh.rm * sh.rn : 0.0));
+           rounds * (kGroupUs + steps * g.step + std::max(birds * (1.0 / 64.0) * per, 1.0) * kBlockUs +
+                     (waves > 1 ? kTileUs * sh.rm * sh.rn : 0.0));
 }
 
 // Region shape and waves per item of least modelled time.  For a batch whose
@@ -723,7 +718,7 @@ Choice gather_split_shape(const GatherGeom &gg, int grid_w, int grid_h, double b
     for (const Shape &sh : kGShapes) {
         if (sh.rm * sh.rn > 16) continue;
         const GatherCost g = gather_regions(sh, gg, grid_w, grid_h, birds);
-        const double us = (g.kept / kGStep * g.step + birds / 64.0 * g.path->block + g.path->group) * (double)(g.ry * g.rx);
+        const double us = (g.kept / kGStep * g.step + birds / 64.0 * kBlockUs + kGroupUs) * (double)(g.ry * g.rx);
         if (us < best.us * 0.999) best = {sh, g, 1, us};
     }
     return best;
