@@ -680,11 +680,13 @@ double gather_us(const Shape &sh, int waves, int split, const GatherCost &g, lon
 // Region shape and waves per item of least modelled time.  For a batch whose
 // clustering (a compute unit per frame of about a thousand birds and more) takes
 // an eighth to half of the chip, a plan of one round that leaves it room is
-// preferred where it is within kNearly of the best: a program that runs both at
-// once otherwise waits for whichever finds the chip full (64 x 2000 birds on 128 x
-// 72 cells, the whole step on two streams: 1.524M frames/s with 192 workgroups,
-// 1.493M with 256, joined after every step 1.370M and 1.305M; this call alone
-// 10.2 and 9.9 us).
+// preferred where it is within kNearly of the best and that one leaves less than
+// half the room (47 frames of 7488 birds on 192 x 108 cells: 23.8 us with 212
+// workgroups, 33.5 with 209 at most): a program that runs both at once otherwise
+// waits for whichever finds the chip full (64 x 2000 birds on 128 x 72 cells, the
+// whole step on two streams: 1.524M frames/s with 192 workgroups, 1.493M with
+// 256, joined after every step 1.370M and 1.305M; this call alone 10.2 and 9.9
+// us).
 constexpr double kNearly = 1.14;  // the model holds such plans' regions for less even than most are
 
 struct Choice {
@@ -707,7 +709,8 @@ Choice gather_shape(const GatherGeom &gg, int grid_w, int grid_h, long long n_fr
             if (room && us < beside.us * 0.999 && item_groups(g, w, 1, n_frames) + n_frames <= n_cus) beside = {sh, g, w, us};
         }
     }
-    return beside.us <= kNearly * best.us ? beside : best;
+    const bool crowds = 2 * (n_cus - item_groups(best.cost, best.waves, 1, n_frames)) < n_frames;
+    return crowds && beside.us <= kNearly * best.us ? beside : best;
 }
 
 // Region shape of a launch split into bird slices (at most 16 tiles, see
