@@ -210,7 +210,7 @@ __device__ __forceinline__ void operands(half8 (&op)[T], const LaneBirds &b, int
 // ranks), and runs a k-step whenever 32 are staged; the last step is padded
 // with birds whose factors are all zero.  No barrier is needed until the
 // final sum.
-template <int TM, int TN, bool DIRECT>
+template <int TM, int TN, bool DIRECT, bool AXES>
 __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) void density_gather_kernel(
     DensityArgs a, GatherGeom gg, int regions_y, int regions_x, int split, int waves, uint32_t items, float *partial) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
     const int r16 = lane & 15, grp = lane >> 4;
     // direct path: a factor row holds the bird's window, or all of the
     // region's chunks where those are fewer
-    const bool whole_y = DIRECT && gg.ay.nc >= 4 * TM, whole_x = DIRECT && gg.ax.nc >= 4 * TN;
+    const bool whole_y = DIRECT && !AXES && gg.ay.nc >= 4 * TM, whole_x = DIRECT && !AXES && gg.ax.nc >= 4 * TN;
     const int32_t ncy = whole_y ? 4 * TM : gg.ay.nc, ncx = whole_x ? 4 * TN : gg.ax.nc;
     // a bird in cell G meets rows [row0, row0 + 16 TM) when
     // row0 - j <= G <= row0 + 16 TM - 1 + j, i.e. when its quantum q lies in
@@ -362,23 +362,25 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
                 // lanes l and l + 32 make bird l's factors, every other chunk of
                 // both axes each (an axis each leaves the lanes of the narrower
                 // window waiting: 460 frames of 4340 birds on 46 x 123 cells,
-                // windows of 8 and 19 cells either side, 152 us, now 96)
+                // windows of 8 and 19 cells either side, 152 us, now 96); or,
+                // with AXES, an axis each
                 const GBird e = ring[head + (lane & 31)];
                 // a padding bird's factors are 0 whatever sigma and the distance
                 const bool none = e.rb_y == kGNone;
                 const float lift = none ? -1.0e30f : 8.0f;  // 2^8 = kLift
                 const int half = lane >> 5;
-                auto make = [&](int32_t q, const GatherAxis &t, int first, bool whole, unsigned char *row, int nc, int k0) {
+                auto make = [&](int32_t q, const GatherAxis &t, int first, bool whole, unsigned char *row, int nc, int k0,
+                                int dk) {
                     const float pos = none ? 0.0f : (float)q * 0.0625f;
                     if (!whole) first = ((int)floorf(pos * t.inv_h) >> 2) - t.j4;  // the row's first chunk, in chunks of the grid
                     float cell = (float)(4 * (first + k0)) + 0.5f;
-                    if (t.step_q > 0.0f) {  // uniform
+                    if (t.step_q > 0.0f) {
                         // the factor and its ratio to the next cell's as exact
                         // exponentials per chunk, the other three cells by
                         // F(d + h) = F(d) R(d), R(d + h) = R(d) step_q.  (Far
                         // off F is 0 and R is held finite; three cells further,
                         // at most 6 s, F is still below fp16's range.)
-                        for (int k = k0; k < nc; k += 2, cell += 8.0f) {
+                        for (int k = k0; k < nc; k += dk, cell += (float)(4 * dk)) {
                             const float d = fmaf(cell, t.h, -pos);
                             const float f0 = __builtin_amdgcn_exp2f(fmaf(d * d, gg.neg_k, lift));
                             const float r0 = __builtin_amdgcn_exp2f(fminf(fmaf(d, t.step_d, t.step_h), 100.0f));
@@ -388,7 +390,7 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
                                 half4{(_Float16)f0, (_Float16)f1, (_Float16)f2, (_Float16)f3};
                         }
                     } else {
-                        for (int k = k0; k < nc; k += 2, cell += 8.0f) {
+                        for (int k = k0; k < nc; k += dk, cell += (float)(4 * dk)) {
                             half4 f;
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {
@@ -400,12 +402,19 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2))) 
                     }
                     return first;
                 };
-                const int fy = make(e.rb_y, gg.ay, row0 >> 2, whole_y, lds + scratch_y + (lane & 31) * rowy, ncy, half);
-                const int fx = make(e.rb_x, gg.ax, col0 >> 2, whole_x, lds + scratch_x + (lane & 31) * rowx, ncx,
-                                    half ^ (ncy & 1));
+                unsigned char *to_y = lds + scratch_y + (lane & 31) * rowy, *to_x = lds + scratch_x + (lane & 31) * rowx;
+                int fy, fx;
+                if constexpr (AXES) {
+                    const GatherAxis t = half ? gg.ax : gg.ay;
+                    fy = fx = make(half ? e.rb_x : e.rb_y, t, 0, false, half ? to_x : to_y, ncy, 0, 1);
+                } else {
+                    fy = make(e.rb_y, gg.ay, row0 >> 2, whole_y, to_y, ncy, half, 2);
+                    fx = make(e.rb_x, gg.ax, col0 >> 2, whole_x, to_x, ncx, half ^ (ncy & 1), 2);
+                }
                 wave_sync();
+                const int from_x = bird + (AXES ? 32 : 0);
                 const int fy0 = __shfl(fy, bird, 64), fy1 = __shfl(fy, bird + 4, 64);
-                const int fx0 = __shfl(fx, bird, 64), fx1 = __shfl(fx, bird + 4, 64);
+                const int fx0 = __shfl(fx, from_x, 64), fx1 = __shfl(fx, from_x + 4, 64);
                 const int ry = scratch_y + bird * rowy, rx = scratch_x + bird * rowx;
                 operands<TN>(bx, LaneBirds{rx, xoff - fx0, rx + 4 * rowx, xoff - fx1}, ncx, lds);
                 operands<TM>(ay, LaneBirds{ry, yoff - fy0, ry + 4 * rowy, yoff - fy1}, ncy, lds);
@@ -926,13 +935,21 @@ hipError_t launch_density(const DensityArgs &a, const DensityPlan &p, float *par
     if (p.split > 1 && !partial) return hipErrorInvalidValue;
     const uint32_t items = (uint32_t)((long long)a.n_frames * p.regions_y * p.regions_x * p.split);
     hipError_t err = hipErrorInvalidValue;
-#define FLOCK_LAUNCH(TM, TN, DIRECT)                                                                              \
-    hipLaunchKernelGGL((density_gather_kernel<TM, TN, DIRECT>), dim3((unsigned)p.blocks), dim3(kGThreads),        \
+    // Lanes of an axis each where both windows have the same number of chunks (an
+    // odd one; halves of both would take one chunk more): 120 frames of 16664 birds
+    // on 29 x 27 cells, windows of 3 chunks, 29.4 us against 33.2.  An instance of its
+    // own: beside the other form in one kernel it made the shortest launches wait
+    // for more code (4.9 to 5.3 us).
+    const bool axes = !p.tables && gg.ay.nc == gg.ax.nc && gg.ay.nc < 4 * p.rm && gg.ax.nc < 4 * p.rn;
+#define FLOCK_LAUNCH(TM, TN, DIRECT, AXES)                                                                        \
+    hipLaunchKernelGGL((density_gather_kernel<TM, TN, DIRECT, AXES>), dim3((unsigned)p.blocks), dim3(kGThreads),  \
                        p.lds_bytes, stream, a, gg, p.regions_y, p.regions_x, p.split, p.waves, items, partial)
 #define FLOCK_GSHAPE(TM, TN)                                                                                      \
     if (p.rm == TM && p.rn == TN) {                                                                               \
-        if (p.tables) FLOCK_LAUNCH(TM, TN, false);                                                                  \
-        else if (TM * TN <= kDirectTiles) FLOCK_LAUNCH(TM, TN, (TM * TN <= kDirectTiles));                         \
+        constexpr bool kDirect = TM * TN <= kDirectTiles;                                                         \
+        if (p.tables) FLOCK_LAUNCH(TM, TN, false, false);                                                         \
+        else if (kDirect && axes) FLOCK_LAUNCH(TM, TN, kDirect, kDirect);                                         \
+        else if (kDirect) FLOCK_LAUNCH(TM, TN, kDirect, false);                                                   \
         else return hipErrorInvalidValue;                                                                         \
         err = hipGetLastError();                                                                                  \
     }

@@ -530,6 +530,20 @@ def test_density_direct_factors_gpu(w, h, gx, gy, sigma, frames, n):
     assert_density_close(got, ref, np.diff(off), sigma, tag=f"{gx}x{gy} sigma {sigma}")
 
 
+@pytest.mark.parametrize("shape", ["1,1", "2,2", "1,4", "4,1", "2,4", "4,2", "3,4", "4,4", "5,4", "9,2", "3,8", "4,8"])
+@pytest.mark.parametrize("sigma", [5.0, 13.0, 22.0])
+def test_density_equal_windows_gpu(shape, sigma, monkeypatch):
+    """Grids off the quanta whose windows are 3, 5 and 7 chunks on both axes:
+    below a region's chunks, where lanes take an axis each, and not."""
+    monkeypatch.setenv("FLOCK_DENSITY_SHAPE", shape)
+    rng = np.random.default_rng(int(sigma))
+    xy, off = wl.pack([np.stack([rng.integers(0, 16 * 1000, k), rng.integers(0, 16 * 700, k)], 1).astype(np.int32)
+                       for k in (600, 1, 0, 333)])
+    got = run_density(xy, off, 1000, 700, 77, 53, sigma)
+    ref = oracle.density_frames(xy, off, 1000, 700, 77, 53, sigma)
+    assert_density_close(got, ref, np.diff(off), sigma, tag=f"{shape} sigma {sigma}")
+
+
 @pytest.mark.parametrize("path", [None, "direct", "table"])
 @pytest.mark.parametrize("frames,n", [(1, 1), (1, 127), (4, 238), (1, 2000), (16, 2000), (64, 200), (64, 2000)])
 def test_density_path_choice_gpu(frames, n, path, monkeypatch):
